@@ -321,9 +321,9 @@ int stencil_coeff_field_adjoint(stencil_dtype dtype, const stencil_field* u, con
                                 const stencil_options* opts, hipStream_t stream);
 
 /* ------------------------------------------------------------- batched */
-/* Many independent fields of uneven sizes in one persistent launch (each
- * field is its own stencil call in the sense of Sec. 2.2; the batch only
- * shares the launch).  Every item obeys the rules of the single-field call
+/* Many independent fields of uneven sizes in a few launches (each field is
+ * its own stencil call in the sense of Sec. 2.2; the batch only shares the
+ * launches).  Every item obeys the rules of the single-field call
  * it stands for, and additionally no output of one item may overlap any
  * buffer of another (all items run concurrently): STENCIL_E_ALIAS.
  * Limits: n <= 1024 items, nk <= 144 per item (STENCIL_E_UNSUPPORTED), the
@@ -357,23 +357,22 @@ size_t stencil_batch_workspace_bytes(stencil_dtype dtype, int n, const stencil_b
 size_t stencil_batch_adjoint_workspace_bytes(stencil_dtype dtype, int n,
                                              const stencil_batch_adjoint_item* items);
 
-/* All n steps in one persistent launch (FP64: two, one for the fields with
- * columns of up to 80 levels, one for the longer ones, which run tiles of
- * tile_i x (128 / tile_i) columns).  opts->tile_i, when set, is the tile of
+/* All n steps in one launch per register class of the column length (up to
+ * three: FP64 up to 80, 96 and 144 levels, FP32 up to 80, 112 and 144; tiles
+ * of tile_i x (256 / tile_i) columns, in the longer classes 128 / tile_i).  opts->tile_i, when set, is the tile of
  * every field; when 0 each field takes its size class's tuned tile, or
  * without one the width (64, 32 or 16) that leaves the fewest lanes idle
  * on its ragged edges.  The call sorts the items longest
  * column first, writes the work list into `ws` with small copy kernels on
  * `stream` (stream-ordered, so the call can be captured into a graph), and
- * launches the kernel(s), whose workgroups pull (field, tile) work items from a
- * device counter in `ws` until none are left.  ws: device memory, 256-byte
+ * launches the kernels, one workgroup per (field, tile).  ws: device memory, 256-byte
  * aligned, at least stencil_batch_workspace_bytes(...) bytes, not
  * overlapping any field (STENCIL_E_WORKSPACE / STENCIL_E_ALIAS); two calls
  * that may run at the same time need distinct workspaces. */
 int stencil_step_batched(stencil_dtype dtype, int n, const stencil_batch_item* items, void* ws,
                          size_t ws_bytes, const stencil_options* opts, hipStream_t stream);
-/* The adjoints of a batch: one persistent launch for the column adjoints
- * (work items: field, 64x4 column tile), then one launch for the horizontal
+/* The adjoints of a batch: one launch per register class for the column
+ * adjoints (up to 96 levels, and longer), then one launch for the horizontal
  * gathers with a workgroup per work item (field, four strips of the padded
  * domain, level; a strip is 60 x 8 points in FP64, 124 x 12 in FP32).  ws as for the forward, sized by
  * stencil_batch_adjoint_workspace_bytes; opts->tile_i is not used. */

@@ -55,7 +55,7 @@ def _units():
                       [f"-DGT4MI_T={t}", "-DGT4MI_VADV", f"-DGT4MI_COL={col}", *UNROLL]))
             u.append(("k_vadj_inst.hip", f"vadj_{t}_c{col}", [f"-DGT4MI_T={t}", f"-DGT4MI_COL={col}", *UNROLL]))
         u.append(("k_batched.hip", f"batched_{t}",
-                  [f"-DGT4MI_T={t}", *(["-DGT4MI_UPLOAD"] if t == "float" else ["-DGT4MI_BATCHED_LONG"]),
+                  [f"-DGT4MI_T={t}", *(["-DGT4MI_UPLOAD"] if t == "float" else []),
                    *UNROLL]))
     for src in ("k_adjoint.hip", "k_halo.hip", "k_hdiff.hip", "k_param.hip", "k_plain.hip", "k_step.hip", "noalloc.hip",
                 "api.cpp", "tune.cpp",

@@ -81,7 +81,7 @@ AdjArgs<T> adj_args(const stencil_field* xbar, const stencil_field* w, T* lam, i
                     int64_t l_sk, stencil_field* ubar, const int64_t* dom, double coeff,
                     double dt_dz, const void* mask);
 
-// persistent batched forward (batched.cpp).  ItemSpans: the buffers one
+// batched forward (batched.cpp).  ItemSpans: the buffers one
 // item reads and writes.  check_step_batch validates the arguments and
 // every item (not the workspace); launch_step_batch runs a validated,
 // non-empty batch with its work list in ws (at least

@@ -1,9 +1,9 @@
-// batched.cpp -- the C ABI of the persistent batched launches: per-item
-// validation (the single-field rules plus no output of one field touching
-// any buffer of another, since all fields run concurrently), the work list
-// (fields sorted longest column first, prefix sums of their work items) and
-// its upload into the caller's workspace, then one persistent launch per
-// kernel.  Workspace layout, each part 256-byte aligned:
+// batched.cpp -- the C ABI of the batched launches: per-item validation (the
+// single-field rules plus no output of one field touching any buffer of
+// another, since fields run concurrently), the work list (fields sorted
+// longest column first, prefix sums of their work items) and its upload into
+// the caller's workspace, then one launch per kernel and register class of
+// the column length.  Workspace layout, each part 256-byte aligned:
 //   forward:  [header + prefix][argument blocks]
 //   adjoint:  [column table][horizontal table][lambda of items without data_bar]
 #include <hip/hip_runtime.h>
@@ -204,66 +204,59 @@ int32_t write_table(std::vector<uint8_t>& blob, size_t off, const std::vector<Ar
   return h.total;
 }
 
-// ---------------------------------------------------------------- forward
-// FP64 fields whose columns exceed kBatchedShortNk levels run in a launch of
-// their own (128-column tiles, e and f in VGPRs); the rest share one launch
-// in the 40-level class.  FP32 fields all run in one launch (the 72-level
-// class): splitting them by class was measured slower.
-bool long_class(stencil_dtype dt, const int64_t* d) { return dt == STENCIL_F64 && d[2] > kBatchedShortNk; }
-
-// Table sizes of the forward batch: [short group, long group].
-void forward_groups(stencil_dtype dt, int n, const stencil_batch_item* it, int m[2]) {
-  m[0] = m[1] = 0;
-  for (int a = 0; a < n; ++a)
-    if (interior_work(it[a].domain)) ++m[long_class(dt, it[a].domain) ? 1 : 0];
+// The range of a table's entries [e0, e1), the table at device address p.
+BatchRange table_range(const char* p, const std::vector<int32_t>& items, int e0, int e1) {
+  BatchRange r;
+  r.prefix = reinterpret_cast<const BatchHeader*>(p)->prefix() + e0;
+  r.n = e1 - e0;
+  r.first = 0;
+  for (int e = 0; e < e0; ++e) r.first += items[e];
+  r.items = 0;
+  for (int e = e0; e < e1; ++e) r.items += items[e];
+  return r;
 }
 
+// ---------------------------------------------------------------- forward
+// Each register class (step_batch_class) of the batch runs in a launch of its
+// own, the longest columns first.
 template <typename T>
 int run_step_batched(int n, const stencil_batch_item* it, void* ws, const stencil_options* opts, hipStream_t s) {
   constexpr stencil_dtype dt = sizeof(T) == 8 ? STENCIL_F64 : STENCIL_F32;
   const std::vector<int> ord = lpt_order(n, it, interior_work);
   if (ord.empty()) return ok();
   char* base = static_cast<char*>(ws);
-  int64_t off = 0;
-  // the long group first: its columns are the longest (longest work first)
-  for (int g = 1; g >= 0; --g) {
-    const bool long_tiles = g == 1;  // FP64 long columns: 128-column tiles
-    const int nt = long_tiles ? kSplitLongNT : kWG;
-    std::vector<StepArgs<T>> args;
-    std::vector<int32_t> items;
-    bool any_mask = false;
-    int64_t total = 0;
-    for (int a : ord) {
-      const stencil_batch_item& x = it[a];
-      if (long_class(dt, x.domain) != (g == 1)) continue;
-      StepArgs<T> A = step_args<T>(&x.u, &x.data, &x.w, const_cast<stencil_field*>(&x.out), x.domain, x.coeff,
-                                   x.dt_dz, x.mask);
-      A.tile_i = field_tile_i(opts, dt, x.domain, nt);
-      const int tile_j = nt / A.tile_i;
-      A.tiles_i = (A.ni + A.tile_i - 1) / A.tile_i;
-      A.ntiles = A.tiles_i * ((A.nj + tile_j - 1) / tile_j);
-      args.push_back(A);
-      items.push_back(A.ntiles);
-      total += A.ntiles;
-      any_mask |= x.mask != nullptr;
-    }
-    const int m = (int)args.size();
-    if (m == 0) continue;
-    if (total > INT32_MAX / 2) return fail(STENCIL_E_UNSUPPORTED, "batch of %lld tiles is too large", (long long)total);
-    std::vector<uint8_t> blob((size_t)table_bytes(m, sizeof(StepArgs<T>)), 0);
-    write_table(blob, 0, args, items);
-    TRY(hip_status(launch_upload(base + off, blob.data(), blob.size(), s), "batched table upload"));
-    BatchHeader* h = reinterpret_cast<BatchHeader*>(base + off);
-    const auto* ent = reinterpret_cast<const StepArgs<T>*>(base + off + table_head_bytes(m));
-    if constexpr (sizeof(T) == 8) {
-      if (long_tiles) {
-        TRY(hip_status(launch_step_batched_long<T>(h, ent, (int)total, any_mask, s), "step (batched, long)"));
-        off += (int64_t)blob.size();
-        continue;
-      }
-    }
-    TRY(hip_status(launch_step_batched<T>(h, ent, (int)total, any_mask, s), "step (batched)"));
-    off += (int64_t)blob.size();
+  const int m = (int)ord.size();
+  std::vector<StepArgs<T>> args(m);
+  std::vector<int32_t> items(m);
+  std::vector<int> cls(m);
+  bool any_mask[kStepBatchClasses] = {};
+  int64_t total = 0;
+  for (int e = 0; e < m; ++e) {
+    const stencil_batch_item& x = it[ord[e]];
+    StepArgs<T> A = step_args<T>(&x.u, &x.data, &x.w, const_cast<stencil_field*>(&x.out), x.domain, x.coeff,
+                                 x.dt_dz, x.mask);
+    cls[e] = step_batch_class<T>(x.domain[2]);
+    const int nt = step_batch_nt<T>(cls[e]);
+    A.tile_i = field_tile_i(opts, dt, x.domain, nt);
+    const int tile_j = nt / A.tile_i;
+    A.tiles_i = (A.ni + A.tile_i - 1) / A.tile_i;
+    A.ntiles = A.tiles_i * ((A.nj + tile_j - 1) / tile_j);
+    args[e] = A;
+    items[e] = A.ntiles;
+    total += A.ntiles;
+    any_mask[cls[e]] |= x.mask != nullptr;
+  }
+  if (total > INT32_MAX / 2) return fail(STENCIL_E_UNSUPPORTED, "batch of %lld tiles is too large", (long long)total);
+  std::vector<uint8_t> blob((size_t)table_bytes(m, sizeof(StepArgs<T>)), 0);
+  write_table(blob, 0, args, items);
+  TRY(hip_status(launch_upload(base, blob.data(), blob.size(), s), "batched table upload"));
+  const auto* ent = reinterpret_cast<const StepArgs<T>*>(base + table_head_bytes(m));
+  for (int e0 = 0; e0 < m;) {
+    int e1 = e0;
+    while (e1 < m && cls[e1] == cls[e0]) ++e1;
+    const BatchRange r = table_range(base, items, e0, e1);
+    TRY(hip_status(launch_step_batched<T>(cls[e0], r, ent + e0, any_mask[cls[e0]], s), "step (batched)"));
+    e0 = e1;
   }
   return ok();
 }
@@ -314,8 +307,9 @@ int run_step_adjoint_batched(int n, const stencil_batch_adjoint_item* it, void* 
     }
   }
 
-  // column adjoints: 64 x 4 column tiles
+  // column adjoints: 64-wide column tiles, one launch per register class
   std::vector<StepArgs<T>> vargs(mv);
+  std::vector<int> vcls(mv);
   std::vector<int32_t> vitems(mv);
   int64_t vtotal = 0;
   for (int e = 0; e < mv; ++e) {
@@ -326,7 +320,9 @@ int run_step_adjoint_batched(int n, const stencil_batch_adjoint_item* it, void* 
     C.o_sj = lsj[a];
     C.o_sk = lsk[a];
     C.tiles_i = (C.ni + 63) / 64;
-    C.ntiles = C.tiles_i * ((C.nj + 3) / 4);
+    vcls[e] = C.nk > kVadjBatchedShortNk ? 0 : 1;
+    const int rows = vadj_batched_tile_rows(sizeof(T) == 8, vcls[e]);
+    C.ntiles = C.tiles_i * ((C.nj + rows - 1) / rows);
     vargs[e] = C;
     vitems[e] = C.ntiles;
     vtotal += C.ntiles;
@@ -360,14 +356,16 @@ int run_step_adjoint_batched(int n, const stencil_batch_adjoint_item* it, void* 
   write_table(blob, 0, vargs, vitems);
   write_table(blob, (size_t)vbytes, hargs, hitems);
   TRY(hip_status(launch_upload(ws, blob.data(), blob.size(), s), "batched table upload"));
-  if (vtotal > 0) {
-    BatchHeader* h = reinterpret_cast<BatchHeader*>(base);
-    const auto* ent = reinterpret_cast<const StepArgs<T>*>(base + table_head_bytes(mv));
-    TRY(hip_status(launch_vadj_batched<T>(h, ent, (int)vtotal, s), "vadv adjoint (batched)"));
+  const auto* vent = reinterpret_cast<const StepArgs<T>*>(base + table_head_bytes(mv));
+  for (int e0 = 0; e0 < mv;) {
+    int e1 = e0;
+    while (e1 < mv && vcls[e1] == vcls[e0]) ++e1;
+    TRY(hip_status(launch_vadj_batched<T>(vcls[e0], table_range(base, vitems, e0, e1), vent + e0, s),
+                   "vadv adjoint (batched)"));
+    e0 = e1;
   }
-  BatchHeader* h = reinterpret_cast<BatchHeader*>(base + vbytes);
-  const auto* ent = reinterpret_cast<const AdjArgs<T>*>(base + vbytes + table_head_bytes(mh));
-  return hip_status(launch_hadj_batched<T>(h, ent, (int)htotal, s), "hdiff adjoint (batched)");
+  const auto* hent = reinterpret_cast<const AdjArgs<T>*>(base + vbytes + table_head_bytes(mh));
+  return hip_status(launch_hadj_batched<T>(table_range(base + vbytes, hitems, 0, mh), hent, s), "hdiff adjoint (batched)");
 }
 
 }  // namespace
@@ -392,12 +390,9 @@ extern "C" {
 
 size_t stencil_batch_workspace_bytes(stencil_dtype dtype, int n, const stencil_batch_item* items) {
   if (check_dtype(dtype) || n <= 0 || n > kMaxBatch || !items) return 0;
-  int m[2];
-  forward_groups(dtype, n, items, m);
-  int64_t b = 0;
-  for (int g = 0; g < 2; ++g)
-    if (m[g]) b += table_bytes(m[g], arg_bytes(dtype, false));
-  return (size_t)b;
+  int m = 0;
+  for (int a = 0; a < n; ++a) m += interior_work(items[a].domain);
+  return m ? (size_t)table_bytes(m, arg_bytes(dtype, false)) : 0;
 }
 
 size_t stencil_batch_adjoint_workspace_bytes(stencil_dtype dtype, int n, const stencil_batch_adjoint_item* items) {

@@ -1,16 +1,18 @@
-// k_batched.hip -- kernels that run a batch of fields of uneven sizes in one
-// launch each.
+// k_batched.hip -- kernels that run a batch of fields of uneven sizes in a
+// few launches, one per register class of the column length.
 //
 // The host sorts the fields longest column first and writes a table into
 // the caller's workspace (a header with the per-field prefix sums of work
 // items, then one argument block per field) with small copy kernels, so the
 // whole call is stream-ordered device work that a HIP graph can capture.
-// The column kernels (forward step, column adjoint) are persistent: every
-// workgroup pulls work items (field, column tile) from an atomic queue in
-// the header until the queue is exhausted.  The horizontal adjoint's items
-// (field, four strips, one level) are short, so it launches one workgroup
-// per item instead, which finds its item in the prefix sums.  A work item
-// runs the same body as the single-field kernel.
+// A launch covers a contiguous range of the table's fields and has one
+// workgroup per work item (a column tile, or four strips of the horizontal
+// adjoint at one level), which finds its field in the prefix sums and runs
+// the same body as the single-field kernel.  The hardware dispatcher keeps
+// the CUs filled: an earlier form whose resident workgroups pulled items
+// from an atomic queue exposed each item's start (queue, search, argument
+// block, first loads: several microseconds) on CUs that hold one or two
+// workgroups, and ran every field in the largest class's registers.
 #include <string.h>
 
 #include "common.hpp"
@@ -18,7 +20,6 @@
 #include "k_hadj_strip.hpp"
 #include "k_split.hpp"
 #include "launch.hpp"
-#include "persist.hpp"
 
 namespace gt4mi {
 
@@ -46,7 +47,7 @@ hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t s
 }
 #endif
 
-// ------------------------------------------------------------------ queue
+// ------------------------------------------------------------------ lookup
 // The work list is written by the upload kernels before the launch and is
 // the same for every lane: values read from it are taken from lane 0, so
 // the field, its argument block and the buffer descriptors built from it
@@ -65,28 +66,18 @@ __device__ __forceinline__ S uniform_ld(const S* p) {
   return __builtin_bit_cast(S, v);
 }
 
-// Next work item of the workgroup (uniform), or -1 when the queue is empty.
-// The table upload of each call zeroes the counter, so no reset is needed.
-__device__ __forceinline__ int next_work(BatchHeader* h, int* slot) {
-  if (threadIdx.x == 0) *slot = (int)atomicAdd(&h->queue, 1u);
-  __syncthreads();
-  // every lane reads the same value; taking lane 0's makes it a scalar, so
-  // the item's argument block and buffer descriptors stay in SGPRs
-  const int w = __builtin_amdgcn_readfirstlane(*slot);
-  __syncthreads();  // every lane has the value before the slot is reused
-  return w < uniform_ld(&h->total) ? w : -1;
-}
-
-// Field of work item w: the last e with prefix[e] <= w.
-__device__ __forceinline__ int find_entry(const BatchHeader* h, int w) {
-  const int32_t* p = h->prefix();
-  int lo = 0, hi = uniform_ld(&h->n) - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (uniform_ld(p + mid) <= w) lo = mid;
-    else hi = mid - 1;
+// Field of work item w among the n fields whose first items are at p: the
+// last e with p[e] <= w.  The wave reads 64 prefixes at a time (one memory
+// latency for up to 64 fields, where a binary search waits for five loads in
+// a row) and counts those at or below w.
+__device__ __forceinline__ int find_entry(const int32_t* __restrict__ p, int n, int w) {
+  const int lane = threadIdx.x & 63;
+  int at_or_below = 0;
+  for (int b = 0; b < n; b += 64) {
+    const int first = b + lane < n ? p[b + lane] : INT32_MAX;
+    at_or_below += __popcll(__ballot(first <= w));
   }
-  return lo;
+  return at_or_below - 1;
 }
 
 // ------------------------------------------------------------------ kernels
@@ -101,8 +92,14 @@ union BatchSmem {
   SplitSmem<T, 16, NT / 16> t16;
 };
 
+// Forward step, half-column register class NKH, tiles of NT columns.
 template <typename T, int NT, int NKH, int PD, bool MASK>
-__device__ __forceinline__ void batched_step_item(const StepArgs<T>& A, int tile, BatchSmem<T, NT>& sm) {
+__global__ void __launch_bounds__(2 * NT) k_step_batched(BatchRange r, const StepArgs<T>* __restrict__ ent) {
+  __shared__ BatchSmem<T, NT> sm;
+  const int w = r.first + (int)blockIdx.x;
+  const int e = find_entry(r.prefix, r.n, w);
+  const StepArgs<T> A = uniform_ld(ent + e);
+  const int tile = w - uniform_ld(r.prefix + e);
   if (A.tile_i == 64)
     step_split_tile<T, 64, NT / 64, NKH, PD, MASK, 1>(A, tile, sm.t64);
   else if (A.tile_i == 32)
@@ -111,76 +108,29 @@ __device__ __forceinline__ void batched_step_item(const StepArgs<T>& A, int tile
     step_split_tile<T, 16, NT / 16, NKH, PD, MASK, 1>(A, tile, sm.t16);
 }
 
-// Forward step, half-column register class NKH.  FP64 columns up to
-// kBatchedShortNk levels run in the 40-level class (the 48-level class
-// would spill beside the persistent loop's own registers), longer ones in
-// k_step_batched_long; FP32 columns all run in the 72-level class.
-template <typename T, int NKH, bool MASK>
-__global__ void __launch_bounds__(2 * kWG) k_step_batched(BatchHeader* h, const StepArgs<T>* ent) {
-  __shared__ BatchSmem<T, kWG> sm;
-  __shared__ int slot;
-  for (;;) {
-    const int w = next_work(h, &slot);
-    if (w < 0) break;
-    const int e = find_entry(h, w);
-    const StepArgs<T> A = uniform_ld(ent + e);
-    const int tile = w - uniform_ld(h->prefix() + e);
-    batched_step_item<T, kWG, NKH, GT4MI_PD, MASK>(A, tile, sm);
-    __syncthreads();  // the LDS is reused by the next item
-  }
-}
-
-#ifdef GT4MI_BATCHED_LONG
-// FP64 columns of kBatchedShortNk+1 .. 144 levels: tiles of kSplitLongNT
-// columns (256 lanes) with e and f in VGPRs, as the single-field long form.
-template <typename T, bool MASK>
-__global__ void __launch_bounds__(2 * kSplitLongNT) k_step_batched_long(BatchHeader* h, const StepArgs<T>* ent) {
-  __shared__ BatchSmem<T, kSplitLongNT> sm;
-  __shared__ int slot;
-  for (;;) {
-    const int w = next_work(h, &slot);
-    if (w < 0) break;
-    const int e = find_entry(h, w);
-    const StepArgs<T> A = uniform_ld(ent + e);
-    const int tile = w - uniform_ld(h->prefix() + e);
-    batched_step_item<T, kSplitLongNT, kSplitStagedNkhF64, GT4MI_PD_LONG, MASK>(A, tile, sm);
-    __syncthreads();
-  }
-}
-#endif
-
 // Column adjoint lambda = T^{-T} x_bar (argument blocks in column form).
-template <typename T>
-__global__ void __launch_bounds__(2 * kWG) k_vadj_batched(BatchHeader* h, const StepArgs<T>* ent) {
-  __shared__ T xch[2][2][kWG];
-  __shared__ int slot;
-  for (;;) {
-    const int w = next_work(h, &slot);
-    if (w < 0) break;
-    const int e = find_entry(h, w);
-    const StepArgs<T> A = uniform_ld(ent + e);
-    const int tile = w - uniform_ld(h->prefix() + e);
-    if constexpr (sizeof(T) == 8) {
-      if (A.nk <= 96)
-        column_split_tile<T, 48, GT4MI_COL_PD, true, 1>(A, tile, xch);
-      else
-        column_split_tile<T, 72, GT4MI_COL_PD, true, 2>(A, tile, xch);
-    } else {
-      column_split_tile<T, 72, GT4MI_COL_PD, true, 1>(A, tile, xch);
-    }
-    __syncthreads();
-  }
+template <typename T, int NKH>
+__global__ void __launch_bounds__((2 * ColClass<T, NKH>::nt), (ColClass<T, NKH>::waves))
+    k_vadj_batched(BatchRange r, const StepArgs<T>* __restrict__ ent) {
+  constexpr int NT = ColClass<T, NKH>::nt, LST = ColClass<T, NKH>::lst;
+  __shared__ ColSmem<T, NT, LST> sm;
+  const int w = r.first + (int)blockIdx.x;
+  const int e = find_entry(r.prefix, r.n, w);
+  const StepArgs<T> A = uniform_ld(ent + e);
+  column_split_tile<T, NKH, GT4MI_COL_PD, true, NT, LST>(A, w - uniform_ld(r.prefix + e), sm);
 }
 
 // Horizontal adjoint: one workgroup per work item (field, group of
 // kStripsPerWG strips, level), as the single-field gather's grid; each wave
 // walks its strip of the group (FP32 strips hold two columns per lane).
+// Items cost the same, so each XCD takes one contiguous run of them and
+// strips that share rows share an L2.
 template <typename T>
-__global__ void __launch_bounds__(kWG) k_hadj_batched(const BatchHeader* h, const AdjArgs<T>* ent) {
-  const int w = blockIdx.x;
-  const int e = find_entry(h, w);
+__global__ void __launch_bounds__(kWG) k_hadj_batched(BatchRange r, const AdjArgs<T>* __restrict__ ent) {
+  const int w = r.first + xcd_tile(blockIdx.x, gridDim.x);
+  const int e = find_entry(r.prefix, r.n, w);
   const AdjArgs<T> A = uniform_ld(ent + e);
-  const int local = w - uniform_ld(h->prefix() + e);
+  const int local = w - uniform_ld(r.prefix + e);
   const int groups = (A.ntiles + kStripsPerWG - 1) / kStripsPerWG;
   const int g = local % groups, k = local / groups;
   const int t = __builtin_amdgcn_readfirstlane(g * kStripsPerWG + (int)(threadIdx.x >> 6));
@@ -199,50 +149,50 @@ __global__ void __launch_bounds__(kWG) k_hadj_batched(const BatchHeader* h, cons
 
 // ------------------------------------------------------------------ launchers
 template <typename T>
-hipError_t launch_step_batched(BatchHeader* h, const StepArgs<T>* ent, int total, bool mask, hipStream_t s) {
-  constexpr int NKH = sizeof(T) == 8 ? kBatchedShortNk / 2 : 72;
-  auto go = [&](auto kernel) {
-    const int grid = persistent_grid(kernel, 2 * kWG, total);
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(2 * kWG), 0, s, h, ent);
+hipError_t launch_step_batched(int cls, const BatchRange& r, const StepArgs<T>* ent, bool mask, hipStream_t s) {
+  auto go = [&](auto kernel, int nt) {
+    hipLaunchKernelGGL(kernel, dim3(r.items), dim3(2 * nt), 0, s, r, ent);
     return hipGetLastError();
   };
-  return mask ? go(k_step_batched<T, NKH, true>) : go(k_step_batched<T, NKH, false>);
+#define GT4MI_BATCH_STEP(C)                                                                               \
+  if (cls == C) {                                                                                         \
+    using K = StepBatchClass<T, C>;                                                                       \
+    return mask ? go(k_step_batched<T, K::nt, K::nkh, K::pd, true>, K::nt)                                \
+                : go(k_step_batched<T, K::nt, K::nkh, K::pd, false>, K::nt);                              \
+  }
+  GT4MI_BATCH_STEP(0)
+  GT4MI_BATCH_STEP(1)
+  GT4MI_BATCH_STEP(2)
+#undef GT4MI_BATCH_STEP
+  return hipErrorInvalidValue;
 }
 
-#ifdef GT4MI_BATCHED_LONG
 template <typename T>
-hipError_t launch_step_batched_long(BatchHeader* h, const StepArgs<T>* ent, int total, bool mask, hipStream_t s) {
-  auto go = [&](auto kernel) {
-    const int grid = persistent_grid(kernel, 2 * kSplitLongNT, total);
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(2 * kSplitLongNT), 0, s, h, ent);
+hipError_t launch_vadj_batched(int cls, const BatchRange& r, const StepArgs<T>* ent, hipStream_t s) {
+  auto go = [&](auto kernel, int nt) {
+    hipLaunchKernelGGL(kernel, dim3(r.items), dim3(2 * nt), 0, s, r, ent);
     return hipGetLastError();
   };
-  return mask ? go(k_step_batched_long<T, true>) : go(k_step_batched_long<T, false>);
+  return cls == 0 ? go(k_vadj_batched<T, 72>, ColClass<T, 72>::nt) : go(k_vadj_batched<T, 48>, ColClass<T, 48>::nt);
+}
+
+template <typename T>
+hipError_t launch_hadj_batched(const BatchRange& r, const AdjArgs<T>* ent, hipStream_t s) {
+  hipLaunchKernelGGL(k_hadj_batched<T>, dim3(r.items), dim3(kWG), 0, s, r, ent);
+  return hipGetLastError();
+}
+
+#ifdef GT4MI_UPLOAD
+int vadj_batched_tile_rows(bool f64, int cls) {
+  if (f64) return (cls == 0 ? ColClass<double, 72>::nt : ColClass<double, 48>::nt) / 64;
+  return (cls == 0 ? ColClass<float, 72>::nt : ColClass<float, 48>::nt) / 64;
 }
 #endif
-
-template <typename T>
-hipError_t launch_vadj_batched(BatchHeader* h, const StepArgs<T>* ent, int total, hipStream_t s) {
-  const int grid = persistent_grid(k_vadj_batched<T>, 2 * kWG, total);
-  hipLaunchKernelGGL(k_vadj_batched<T>, dim3(grid), dim3(2 * kWG), 0, s, h, ent);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_hadj_batched(BatchHeader* h, const AdjArgs<T>* ent, int total, hipStream_t s) {
-  if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_hadj_batched<T>, dim3(total), dim3(kWG), 0, s, h, ent);
-  return hipGetLastError();
-}
 
 // one object per element type (-DGT4MI_T=float|double); the float one also
-// holds the table upload (-DGT4MI_UPLOAD), the double one the long-column
-// forward (-DGT4MI_BATCHED_LONG)
-template hipError_t launch_step_batched<GT4MI_T>(BatchHeader*, const StepArgs<GT4MI_T>*, int, bool, hipStream_t);
-template hipError_t launch_vadj_batched<GT4MI_T>(BatchHeader*, const StepArgs<GT4MI_T>*, int, hipStream_t);
-template hipError_t launch_hadj_batched<GT4MI_T>(BatchHeader*, const AdjArgs<GT4MI_T>*, int, hipStream_t);
-#ifdef GT4MI_BATCHED_LONG
-template hipError_t launch_step_batched_long<GT4MI_T>(BatchHeader*, const StepArgs<GT4MI_T>*, int, bool, hipStream_t);
-#endif
+// holds the table upload (-DGT4MI_UPLOAD)
+template hipError_t launch_step_batched<GT4MI_T>(int, const BatchRange&, const StepArgs<GT4MI_T>*, bool, hipStream_t);
+template hipError_t launch_vadj_batched<GT4MI_T>(int, const BatchRange&, const StepArgs<GT4MI_T>*, hipStream_t);
+template hipError_t launch_hadj_batched<GT4MI_T>(const BatchRange&, const AdjArgs<GT4MI_T>*, hipStream_t);
 
 }  // namespace gt4mi

@@ -9,9 +9,19 @@
 //   bottom, level k: near = a_{k+1} = -r/4 w_{k+1},  far = c_{k-1} = +r/4 w_k
 // while the diagonal b_k = 1 + |a_k| + |c_k| = 1 + |near| + |far| is the same.
 // So both solves are one kernel: a sign and the right-hand side differ.
+//
+// Bound by HBM (three or four streams, each touched once).  e and f of every
+// level stay on the CU until the back substitution: e in VGPRs, f in VGPRs
+// except for the LST outermost levels of each half, whose f sits in LDS (one
+// 8- or 4-byte word per lane and level, no bank conflicts).  The outermost
+// levels are eliminated first and substituted last, so their LDS words are
+// read in one straight run at the end.  LDS is otherwise idle here, and what
+// it takes off the VGPRs decides how many waves a SIMD holds.
 #pragma once
 
 #include "k_step.hpp"
+
+#include <type_traits>
 
 // Levels loaded ahead by the column-only kernels (two loads per level, so
 // they can run further ahead than the fused step at the same registers).
@@ -21,14 +31,22 @@
 
 namespace gt4mi {
 
-// COL = 1: e and f of every level in VGPRs; COL = 2: f staged in `out`.
-template <typename T, int NKH, int PD, bool ADJ, int COL>
-__device__ __forceinline__ void column_split_tile(const StepArgs<T>& A, int tile, T (&xch)[2][2][kWG]) {
-  constexpr int NT = kWG;
+// NT: columns of the workgroup's tile (64 wide, NT/64 rows), two lanes each.
+template <typename T, int NT, int LST>
+struct ColSmem {
+  T xch[2][2][NT];                  // innermost (e, f) of each half and column
+  T st[LST > 0 ? LST : 1][2 * NT];  // f of the outermost levels (LST > 0)
+};
+
+// Every half eliminates at least LST levels (A.nk / 2 >= LST: the host's
+// register classes see to it), so the stashed levels need no check.
+template <typename T, int NKH, int PD, bool ADJ, int NT, int LST>
+__device__ __forceinline__ void column_split_tile(const StepArgs<T>& A, int tile, ColSmem<T, NT, LST>& sm) {
+  constexpr int TJ = NT / 64;
   const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);  // 0: top, 1: bottom
   const int ltid = threadIdx.x - half * NT;
   const int bi = tile % A.tiles_i, bj = tile / A.tiles_i;
-  const int i = bi * 64 + (ltid & 63), j = bj * 4 + (ltid >> 6);
+  const int i = bi * 64 + (ltid & 63), j = bj * TJ + (ltid >> 6);
   const bool active = (i < A.ni) && (j < A.nj);
   const int ic = min(i, A.ni - 1), jc = min(j, A.nj - 1);
   const int nk = A.nk, m = nk / 2;
@@ -64,7 +82,7 @@ __device__ __forceinline__ void column_split_tile(const StepArgs<T>& A, int tile
   for (int s = 0; s < PD; ++s) issue(s, s);
 
   T ev[NKH];
-  T fv[COL == 1 ? NKH : 1];
+  T fv[NKH];
   T wp = T(0), e = T(0), f = T(0);
   const T sn = (half ? A.r4 : -A.r4) * (ADJ ? T(-1) : T(1));
 #pragma unroll
@@ -87,96 +105,97 @@ __device__ __forceinline__ void column_split_tile(const StepArgs<T>& A, int tile
     f = act ? fn : f;
     wp = act ? wn : wp;
     ev[s] = e;
-    if constexpr (COL == 1) fv[s] = f;
-    else buf_st(vo.at(min(max(k, 0), nk - 1)), act ? ooff : kOffNone, f);
+    if (s < LST) sm.st[s][threadIdx.x] = f;  // read back by the same lane
+    else fv[s] = f;
   }
-  xch[half][0][ltid] = e;
-  xch[half][1][ltid] = f;
+  sm.xch[half][0][ltid] = e;
+  sm.xch[half][1][ltid] = f;
   __syncthreads();
-  const T eo = xch[1 - half][0][ltid], fo = xch[1 - half][1][ltid];
+  const T eo = sm.xch[1 - half][0][ltid], fo = sm.xch[1 - half][1][ltid];
   const T et = half ? eo : e, ft = half ? fo : f;
   const T eb = half ? e : eo, fb = half ? f : fo;
   const T xm = (fb - eb * ft) * recip(T(1) - eb * et);
   const T xm1 = ft - et * xm;
   T x = half ? xm1 : xm;
-  if constexpr (COL == 1) {
 #pragma unroll
-    for (int s = NKH - 1; s >= 0; --s) {
-      if (s < nlev) {
-        const auto ro = vo.at(k0 + dir * s);
-        x = fv[s] - ev[s] * x;
-        buf_st(ro, ooff, x);
-      }
+  for (int s = NKH - 1; s >= LST; --s) {
+    if (s < nlev) {
+      const auto ro = vo.at(k0 + dir * s);
+      x = fv[s] - ev[s] * x;
+      buf_st(ro, ooff, x);
     }
-  } else {
-    // The staged f comes back PDB levels ahead of its use.  The walk is
-    // branch-free so that the load counters stay exact: levels this half
-    // does not own read 0 and store nothing (offset outside the window), and
-    // leave x unchanged.  Level s's value is consumed before slot s % PDB is
-    // refilled with level s - PDB.
-    constexpr int PDB = 4;
-    T pf[PDB];
-    auto level = [&](int s) { return vo.at(min(max(k0 + dir * s, 0), nk - 1)); };
+  }
 #pragma unroll
-    for (int s = NKH - 1 + PDB; s >= 0; --s) {
-      if (s < NKH) {
-        const bool act = s < nlev;
-        const T xn = pf[s % PDB] - ev[s] * x;
-        x = act ? xn : x;
-        buf_st(level(s), act ? ooff : kOffNone, x);
-      }
-      const int sl = s - PDB;
-      if (sl >= 0) pf[sl % PDB] = buf_ld(level(sl), sl < nlev ? ooff : kOffNone, T());
-    }
+  for (int s = LST - 1; s >= 0; --s) {
+    const auto ro = vo.at(k0 + dir * s);
+    x = sm.st[s][threadIdx.x] - ev[s] * x;
+    buf_st(ro, ooff, x);
   }
 }
 
-template <typename T, int NKH, int PD, bool ADJ, int COL>
-__global__ void __launch_bounds__(2 * kWG) k_column_split(StepArgs<T> A) {
-  __shared__ T xch[2][2][kWG];
-  column_split_tile<T, NKH, PD, ADJ, COL>(A, xcd_tile(blockIdx.x, gridDim.x), xch);
+// The register classes: half-columns of up to `nkh` levels in tiles of NT
+// columns with LST levels' f in LDS.  A class's columns have more than twice
+// the previous class's levels, so every half holds more than that many and
+// LST may not exceed it.  Measured on cold buffers, 512x512 columns:
+//   FP64, 97..144 levels: f of 36 levels in LDS lets e and f of the whole
+//     column stay on chip at two waves per SIMD (2 x 80 KB of LDS per CU);
+//     with f staged in the output instead (read back in the substitution)
+//     the adjoint at 137 levels took 242 us against 190, the forward solve
+//     306 against 237.
+//   FP64, up to 96 levels: three waves per SIMD (10 to 25 levels in LDS) were
+//     no faster than two (109.8 against 108.6 us at 80): memory bound.
+//   FP32, 49..80 levels: 20 levels in LDS make room for six waves per SIMD
+//     (56.2 against 58.9 us with four).
+//   FP32, 97..144: 128-column tiles hold three workgroups per CU (three waves
+//     per SIMD) where 256-column tiles of 160 levels held two waves: 97.8
+//     against 104.5 us at 137.
+template <typename T, int NKH>
+struct ColClass {
+  static constexpr int nt = 256, lst = 0, waves = 2;
+};
+template <>
+struct ColClass<double, 72> {
+  static constexpr int nt = 128, lst = 36, waves = 2;
+};
+template <>
+struct ColClass<float, 40> {
+  static constexpr int nt = 128, lst = 20, waves = 6;
+};
+template <>
+struct ColClass<float, 48> {
+  static constexpr int nt = 256, lst = 0, waves = 4;
+};
+template <>
+struct ColClass<float, 72> {
+  static constexpr int nt = 128, lst = 0, waves = 3;
+};
+
+template <typename T, int NKH, int PD, bool ADJ>
+__global__ void __launch_bounds__((2 * ColClass<T, NKH>::nt), (ColClass<T, NKH>::waves)) k_column_split(StepArgs<T> A) {
+  constexpr int NT = ColClass<T, NKH>::nt, LST = ColClass<T, NKH>::lst;
+  __shared__ ColSmem<T, NT, LST> sm;
+  column_split_tile<T, NKH, PD, ADJ, NT, LST>(A, xcd_tile(blockIdx.x, gridDim.x), sm);
 }
 
-// FP64 keeps e and f of both halves in VGPRs up to 96 levels, then stages f
-// in the output up to 144; FP32 keeps both up to 160.
-#ifndef GT4MI_COLSPLIT_REG_NK_F64
-#define GT4MI_COLSPLIT_REG_NK_F64 96
-#endif
-#ifndef GT4MI_COLSPLIT_STAGED_CLASSES
-#define GT4MI_COLSPLIT_STAGED_CLASSES(X) X(72)
-#endif
-constexpr int kColsplitRegNkF64 = GT4MI_COLSPLIT_REG_NK_F64;
-constexpr int kColsplitStagedNkhF64 = 72;
-
-template <typename T>
-constexpr int column_split_max_nk() {
-  return sizeof(T) == 8 ? 2 * kColsplitStagedNkhF64 : 160;
-}
-
+// longest column of the two-ended solves: FP64 144 levels, FP32 160
 template <typename T, bool ADJ>
 hipError_t launch_column_split_classes(StepArgs<T> A, hipStream_t s) {
   A.tiles_i = (A.ni + 63) / 64;
-  A.ntiles = A.tiles_i * ((A.nj + 3) / 4);
-  const dim3 grid(A.ntiles), block(2 * kWG);
   const int nkh = A.nk - A.nk / 2;
-#define GT4MI_COLSPLIT_CASE(N)                                                                 \
-  if constexpr (2 * N <= (sizeof(T) == 8 ? kColsplitRegNkF64 : 160)) {                         \
-    if (nkh <= N) {                                                                            \
-      hipLaunchKernelGGL((k_column_split<T, N, GT4MI_COL_PD, ADJ, 1>), grid, block, 0, s, A);     \
-      return hipGetLastError();                                                                \
-    }                                                                                          \
-  }
-  GT4MI_COLSPLIT_CASE(16) GT4MI_COLSPLIT_CASE(24) GT4MI_COLSPLIT_CASE(48) GT4MI_COLSPLIT_CASE(80)
-#undef GT4MI_COLSPLIT_CASE
-  if constexpr (sizeof(T) == 8) {
-#define GT4MI_COLSPLIT_STAGED(N)                                                                 \
-    if (nkh <= N) {                                                                              \
-      hipLaunchKernelGGL((k_column_split<T, N, GT4MI_COL_PD, ADJ, 2>), grid, block, 0, s, A);    \
-      return hipGetLastError();                                                                  \
-    }
-    GT4MI_COLSPLIT_STAGED_CLASSES(GT4MI_COLSPLIT_STAGED)
-#undef GT4MI_COLSPLIT_STAGED
-  }
+  auto go = [&](auto cls) {
+    constexpr int N = decltype(cls)::value, NT = ColClass<T, N>::nt, TJ = NT / 64;
+    A.ntiles = A.tiles_i * ((A.nj + TJ - 1) / TJ);
+    hipLaunchKernelGGL((k_column_split<T, N, GT4MI_COL_PD, ADJ>), dim3(A.ntiles), dim3(2 * NT), 0, s, A);
+    return hipGetLastError();
+  };
+  if (nkh <= 16) return go(std::integral_constant<int, 16>{});
+  if (nkh <= 24) return go(std::integral_constant<int, 24>{});
+  if constexpr (sizeof(T) == 4)
+    if (nkh <= 40) return go(std::integral_constant<int, 40>{});
+  if (nkh <= 48) return go(std::integral_constant<int, 48>{});
+  if (nkh <= 72) return go(std::integral_constant<int, 72>{});
+  if constexpr (sizeof(T) == 4)
+    if (nkh <= 80) return go(std::integral_constant<int, 80>{});
   return hipErrorInvalidValue;
 }
 

@@ -68,33 +68,77 @@ hipError_t launch_hdiff_adjoint(AdjArgs<T> A, hipStream_t s);
 
 // batched launches (k_batched.hip).  The work list sits in device memory: a
 // BatchHeader, then prefix[n + 1] (first work item of each field), then the
-// fields' argument blocks.
+// fields' argument blocks, fields sorted longest column first.
 struct BatchHeader {
-  uint32_t queue;  // next work item, taken with atomicAdd (persistent launches)
-  int32_t n;       // fields
-  int32_t total;   // work items
-  int32_t pad;
+  int32_t n;      // fields
+  int32_t total;  // work items
+  int32_t pad[2];
   __host__ __device__ const int32_t* prefix() const { return reinterpret_cast<const int32_t*>(this + 1); }
 };
-// longest column of a batched field (both halves' e in VGPRs, f staged)
+// The part of a table that one launch runs: n consecutive fields, whose
+// first items are at prefix (a device pointer) and whose work items are
+// first .. first + items - 1.
+struct BatchRange {
+  const int32_t* prefix;
+  int32_t n, first, items;
+};
+// longest column of a batched field
 constexpr int kMaxBatchedNk = 144;
 // stream-ordered copy of a small host table into device memory (kernel
 // arguments, so that a captured graph holds its own copy)
 hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t s);
-// FP64 columns of up to kBatchedShortNk levels run in the 40-level
-// half-column class, longer ones in launch_step_batched_long; FP32 columns
-// all run in the 72-level class.  Each argument block names its field's
-// tile width (StepArgs::tile_i: tiles of kWG columns, kSplitLongNT in the
-// long launch).
-constexpr int kBatchedShortNk = 80;
+
+// Register classes of the batched forward step, longest columns first: the
+// fields of a class share one launch.  max_nk: its longest column; nkh: levels
+// of a half column held in VGPRs; nt: columns per tile; pd: levels loaded ahead.
+// Each argument block names its field's tile width (StepArgs::tile_i).
+constexpr int kStepBatchClasses = 3;
+template <typename T, int C>
+struct StepBatchClass;
+template <>
+struct StepBatchClass<double, 0> {
+  static constexpr int max_nk = 144, nkh = 72, nt = kSplitLongNT, pd = 4;
+};
+template <>
+struct StepBatchClass<double, 1> {
+  static constexpr int max_nk = 96, nkh = 48, nt = 256, pd = 2;
+};
+template <>
+struct StepBatchClass<double, 2> {
+  static constexpr int max_nk = 80, nkh = 40, nt = 256, pd = 2;
+};
+template <>
+struct StepBatchClass<float, 0> {
+  static constexpr int max_nk = 144, nkh = 72, nt = 128, pd = 2;
+};
+template <>
+struct StepBatchClass<float, 1> {
+  static constexpr int max_nk = 112, nkh = 56, nt = 128, pd = 2;
+};
+template <>
+struct StepBatchClass<float, 2> {
+  static constexpr int max_nk = 80, nkh = 40, nt = 256, pd = 2;
+};
+// class of a column, and the columns per tile of a class
 template <typename T>
-hipError_t launch_step_batched(BatchHeader* h, const StepArgs<T>* ent, int total, bool mask, hipStream_t s);
+constexpr int step_batch_class(int64_t nk) {
+  return nk <= StepBatchClass<T, 2>::max_nk ? 2 : nk <= StepBatchClass<T, 1>::max_nk ? 1 : 0;
+}
 template <typename T>
-hipError_t launch_step_batched_long(BatchHeader* h, const StepArgs<T>* ent, int total, bool mask, hipStream_t s);
+constexpr int step_batch_nt(int cls) {
+  return cls == 0 ? StepBatchClass<T, 0>::nt : cls == 1 ? StepBatchClass<T, 1>::nt : StepBatchClass<T, 2>::nt;
+}
 template <typename T>
-hipError_t launch_vadj_batched(BatchHeader* h, const StepArgs<T>* ent, int total, hipStream_t s);
+hipError_t launch_step_batched(int cls, const BatchRange& r, const StepArgs<T>* ent, bool mask, hipStream_t s);
+
+// column adjoint: class 0 above kVadjBatchedShortNk levels, class 1 up to it;
+// the rows of its 64-wide tiles
+constexpr int kVadjBatchedShortNk = 96;
+int vadj_batched_tile_rows(bool f64, int cls);
 template <typename T>
-hipError_t launch_hadj_batched(BatchHeader* h, const AdjArgs<T>* ent, int total, hipStream_t s);
+hipError_t launch_vadj_batched(int cls, const BatchRange& r, const StepArgs<T>* ent, hipStream_t s);
+template <typename T>
+hipError_t launch_hadj_batched(const BatchRange& r, const AdjArgs<T>* ent, hipStream_t s);
 
 // parameter gradients of a step (k_param.hip)
 template <typename T>

@@ -1,8 +1,7 @@
 // noalloc.hip -- the batched forward step for callers that cannot allocate
 // device memory (code under stream capture, tight serving loops, harnesses
-// that forbid hipMalloc).  The work list the persistent launch needs (the
-// header with its work counter, the per-field prefix sums and argument
-// blocks) goes into a fixed device array of this file instead of a
+// that forbid hipMalloc).  The work list the launches need (header, per-field
+// prefix sums and argument blocks) goes into a fixed device array of this file instead of a
 // caller-provided workspace; everything else is stencil_step_batched.
 //
 // Each device the library runs on holds its own copy of the array for the
@@ -10,9 +9,7 @@
 // (on the host it is only a stand-in for the symbol): the device address is
 // looked up once per device with hipGetSymbolAddress, with that device
 // current, and kept.  Every call on a device reuses the same array, so two
-// calls that may run at the same time on one device race; the table upload
-// of each call rewrites the header, whose work counter therefore starts at
-// zero every call.
+// calls that may run at the same time on one device race.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
