@@ -24,7 +24,7 @@ CACHE = os.environ.get("GT4MI_STENCIL_CACHE", os.path.join(PKG, "_gtcache"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-variable",
-         "-Wno-unused-function", "-I", os.path.join(ROOT, "include")]
+         "-Wno-unused-function", "-mllvm", "-pragma-unroll-threshold=1000000", "-I", os.path.join(ROOT, "include")]
 
 
 

@@ -1,8 +1,10 @@
 """HIP code generation for gfx950 from an analysed stencil (the backend of
 the toolchain in the GT4Py paper, Sec. 2.3).
 
-One kernel per computation, launched in program order (Sec. 2.2: the
-computations behave as if run one after the other):
+One kernel per group of fused computations, launched in program order (Sec.
+2.2: the computations behave as if run one after the other).  A group whose
+values can be evaluated point by point takes hippoint.py's form; the others
+are staged:
 
 * PARALLEL: a workgroup of 256 lanes owns a 64 x 4 tile of the domain and
   marches a block of levels.  Per level, each input field read at a
@@ -26,8 +28,9 @@ from __future__ import annotations
 
 from . import ir
 from .analysis import Plan
+from .hippoint import Ineligible, PointKernel
 
-GEN_VERSION = 4
+GEN_VERSION = 5
 TI, TJ = 64, 4
 MIN_WGS = 2048
 
@@ -63,6 +66,13 @@ class _Gen:
                 self.bidx[(cp.index, bi)] = n
                 n += 1
         self.nblocks = n
+        # groups evaluated point by point; the others stage their temporaries
+        self.point = {}
+        for gi, g in enumerate(plan.groups):
+            try:
+                self.point[gi] = PointKernel(self, gi, [plan.comps[c] for c in g])
+            except Ineligible:
+                pass
 
     # ------------------------------------------------------------ helpers
     def f_inside(self, name, i, j):
@@ -73,13 +83,13 @@ class _Gen:
         e = self.p.temps[name].ext
         return f"({i} >= {e[0]} && {i} < A.ni + {e[1]} && {j} >= {e[2]} && {j} < A.nj + {e[3]})"
 
-    def gld_field(self, name, i, j, k):
+    def gld_field(self, name, i, j, k, valid="true"):
         return (f"gld(A.f_{name}, A.f_{name}_sj, A.f_{name}_sk, {i}, {j}, {k}, "
-                f"{self.f_inside(name, i, j)})")
+                f"{self.f_inside(name, i, j)} && ({valid}))")
 
-    def gld_temp(self, name, i, j, k):
+    def gld_temp(self, name, i, j, k, valid="true"):
         return (f"gld(A.t_{name}, A.t_{name}_sj, A.t_{name}_sk, {i}, {j}, {k}, "
-                f"{self.t_inside(name, i, j)})")
+                f"{self.t_inside(name, i, j)} && ({valid}))")
 
     # ------------------------------------------------------------ expressions
     def expr(self, e, acc):
@@ -482,10 +492,25 @@ class _Gen:
         out.append("}")
         return out
 
+    def later_sweeps(self, gi, seqs, first):
+        """The sweeps after the one a tile kernel's level loop runs: everything
+        earlier members wrote is complete for the lane's column (this lane's
+        sweep, or other lanes before the last barrier)."""
+        L = []
+        for n, cp in enumerate(seqs):
+            pipe = _Gen._Pipe(f"{gi}_{n + first}")
+            inner = self.seq_level(cp, None, pipe, set(cp.writes))
+            L += ["  if (act) {"] + ["    " + l for l in self.level_loop(cp.order, f"A.clo[{cp.index}]",
+                                                                            f"A.chi[{cp.index}]", inner, pipe,
+                                                                            "i", "j")] + ["  }"]
+        return L
+
     # ------------------------------------------------------------ kernels
     def group_kernel(self, gi, g):
         p = self.p
         members = [p.comps[c] for c in g]
+        if gi in self.point:
+            return self.point[gi].source()
         prun = [cp for cp in members if cp.order == ir.PARALLEL]
         seqs = [cp for cp in members if cp.order != ir.PARALLEL]
         written = set()
@@ -539,14 +564,7 @@ class _Gen:
         if seqs:
             L += ["  " + l for l in self.level_loop(seqs[0].order, f"A.glo[{gi}]", f"A.ghi[{gi}]", body, pipe,
                                                      "i", "j")]
-            for n, cp in enumerate(seqs[1:]):
-                p2 = _Gen._Pipe(f"{gi}_{n + 1}")
-                # everything earlier members wrote is complete for this column
-                # (this lane's sweep, or other lanes before the last barrier)
-                inner = self.seq_level(cp, None, p2, set(cp.writes))
-                L += ["  if (act) {"] + ["    " + l for l in self.level_loop(cp.order, f"A.clo[{cp.index}]",
-                                                                                f"A.chi[{cp.index}]", inner, p2,
-                                                                                "i", "j")] + ["  }"]
+            L += self.later_sweeps(gi, seqs[1:], 1)
         else:
             L += ["  const int kbeg = blockIdx.y * A.kchunk, kend = min(kbeg + A.kchunk, A.nk);"]
             L += ["  " + l for l in self.level_loop(ir.FORWARD, "kbeg", "kend", body, pipe, "i", "j")]
@@ -646,7 +664,14 @@ class _Gen:
                 L.append(f"    if (A.blo[{x}] < A.bhi[{x}] && (A.blo[{x}] + ({dk}) < -F->lo[2] || A.bhi[{x}] + ({dk}) > F->hi[2]))")
                 L.append(f"      return fail(GTS_E_HALO, \"field {f}: levels read beyond the field\");")
             L.append(f"    A.f_{f} = (real*)F->data; A.f_{f}_sj = F->stride[1]; A.f_{f}_sk = F->stride[2];")
-            L.append(f"    A.f_{f}_klo = F->lo[2]; A.f_{f}_khi = F->hi[2]; }}")
+            L.append(f"    A.f_{f}_klo = F->lo[2]; A.f_{f}_khi = F->hi[2];")
+            L.append(f"    A.f_{f}_any = F->lo[2] + F->hi[2] > 0;")
+            L.append(f"    if (A.f_{f}_any) {{ A.f_{f}_kl = -(int)(F->lo[2] < BIG ? F->lo[2] : BIG); "
+                     f"A.f_{f}_kh = (int)(F->hi[2] < BIG ? F->hi[2] : BIG) - 1; }} }}")
+        # a field without levels is never read: its clamped loads take any valid address
+        wr = [f for f in sd.fields if p.fields[f].written]
+        for f in sd.fields if wr else ():
+            L.append(f"  if (!A.f_{f}_any) A.f_{f} = A.f_{wr[0]};")
         for si, s in enumerate(sd.scalars):
             L.append(f"  A.s_{s} = (real)scalars[{si}];")
         L.append("  const size_t need = ws_bytes(ni, nj, nk);")
@@ -673,8 +698,9 @@ class _Gen:
                       "    A.kchunk = kc;",
                       f"    hipLaunchKernelGGL(gts_g{gi}, dim3(tiles, (unsigned)((nk + kc - 1) / kc)), dim3(256), 0, stream, A);",
                       "  }"]
-            elif prun:
-                sweep = [cp for cp in prun] + seqs[:1]
+            elif prun or gi in self.point:
+                stash = gi in self.point and self.point[gi].stash
+                sweep = prun + seqs[:2 if stash else 1]
                 L.append(f"  A.glo[{gi}] = (int)nk; A.ghi[{gi}] = 0;")
                 for cp in sweep:
                     L.append(f"  if (A.clo[{cp.index}] < A.chi[{cp.index}]) {{ A.glo[{gi}] = imin(A.glo[{gi}], "
@@ -713,14 +739,17 @@ class _Gen:
                 "static int fail(int code, const char* fmt, ...) {",
                 "  va_list ap; va_start(ap, fmt); vsnprintf(g_err, sizeof g_err, fmt, ap); va_end(ap); return code;",
                 "}",
-                "static inline int imin(int a, int b) { return a < b ? a : b; }",
-                "static inline int imax(int a, int b) { return a > b ? a : b; }",
+                "#define BIG (1 << 30)",
+                "__host__ __device__ static inline int imin(int a, int b) { return a < b ? a : b; }",
+                "__host__ __device__ static inline int imax(int a, int b) { return a > b ? a : b; }",
+                "__device__ __forceinline__ int kclamp(int k, int lo, int hi) { return imax(lo, imin(k, hi)); }",
                 "__device__ __forceinline__ real gld(const real* p, int64_t sj, int64_t sk, int i, int j, int k, bool ok) {",
                 "  return ok ? p[(int64_t)i + (int64_t)j * sj + (int64_t)k * sk] : (real)0;",
                 "}",
                 "struct Args {"]
         for f in sd.fields:
-            head.append(f"  real* f_{f}; int64_t f_{f}_sj, f_{f}_sk, f_{f}_klo, f_{f}_khi;")
+            head.append(f"  real* f_{f}; int64_t f_{f}_sj, f_{f}_sk, f_{f}_klo, f_{f}_khi; "
+                        f"int f_{f}_any, f_{f}_kl, f_{f}_kh;")
         for t in self.hbm:
             head.append(f"  real* t_{t.name}; int64_t t_{t.name}_sj, t_{t.name}_sk;")
         for s in sd.scalars:
