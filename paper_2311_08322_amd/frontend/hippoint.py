@@ -38,6 +38,10 @@ PD = 4
 # 512x380x107 125 -> 120 us; 16 the same).
 PDW = 8
 MAX_LOCALS = 160
+# A ring holds PD values of every input; past RING_VALUES inputs it is half as
+# deep, past three times that (or boxes beyond a workgroup's share of LDS) the
+# group is staged.
+RING_VALUES = 8
 # The stash by element size: waves per SIMD (workgroups per CU), and the VGPRs a
 # lane spends on it.  The column could stay on chip whole at one wave per SIMD,
 # but 512x512x80 FP64 then takes 274 us against 199: the second wave hides the
@@ -178,6 +182,10 @@ class PointKernel:
             self.body = self._par_code() + self._sweep_code()
             self.boxes = {k: (min(o[0] for o in v), max(o[0] for o in v), min(o[1] for o in v), max(o[1] for o in v))
                           for k, v in sorted(self.hoff.items()) if any(o != (0, 0) for o in v)}
+        self.values = values = len(self._lead(self.cols)[0]) + sum(self._box(k)[2] for k in self.boxes)
+        self.pd = PD if values <= RING_VALUES else PD // 2
+        if values > 3 * RING_VALUES or sum(2 * self._box(k)[1] * self.size for k in self.boxes) > LDS_BYTES // 4:
+            raise Ineligible("too many inputs in flight")
         self.cols1 = []  # what the sweep that reads the stash loads
         self.body1 = self._second_code(self.seqs[1], self.cols1) if self.stash else []
 
@@ -207,8 +215,10 @@ class PointKernel:
     def _sizes(self):
         """(waves per SIMD, levels in registers, levels in LDS) of the stash."""
         waves, regs = STASH[self.size]
+        # STASH leaves room for rings of the step's size (5 values)
+        regs -= max(0, self.values * self.pd - 5 * PD) * self.size // 4
         per = len(self.stash)
-        R = max(PD, regs * 4 // (per * self.size) // PD * PD)
+        R = max(self.pd, regs * 4 // (per * self.size) // self.pd * self.pd)
         box = sum(2 * self._box(k)[1] * self.size for k in self.boxes)
         NL = max(0, (LDS_BYTES // waves - box - 512) // (per * NT * self.size))
         return waves, R, NL
@@ -330,6 +340,7 @@ class PointKernel:
         p, gi, seqs = self.p, self.gi, self.seqs
         stash = self.stash
         waves, R, NL = self._sizes() if stash else (0, 0, 0)
+        pd = self.pd
         bounds = f"__launch_bounds__({NT}, {waves})" if stash else f"__launch_bounds__({NT})"
         I = "__attribute__((always_inline))"
         L = [f"__global__ void {bounds} gts_g{gi}(Args A) {{",
@@ -379,9 +390,9 @@ class PointKernel:
         loaded, carried = self._lead(self.cols)
         q = [f"q_{kd}_{n}_{_off(dk)}" for kd, n, dk in loaded]
         for r in q:
-            L.append(f"  real {r}[{PD}];")
+            L.append(f"  real {r}[{pd}];")
         for key in self.boxes:
-            L.append(f"  real qb_{key[0]}_{_off(key[1])}[{PD}][{self._box(key)[2]}];")
+            L.append(f"  real qb_{key[0]}_{_off(key[1])}[{pd}][{self._box(key)[2]}];")
         L += [f"  auto issue = [&](int slot, int s) {I} {{",
               f"    const int k = {kof.format(s='imax(imin(s, n - 1), 0)')};"]
         for r, key in zip(q, loaded):
@@ -392,7 +403,7 @@ class PointKernel:
                   "#pragma unroll",
                   f"    for (int t = 0; t < {self._box(key)[2]}; ++t) qb_{tag}[slot][t] = bp_{tag}[t][o_{tag}];"]
         L.append("  };")
-        L += ["#pragma unroll", f"  for (int s = 0; s < {PD}; ++s) issue(s, s);"]
+        L += ["#pragma unroll", f"  for (int s = 0; s < {pd}; ++s) issue(s, s);"]
         for (kd, n, dk) in carried:
             L.append(f"  real h_{kd}_{n}_{_off(dk)} = {self._ld((kd, n, dk), kof.format(s='0'))};")
         # one level
@@ -410,7 +421,7 @@ class PointKernel:
             w, cnt, it = self._box(key)
             L += [f"    real* const B_{tag} = S_{tag} + (s & 1) * {cnt};", "#pragma unroll",
                   f"    for (int t = 0; t < {it}; ++t) B_{tag}[tid + t * {NT}] = qb_{tag}[slot][t];"]
-        L += [f"    issue(slot, s + {PD});", '    __asm__ volatile("" ::: "memory");  // the loads stay here']
+        L += [f"    issue(slot, s + {pd});", '    __asm__ volatile("" ::: "memory");  // the loads stay here']
         if self.boxes:
             L.append("    __syncthreads();")
         for key in self.boxes:
@@ -419,21 +430,21 @@ class PointKernel:
         L += ["    " + l for l in self.body]
         L.append("  };")
         if not stash:
-            L += [f"  for (int s0 = 0; s0 < n; s0 += {PD}) {{", "#pragma unroll",
-                  f"    for (int t = 0; t < {PD}; ++t)", "      if (s0 + t < n) level(s0 + t, t);", "  }"]
+            L += [f"  for (int s0 = 0; s0 < n; s0 += {pd}) {{", "#pragma unroll",
+                  f"    for (int t = 0; t < {pd}; ++t)", "      if (s0 + t < n) level(s0 + t, t);", "  }"]
         else:
             c0 = seqs[0].index
             L += [f"  // the stash: levels [nl, n) in registers, [nw, nl) in LDS, [0, nw) in the workspace",
-                  f"  const int nl = n > {R} ? (n - {R} + {PD - 1}) / {PD} * {PD} : 0, m = n - nl;",
+                  f"  const int nl = n > {R} ? (n - {R} + {pd - 1}) / {pd} * {pd} : 0, m = n - nl;",
                   f"  const int nw = imax(nl - {NL}, 0);",
-                  f"  for (int s0 = 0; s0 < nl; s0 += {PD}) {{", "#pragma unroll",
-                  f"    for (int t = 0; t < {PD}; ++t) {{", "      const int s = s0 + t;", "      level(s, t);"]
+                  f"  for (int s0 = 0; s0 < nl; s0 += {pd}) {{", "#pragma unroll",
+                  f"    for (int t = 0; t < {pd}; ++t) {{", "      const int s = s0 + t;", "      level(s, t);"]
             lds = [f"L_{n}[(s - nw) * {NT} + tid] = cur_{c0}_{n};" for n in stash] if NL else []
             ws = [f"tp_{n}[(int64_t)({kof.format(s='s')}) * A.t_{n}_sk] = cur_{c0}_{n};" for n in stash]
             L += ["      if (s >= nw) {"] + ["        " + l for l in lds] + ["      } else if (act) {"]
             L += ["        " + l for l in ws] + ["      }", "    }", "  }"]
             L += ["#pragma unroll", f"  for (int r = 0; r < {R}; ++r)", "    if (r < m) {",
-                  f"      level(nl + r, r % {PD});"]
+                  f"      level(nl + r, r % {pd});"]
             L += [f"      R_{n}[r] = cur_{c0}_{n};" for n in stash] + ["    }"]
             # the opposite sweep
             for (kd, n, dk) in cols1:
