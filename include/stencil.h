@@ -291,11 +291,12 @@ int stencil_halo_update(stencil_dtype dtype, stencil_field* f, const int64_t dom
  *   u: the step's input (domain plus 2-point halo); lam, x: domain;
  *   w, w_bar: nk+1 staggered levels (w_bar written on all of them);
  *   coeff_bar: device pointer to one double (FP64 for both dtypes; the
- *     per-point products are summed in FP64 per 64 x 4 tile, then over the
- *     tiles in a fixed order, so the result is reproducible).
+ *     per-point products are summed in FP64 in an order that the domain and
+ *     the workspace's size fix, so the result is reproducible).
  * Either output may be NULL (not both).  coeff_bar needs a device
- * workspace of stencil_param_workspace_bytes(domain) bytes (8-byte aligned)
- * for the per-tile sums.  Outputs may not overlap inputs, the workspace or
+ * workspace for partial sums (8-byte aligned): at least a double per 64 x 4
+ * tile, rounded up to 256 bytes; up to stencil_param_workspace_bytes more
+ * shortens the sums.  Outputs may not overlap inputs, the workspace or
  * each other (STENCIL_E_ALIAS).  opts (NULL: defaults): hdiff_form selects
  * the D of coeff_bar; a forward with opts->coeff_field has no scalar
  * coefficient, so coeff_bar must then be NULL (STENCIL_E_ARG; its gradient

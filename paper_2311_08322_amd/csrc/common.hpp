@@ -115,10 +115,41 @@ __device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, uint32_t off, f
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, off, 0, CP);
 }
 
+// Two adjacent binary32 columns a and b = a + 1 of a row in one access (one
+// request per cache line instead of two; 4-byte alignment is enough).  A row of
+// `width` >= 2 elements: the pair at element e, or, in the lane whose a is the
+// row's last element (odd widths), the pair ending there (`last`: a then comes
+// second and b is outside).
+struct PairAt {
+  uint32_t off;
+  bool last;
+};
+__device__ __forceinline__ PairAt pair_at(int e, int width, bool want);
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+// taken apart as a float vector: element access on the builtin's integer vector
+// narrowed the load to its first word
+__device__ __forceinline__ f32x2_t buf_ld2(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+}
+// ODD: rows may end inside a pair
+template <bool ODD>
+__device__ __forceinline__ void buf_st2(__amdgpu_buffer_rsrc_t r, PairAt at, float a, float b);
+
 // A per-lane byte offset that lies outside every window: a buffer store to
 // it is discarded and a load returns 0, which predicates a lane's access
 // without a branch.
 constexpr uint32_t kOffNone = 0xFFFFFFF0u;
+
+__device__ __forceinline__ PairAt pair_at(int e, int width, bool want) {
+  const bool last = e == width - 1;
+  return {want && e >= 0 && e < width ? (uint32_t)(last ? e - 1 : e) * 4u : kOffNone, last};
+}
+template <bool ODD>
+__device__ __forceinline__ void buf_st2(__amdgpu_buffer_rsrc_t r, PairAt at, float a, float b) {
+  const bool half = ODD && at.last;
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, f32x2_t{a, b}), r, half ? kOffNone : at.off, 0, 0);
+  if constexpr (ODD) buf_st(r, half && at.off != kOffNone ? at.off + 4 : kOffNone, a);
+}
 
 // DPP wave shifts of GFX9: lane l reads lane l+1 (shl) or lane l-1 (shr);
 // the lane past the wave's end reads 0.  Every lane must be active.
@@ -274,14 +305,5 @@ struct AdjArgs {
   const T* kappa;
   int64_t c_sj, c_sk;
 };
-
-// ni is even and lambda's rows keep 8-byte alignment (base, row and level
-// strides): the binary32 gather then reads a lane's two columns, an even and
-// an odd one, with one load
-template <typename T>
-__host__ __device__ inline bool lambda_pairs_ok(const AdjArgs<T>& A) {
-  return A.ni % 2 == 0 && reinterpret_cast<uintptr_t>(A.lam) % 8 == 0 &&
-         (A.l_sj * (int64_t)sizeof(T)) % 8 == 0 && (A.l_sk * (int64_t)sizeof(T)) % 8 == 0;
-}
 
 }  // namespace gt4mi

@@ -19,6 +19,8 @@
 // sets ([-1,ni) x [0,nj) and [0,ni) x [-1,nj)) equal to zero.
 #include <string.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 #include "k_hadj_strip.hpp"
 #include "launch.hpp"
@@ -119,20 +121,23 @@ template <typename T>
 hipError_t launch_hdiff_adjoint(AdjArgs<T> A, hipStream_t s) {
   const bool var = A.kappa != nullptr && A.lam != nullptr;  // per-point coefficient
   if constexpr (sizeof(T) == 4) {
-    // binary32: two columns per lane, strips of 124 x strip_rows outputs
-    A.tiles_i = (A.ni + 4 + kStripOut2 - 1) / kStripOut2;
-    A.ntiles = A.tiles_i * ((A.nj + 4 + strip_rows<T>() - 1) / strip_rows<T>());
-    const dim3 grid((A.ntiles + kStripsPerWG - 1) / kStripsPerWG, A.nk), block(kWG);
-    const bool pair = lambda_pairs_ok(A);
-    if (var && pair)
-      hipLaunchKernelGGL((k_hdiff_adjoint_strip2<true, true>), grid, block, 0, s, A);
-    else if (var)
-      hipLaunchKernelGGL((k_hdiff_adjoint_strip2<true, false>), grid, block, 0, s, A);
-    else if (pair)
-      hipLaunchKernelGGL((k_hdiff_adjoint_strip2<false, true>), grid, block, 0, s, A);
-    else
-      hipLaunchKernelGGL((k_hdiff_adjoint_strip2<false, false>), grid, block, 0, s, A);
-    return hipGetLastError();
+    if (A.ni > 1) {  // two columns per lane, strips of 124 x strip_rows outputs
+      A.tiles_i = (A.ni + 4 + kStripOut2 - 1) / kStripOut2;
+      A.ntiles = A.tiles_i * ((A.nj + 4 + strip_rows<T>() - 1) / strip_rows<T>());
+      const dim3 grid((A.ntiles + kStripsPerWG - 1) / kStripsPerWG, A.nk), block(kWG);
+      auto go = [&](auto odd) {
+        constexpr bool O = decltype(odd)::value;
+        if (var)
+          hipLaunchKernelGGL((k_hdiff_adjoint_strip2<true, O, false>), grid, block, 0, s, A);
+        else if (gather_pair_stores(A))
+          hipLaunchKernelGGL((k_hdiff_adjoint_strip2<false, O, true>), grid, block, 0, s, A);
+        else
+          hipLaunchKernelGGL((k_hdiff_adjoint_strip2<false, O, false>), grid, block, 0, s, A);
+      };
+      if (A.ni % 2) go(std::true_type{});
+      else go(std::false_type{});
+      return hipGetLastError();
+    }
   }
   A.tiles_i = (A.ni + 4 + kStripOut - 1) / kStripOut;
   A.ntiles = A.tiles_i * ((A.nj + 4 + strip_rows<T>() - 1) / strip_rows<T>());

@@ -135,15 +135,13 @@ __global__ void __launch_bounds__(kWG) k_hadj_batched(BatchRange r, const AdjArg
   const int g = local % groups, k = local / groups;
   const int t = __builtin_amdgcn_readfirstlane(g * kStripsPerWG + (int)(threadIdx.x >> 6));
   if (t < A.ntiles) {
-    if constexpr (sizeof(T) == 4)
-    {  // two columns per lane, read in pairs where the item's lambda allows (uniform)
-      if (lambda_pairs_ok(A))
-        hdiff_adjoint_strip2<strip_rows<float>(), strip_pd<float>(), false, true>(A, t, k);
-      else
-        hdiff_adjoint_strip2<strip_rows<float>(), strip_pd<float>(), false, false>(A, t, k);
+    constexpr int TJ = strip_rows<T>(), PD = strip_pd<T>();
+    if constexpr (sizeof(T) == 4) {
+      // two columns per lane (uniform branches on the item's ni)
+      if (A.ni > 1 && A.ni % 2 == 0) return hdiff_adjoint_strip2<TJ, PD, false, false, true>(A, t, k);
+      if (A.ni > 1) return hdiff_adjoint_strip2<TJ, PD, false, true, true>(A, t, k);
     }
-    else
-      hdiff_adjoint_strip<T, strip_rows<T>(), strip_pd<T>(), false>(A, t, k);
+    hdiff_adjoint_strip<T, TJ, PD, false>(A, t, k);
   }
 }
 

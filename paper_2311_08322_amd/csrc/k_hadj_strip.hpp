@@ -141,10 +141,10 @@ __device__ __forceinline__ void hdiff_adjoint_strip(const AdjArgs<T>& A, int t, 
 // neighbour of a and the west neighbour of b are in the lane itself, so a
 // row needs half the shifts, and both columns' limiter bits sit in one 32-bit
 // word of each mask plane.  Same values as hdiff_adjoint_strip, in the same
-// order of operations.  PAIR: ni is even and lambda's rows keep 8-byte
-// alignment (the caller checks: lambda_pairs_ok), so a lane reads its two
-// columns with one 8-byte load, one request per cache line instead of two.
-template <int TJ, int PD, bool VAR, bool PAIR = false>
+// order of operations.  ni >= 2; a lane reads and writes its two columns with one
+// access (pair_at), ODD: ni is odd and the last pair ends at the row's end.  ST2
+// writes them in pairs as well, see gather_pair_stores.
+template <int TJ, int PD, bool VAR, bool ODD, bool ST2>
 __device__ __forceinline__ void hdiff_adjoint_strip2(const AdjArgs<float>& A, int t, int k) {
   static_assert((TJ + 4) % PD == 0, "the row walk is unrolled by the prefetch depth");
   using T = float;
@@ -170,16 +170,12 @@ __device__ __forceinline__ void hdiff_adjoint_strip2(const AdjArgs<float>& A, in
   const int64_t W = A.ml.words, plane_xy = (int64_t)nj * W * 8;
   const char* xbase = mbase + A.ml.x_off + (int64_t)k * plane_xy;
   const char* ybase = mbase + A.ml.y_off + (int64_t)k * plane_xy;
-  const uint32_t la_off = ia >= 0 ? (uint32_t)ia * S : kOffNone;  // window: ni
-  const uint32_t lb_off = ib >= 0 ? (uint32_t)ib * S : kOffNone;
-  // PAIR: both columns in one load (ia even and ni even: a inside the row
-  // means b inside too; ia < 0 means both outside)
-  [[maybe_unused]] const uint32_t lp_off = (ia >= 0 && ia < ni) ? (uint32_t)ia * S : kOffNone;
+  const PairAt lat = pair_at(ia, ni, true), bat = pair_at(ia + 2, ni + 4, outl);
+  const uint32_t ba_off = (outl && ia < ni + 2) ? (uint32_t)(ia + 2) * S : kOffNone;  // window: ni + 4
+  const uint32_t bb_off = (outl && ib < ni + 2) ? (uint32_t)(ib + 2) * S : kOffNone;
   // the 32-bit word of a mask row that holds bits a and b (a even)
   const uint32_t m_off = (aI && has_mask) ? (uint32_t)((ia >> 6) * 8 + ((ia >> 5) & 1) * 4) : kOffNone;
   const int mbit = ia & 31;
-  const uint32_t ba_off = (outl && ia < ni + 2) ? (uint32_t)(ia + 2) * S : kOffNone;  // window: ni + 4
-  const uint32_t bb_off = (outl && ib < ni + 2) ? (uint32_t)(ib + 2) * S : kOffNone;
   const bool edge_i = si == 0;  // lane 1's b column is i = -1, the x fluxes' extra column
   const auto rex = make_rsrc(mbase + A.ml.ex_off + (int64_t)k * nj, has_mask ? (uint32_t)nj : 0u);
   const auto rey = make_rsrc(mbase + A.ml.ey_off + (int64_t)k * ni, has_mask ? (uint32_t)ni : 0u);
@@ -201,21 +197,13 @@ __device__ __forceinline__ void hdiff_adjoint_strip2(const AdjArgs<float>& A, in
   uint32_t pmx[PD], pmy[PD];
   auto issue = [&](int r, int s) {
     const auto rl = row_rsrc(lbase, A.l_sj * S, r, nj, (uint32_t)ni * S);
-    if constexpr (PAIR) {
-      // the 8 bytes are taken apart as a float vector: element access on the
-      // builtin's integer vector narrowed the load to its first word here
-      typedef float f32x2_t __attribute__((ext_vector_type(2)));
-      const f32x2_t v = __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rl, lp_off, 0, 0));
-      pla[s] = v[0];
-      plb[s] = v[1];
-    } else {
-      pla[s] = buf_ld(rl, la_off, T());
-      plb[s] = buf_ld(rl, lb_off, T());
-    }
+    const f32x2_t l = buf_ld2(rl, lat.off);
+    pla[s] = l[0];
+    plb[s] = l[1];
     if constexpr (VAR) {
-      const auto rk = row_rsrc(kbase, A.c_sj * S, r, nj, (uint32_t)ni * S);
-      pka[s] = buf_ld(rk, la_off, T());
-      pkb[s] = buf_ld(rk, lb_off, T());
+      const f32x2_t c = buf_ld2(row_rsrc(kbase, A.c_sj * S, r, nj, (uint32_t)ni * S), lat.off);
+      pka[s] = c[0];
+      pkb[s] = c[1];
     }
     pmx[s] = buf_ld_u32(row_rsrc(xbase, W * 8, r, nj, (uint32_t)(W * 8)), m_off);
     pmy[s] = buf_ld_u32(row_rsrc(ybase, W * 8, r, nj, (uint32_t)(W * 8)), m_off);
@@ -228,10 +216,15 @@ __device__ __forceinline__ void hdiff_adjoint_strip2(const AdjArgs<float>& A, in
     const int r = r0 + n;
     T lama = pla[s], lamb = plb[s];
     asm volatile("" : "+v"(lama), "+v"(lamb));  // copies of their own: the slots are free for the refill
+    if constexpr (ODD) {
+      lama = lat.last ? lamb : lama;
+      lamb = lat.last ? T(0) : lamb;
+    }
     T mua = lama, mub = lamb;
     if constexpr (VAR) {
-      mua = pka[s] * lama;
+      mua = (ODD && lat.last ? pkb[s] : pka[s]) * lama;
       mub = pkb[s] * lamb;
+      if constexpr (ODD) mub = lat.last ? T(0) : mub;  // a neighbour's kappa there
     }
     const uint32_t ex = (uint32_t)__builtin_amdgcn_readlane((int)exv[NEX == 1 ? 0 : n / 64], n % 64);
     const uint32_t wx = pmx[s] >> mbit, wy = pmy[s] >> mbit;
@@ -256,8 +249,12 @@ __device__ __forceinline__ void hdiff_adjoint_strip2(const AdjArgs<float>& A, in
     const T vb = lam2b + T(4) * lb2b - lb2a_e - lb2a - lb1b - lb3b;
     if (q >= j0) {
       const auto rb = row_rsrc(bbase, A.b_sj * S, q + 2, nj + 4, (uint32_t)(ni + 4) * S);
-      buf_st(rb, ba_off, va);
-      buf_st(rb, bb_off, vb);
+      if constexpr (ST2) {
+        buf_st2<ODD>(rb, bat, va, vb);
+      } else {
+        buf_st(rb, ba_off, va);
+        buf_st(rb, bb_off, vb);
+      }
     }
     lb3a = lb2a; lb3b = lb2b;
     lb2a = lb1a; lb2b = lb1b;
@@ -280,12 +277,19 @@ __device__ __forceinline__ void hdiff_adjoint_strip2(const AdjArgs<float>& A, in
   for (int s = 0; s < PD; ++s) step(n + s, s, false);
 }
 
-template <bool VAR, bool PAIR>
+// Writing ubar in pairs halves the stores, which pays where ubar goes to HBM
+// (512x512x80: 46 us against 50) and costs where the last-level cache holds the
+// fields (256x256x80: 17.8 against 15.4; 501x403x60, 97 MB: 30.1 against 29.9).
+inline bool gather_pair_stores(const AdjArgs<float>& A) {
+  return (int64_t)A.ni * A.nj * A.nk * 8 > (int64_t)128 << 20;
+}
+
+template <bool VAR, bool ODD, bool ST2>
 __global__ void __launch_bounds__(kWG) k_hdiff_adjoint_strip2(AdjArgs<float> A) {
   const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * kStripsPerWG +
                                                (int)(threadIdx.x >> 6));
   if (t >= A.ntiles) return;  // whole waves only: no barrier follows
-  hdiff_adjoint_strip2<strip_rows<float>(), strip_pd<float>(), VAR, PAIR>(A, t, blockIdx.y);
+  hdiff_adjoint_strip2<strip_rows<float>(), strip_pd<float>(), VAR, ODD, ST2>(A, t, blockIdx.y);
 }
 
 // One strip per wave, at one level per grid row.

@@ -1,6 +1,6 @@
 // k_hdiff.hip -- launcher of the horizontal diffusion alone: the row walk
-// (k_hdiff_strip.hpp) for the stated form with a scalar coefficient, the
-// tile kernel (k_step.hpp) for the generalised diffusion.
+// (k_hdiff_strip.hpp), or the tile kernel (k_step.hpp) where the walk's 32-bit
+// mask window or its grid does not reach.
 #include "k_hdiff_strip.hpp"
 #include "k_step.hpp"
 
@@ -11,27 +11,13 @@ hipError_t launch_hdiff_fused(StepArgs<T> A, int tile_i, hipStream_t s) {
   const bool var = A.kappa != nullptr || A.form != 0;  // the generalised diffusion
   // the walk addresses the mask through one 32-bit window
   const bool small_mask = A.mask == nullptr || A.ml.total <= (int64_t)kOffNone - 16;
-  if (!var && small_mask) {
-    // the row walk: strips of 56 x kHStripRows outputs (FP32: 120, two
-    // columns per lane), four per workgroup, one level per grid row (the tile
-    // option does not apply)
-    if constexpr (sizeof(T) == 4) {
-      A.tiles_i = (A.ni + kHStripOut2 - 1) / kHStripOut2;
-      A.ntiles = A.tiles_i * ((A.nj + kHStripRows - 1) / kHStripRows);
-      const dim3 grid((A.ntiles + kStripsPerWG - 1) / kStripsPerWG, A.nk), block(kWG);
-      if (hdiff_pairs_ok(A))
-        hipLaunchKernelGGL(k_hdiff_strip2<true>, grid, block, 0, s, A);
-      else
-        hipLaunchKernelGGL(k_hdiff_strip2<false>, grid, block, 0, s, A);
-      return hipGetLastError();
-    }
-    A.tiles_i = (A.ni + kHStripOut - 1) / kHStripOut;
-    A.ntiles = A.tiles_i * ((A.nj + kHStripRows - 1) / kHStripRows);
-    const dim3 grid((A.ntiles + kStripsPerWG - 1) / kStripsPerWG, A.nk), block(kWG);
-    hipLaunchKernelGGL(k_hdiff_strip<T>, grid, block, 0, s, A);
-    return hipGetLastError();
+  if (small_mask) {
+    // strips of 56 x kHStripRows outputs (FP32: 120, two columns per lane),
+    // four per workgroup, one level per grid row (the tile option does not apply)
+    if (!var) return launch_hdiff_strip<T, kHPlain>(A, s);
+    if (A.nk <= kMaxGridY) return launch_hdiff_strip<T, kHVar>(A, s);
   }
-  // the generalised diffusion (and masks of 4 GiB or more): a tile marched
+  // masks of 4 GiB or more (and very many levels): a tile marched
   // over a block of levels; enough workgroups to fill the chip
   const int tj = kWG / tile_i;
   A.tiles_i = (A.ni + tile_i - 1) / tile_i;

@@ -1,5 +1,5 @@
-// k_hdiff_strip.hpp -- the horizontal diffusion alone (stated form, scalar
-// coefficient) as a row walk.
+// k_hdiff_strip.hpp -- the horizontal diffusion alone and the coefficient's
+// gradients, as a row walk.
 //
 // Per level, on the interior:
 //   lap(p)  = 4 u(p) - ((u(p - e_i) + u(p + e_i)) + (u(p - e_j) + u(p + e_j)))
@@ -17,7 +17,21 @@
 // 4..59 own the strip's 56 output columns, which start on a byte of the
 // mask rows, so a strip writes its limiter bits as whole bytes (a wave
 // ballot) and strips never share a byte.  No LDS, no barriers.
+//
+// The same walk, with a second interior field read row by row beside u:
+//   kHVar       the generalised diffusion (per-point coefficient kappa or the
+//               scalar; the form's sign on limiter and coefficient)
+//   kHKappaBar  out(p) = -lam(p) D(u)(p), D the divergence of the kept fluxes
+//   kHCoeffBar  the sum of lam(p) D(u)(p) over the strip
+// (the form's sign folded in as in hdiff_var_of).  Bound by memory, like the
+// plain walk.  Times on cold buffers against tile kernels that staged u in LDS
+// behind a barrier per level, 512x512x80 and 256x256x80: FP64 kappa field 111 ->
+// 98 and 28.6 -> 29.6 us, damping 94 -> 75 and 25.7 -> 23.4, kappa_bar 105 -> 95.5
+// (5.3 TB/s) and 49 -> 29; FP32 59 -> 53 and 16.4 -> 16.0, 53 -> 40 and 13.8 ->
+// 13.3, 59 -> 53 and 36 -> 16.
 #pragma once
+
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -26,10 +40,38 @@ namespace gt4mi {
 constexpr int kHStripOut = 56;   // output columns per strip: 7 bytes of a mask row
 constexpr int kHStripRows = 16;  // output rows per strip
 constexpr int kHStripPD = 4;     // u rows in flight ahead of their use
+// the same with a second field read and a result written (10 and 20 rows: FP32
+// kappa_bar 256x256x80 17.2 and 19.2 us against 16.3; FP64 the same within 2%).
+// The sum takes 4 (10 and 20: 256x256x80 FP64 30.3 and 33.9 us against 28.4).
+constexpr int kHStripPD2 = 5;
+
+enum HdiffMode { kHPlain, kHVar, kHKappaBar, kHCoeffBar };
+
+// the second field of a mode: kappa (VAR) or lam, which sits in the data slot
+template <int MODE, typename T>
+struct HdiffSecond {
+  const char* base = nullptr;
+  int64_t row = 0, level = 0;  // bytes
+  bool has = false;
+  __device__ __forceinline__ explicit HdiffSecond(const StepArgs<T>& A) {
+    if constexpr (MODE == kHVar) {
+      has = A.kappa != nullptr;
+      base = reinterpret_cast<const char*>(A.kappa);
+      row = A.c_sj * (int64_t)sizeof(T);
+      level = A.c_sk * (int64_t)sizeof(T);
+    } else if constexpr (MODE != kHPlain) {
+      has = true;
+      base = reinterpret_cast<const char*>(A.data);
+      row = A.d_sj * (int64_t)sizeof(T);
+      level = A.d_sk * (int64_t)sizeof(T);
+    }
+  }
+};
 
 // The strip `t` (A.tiles_i strips in i times the row blocks in j) at level k.
-template <typename T, int TJ, int PD>
-__device__ __forceinline__ void hdiff_strip(const StepArgs<T>& A, int t, int k) {
+// Returns the lane's share of the sum (kHCoeffBar).
+template <typename T, int TJ, int PD, int MODE>
+__device__ __forceinline__ double hdiff_strip(const StepArgs<T>& A, int t, int k) {
   static_assert((TJ + 4) % PD == 0, "the row walk is unrolled by the prefetch depth");
   constexpr uint32_t S = sizeof(T);
   const int lane = threadIdx.x & 63;
@@ -38,8 +80,12 @@ __device__ __forceinline__ void hdiff_strip(const StepArgs<T>& A, int t, int k) 
   const int i = kHStripOut * si - 4 + lane;  // lane 4 is the strip's first output column
   const int j0 = TJ * sj;                    // first output row
   const bool own = lane >= 4 && lane < 4 + kHStripOut && i < ni;
-  const bool has_mask = A.mask != nullptr;
+  constexpr bool SUM = MODE == kHCoeffBar;
+  const bool has_mask = (MODE == kHPlain || MODE == kHVar) && A.mask != nullptr;
   const T coeff = A.coeff;
+  const T gs = MODE == kHPlain ? T(1) : form_sign<T>(A.form);
+  const HdiffSecond<MODE, T> second(A);
+  [[maybe_unused]] double sum = 0.0;
 
   // One descriptor per row (uniform base, a window of the row's width, empty
   // for a row outside the field) and a lane offset fixed for the walk.
@@ -65,9 +111,16 @@ __device__ __forceinline__ void hdiff_strip(const StepArgs<T>& A, int t, int k) 
   const uint32_t ex_base = (uint32_t)(A.ml.ex_off + (int64_t)k * nj), ey_base = (uint32_t)(A.ml.ey_off + (int64_t)k * ni);
 
   T pu[PD];
+  [[maybe_unused]] T p2[MODE == kHPlain ? 1 : PD];
   const int r0 = j0 - 2;
   constexpr int NR = TJ + 4;
-  auto issue = [&](int r, int s) { pu[s] = buf_ld(row_rsrc(ubase, A.u_sj * S, r + 2, nj + 4, (uint32_t)(ni + 4) * S), u_off, T()); };
+  // u of row r, and the second field of row r - 2, which the step that takes
+  // row r's slot completes
+  auto issue = [&](int r, int s) {
+    pu[s] = buf_ld(row_rsrc(ubase, A.u_sj * S, r + 2, nj + 4, (uint32_t)(ni + 4) * S), u_off, T());
+    if constexpr (MODE != kHPlain)
+      p2[s] = buf_ld(row_rsrc(second.base + k * second.level, second.row, r - 2, second.has ? nj : 0, (uint32_t)ni * S), o_off, T());
+  };
 
   // the walk's state: u of rows R-1 and R-2, lap of row R-2, the kept x
   // fluxes of row R-2 and the kept y fluxes between rows R-3 and R-2
@@ -76,6 +129,11 @@ __device__ __forceinline__ void hdiff_strip(const StepArgs<T>& A, int t, int k) 
     const int R = r0 + n;
     T uR = pu[s];
     asm volatile("" : "+v"(uR));  // a copy of its own: the slot is free for the refill
+    [[maybe_unused]] T x2 = T(0);
+    if constexpr (MODE != kHPlain) {
+      x2 = p2[s];
+      asm volatile("" : "+v"(x2));
+    }
     if (refill) issue(R + PD, s);
     // the shifts run with every lane active (a disabled lane would read as 0)
     const T ue1 = lane_shift<kDppWaveShl1>(u1), uw1 = lane_shift<kDppWaveShr1>(u1);
@@ -83,15 +141,22 @@ __device__ __forceinline__ void hdiff_strip(const StepArgs<T>& A, int t, int k) 
     const T lape1 = lane_shift<kDppWaveShl1>(lap1);
     const T Fxw2 = lane_shift<kDppWaveShr1>(Fx2);
     const T fx = lape1 - lap1;  // x flux of row R-1
-    const bool kx = flux_kept(fx, ue1 - u1);
+    const bool kx = flux_kept(fx, gs * (ue1 - u1));
     const T Fx1 = kx ? fx : T(0);
     const T fy = lap1 - lap2;  // y flux between rows R-2 and R-1
-    const bool ky = flux_kept(fy, u1 - u2);
+    const bool ky = flux_kept(fy, gs * (u1 - u2));
     const T Fy2 = ky ? fy : T(0);
     const int q = R - 2;  // out(R-2)
-    const T v = u2 - coeff * ((Fx2 - Fxw2) + (Fy2 - Fy3));
+    const T div = (Fx2 - Fxw2) + (Fy2 - Fy3);
     const bool qrow = q >= j0 && q < j0 + TJ;  // uniform
-    if (qrow) buf_st(row_rsrc(obase, A.o_sj * S, q, nj, (uint32_t)ni * S), o_off, v);
+    if constexpr (SUM) {
+      if (qrow && q < nj) sum += own ? (double)x2 * (double)(gs * div) : 0.0;
+    }
+    T v;
+    if constexpr (MODE == kHPlain) v = u2 - coeff * div;
+    else if constexpr (MODE == kHVar) v = u2 - (gs * (second.has ? x2 : coeff)) * div;
+    else v = -(x2 * (gs * div));
+    if (!SUM && qrow) buf_st(row_rsrc(obase, A.o_sj * S, q, nj, (uint32_t)ni * S), o_off, v);
     if (has_mask) {
       // x bits of row R-1 and y bits between rows R-2 and R-1, one store
       const int rx = R - 1;
@@ -121,6 +186,7 @@ __device__ __forceinline__ void hdiff_strip(const StepArgs<T>& A, int t, int k) 
   }
 #pragma unroll
   for (int s = 0; s < PD; ++s) step(n + s, s, false);
+  return sum;
 }
 
 // FP32: two adjacent columns per lane (a = 120 s - 4 + 2 l, b = a + 1), 128
@@ -136,11 +202,11 @@ __device__ __forceinline__ uint32_t spread4(uint32_t v) {
   return (v & 1u) | ((v & 2u) << 1) | ((v & 4u) << 2) | ((v & 8u) << 3);
 }
 
-// PAIR: ni is even and the rows of u (from its padded corner) and out keep
-// 8-byte alignment, so a lane reads and writes its two columns with one
-// 8-byte access each (one request per cache line instead of two).
-template <int TJ, int PD, bool PAIR = false>
-__device__ __forceinline__ void hdiff_strip2(const StepArgs<float>& A, int t, int k) {
+// ni >= 2; ODD: ni is odd, so the last lane's pair ends at the row's end
+// (pair_at).  Reading odd rows column by column took 30.2 us at 501x403x60
+// against 26.2.
+template <int TJ, int PD, int MODE, bool ODD>
+__device__ __forceinline__ double hdiff_strip2(const StepArgs<float>& A, int t, int k) {
   static_assert((TJ + 4) % PD == 0, "the row walk is unrolled by the prefetch depth");
   using T = float;
   constexpr uint32_t S = 4;
@@ -151,8 +217,12 @@ __device__ __forceinline__ void hdiff_strip2(const StepArgs<float>& A, int t, in
   const int j0 = TJ * sj;
   const bool owna = lane >= 2 && lane < 2 + kHStripOut2 / 2 && ia < ni;
   const bool ownb = lane >= 2 && lane < 2 + kHStripOut2 / 2 && ib < ni;
-  const bool has_mask = A.mask != nullptr;
+  constexpr bool SUM = MODE == kHCoeffBar;
+  const bool has_mask = (MODE == kHPlain || MODE == kHVar) && A.mask != nullptr;
   const T coeff = A.coeff;
+  const T gs = MODE == kHPlain ? T(1) : form_sign<T>(A.form);
+  const HdiffSecond<MODE, T> second(A);
+  [[maybe_unused]] double sum = 0.0;
 
   const auto row_rsrc = [&](const char* base, int64_t row_bytes, int r, int rows, uint32_t width) {
     const bool in = r >= 0 && r < rows;
@@ -160,14 +230,7 @@ __device__ __forceinline__ void hdiff_strip2(const StepArgs<float>& A, int t, in
   };
   const char* ubase = reinterpret_cast<const char*>(A.u) + ((int64_t)k * A.u_sk - 2 - 2 * A.u_sj) * S;
   const char* obase = reinterpret_cast<const char*>(A.out) + (int64_t)k * A.o_sk * S;
-  const uint32_t ua_off = (ia >= -2 && ia < ni + 2) ? (uint32_t)(ia + 2) * S : kOffNone;  // window: ni + 4
-  const uint32_t ub_off = (ib >= -2 && ib < ni + 2) ? (uint32_t)(ib + 2) * S : kOffNone;
-  const uint32_t oa_off = owna ? (uint32_t)ia * S : kOffNone;  // window: ni
-  const uint32_t ob_off = ownb ? (uint32_t)ib * S : kOffNone;
-  // PAIR (ni even, ia even): a inside its window means b inside too
-  typedef float f32x2_t __attribute__((ext_vector_type(2)));
-  [[maybe_unused]] const uint32_t up_off = ua_off;
-  [[maybe_unused]] const uint32_t op_off = oa_off;
+  const PairAt uat = pair_at(ia + 2, ni + 4, true), oat = pair_at(ia, ni, owna);
   // limiter bytes: one descriptor over the whole mask (below 4 GiB), lanes
   // 0..14 the x bytes of a row, lanes 16..30 its y bytes
   const auto rm = make_rsrc(A.mask, has_mask ? (uint32_t)A.ml.total : 0u);
@@ -181,20 +244,19 @@ __device__ __forceinline__ void hdiff_strip2(const StepArgs<float>& A, int t, in
   const uint32_t ex_base = (uint32_t)(A.ml.ex_off + (int64_t)k * nj), ey_base = (uint32_t)(A.ml.ey_off + (int64_t)k * ni);
 
   T pa[PD], pb[PD];
+  [[maybe_unused]] T p2a[MODE == kHPlain ? 1 : PD], p2b[MODE == kHPlain ? 1 : PD];
   const int r0 = j0 - 2;
   constexpr int NR = TJ + 4;
   auto issue = [&](int r, int s) {
     const auto ru = row_rsrc(ubase, A.u_sj * S, r + 2, nj + 4, (uint32_t)(ni + 4) * S);
-    if constexpr (PAIR) {
-      // taken apart as a float vector: element access on the builtin's
-      // integer vector narrowed the load to its first word
-      const f32x2_t v = __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(ru, up_off, 0, 0));
-      pa[s] = v[0];
-      pb[s] = v[1];
-    } else {
-      pa[s] = buf_ld(ru, ua_off, T());
-      pb[s] = buf_ld(ru, ub_off, T());
+    if constexpr (MODE != kHPlain) {
+      const f32x2_t v = buf_ld2(row_rsrc(second.base + k * second.level, second.row, r - 2, second.has ? nj : 0, (uint32_t)ni * S), oat.off);
+      p2a[s] = v[0];
+      p2b[s] = v[1];
     }
+    const f32x2_t v = buf_ld2(ru, uat.off);
+    pa[s] = v[0];
+    pb[s] = v[1];
   };
 
   T u1a = 0, u1b = 0, u2a = 0, u2b = 0, lap2a = 0, lap2b = 0, Fx2a = 0, Fx2b = 0, Fy3a = 0, Fy3b = 0;
@@ -202,6 +264,17 @@ __device__ __forceinline__ void hdiff_strip2(const StepArgs<float>& A, int t, in
     const int R = r0 + n;
     T uRa = pa[s], uRb = pb[s];
     asm volatile("" : "+v"(uRa), "+v"(uRb));  // copies of their own: the slots are free for the refill
+    if constexpr (ODD) {
+      uRa = uat.last ? uRb : uRa;
+      uRb = uat.last ? T(0) : uRb;
+    }
+    [[maybe_unused]] T x2a = T(0), x2b = T(0);
+    if constexpr (MODE != kHPlain) {
+      x2a = p2a[s];
+      x2b = p2b[s];
+      asm volatile("" : "+v"(x2a), "+v"(x2b));
+      if constexpr (ODD) x2a = oat.last ? x2b : x2a;  // column b of that lane is not owned
+    }
     if (refill) issue(R + PD, s);
     // the shifts run with every lane active (a disabled lane would read as 0)
     const T u1a_e = lane_shift<kDppWaveShl1>(u1a);  // east of b
@@ -211,25 +284,32 @@ __device__ __forceinline__ void hdiff_strip2(const StepArgs<float>& A, int t, in
     const T lap1a_e = lane_shift<kDppWaveShl1>(lap1a);
     const T Fx2b_w = lane_shift<kDppWaveShr1>(Fx2b);
     const T fxa = lap1b - lap1a, fxb = lap1a_e - lap1b;  // x fluxes of row R-1
-    const bool kxa = flux_kept(fxa, u1b - u1a), kxb = flux_kept(fxb, u1a_e - u1b);
+    const bool kxa = flux_kept(fxa, gs * (u1b - u1a)), kxb = flux_kept(fxb, gs * (u1a_e - u1b));
     const T Fx1a = kxa ? fxa : T(0), Fx1b = kxb ? fxb : T(0);
     const T fya = lap1a - lap2a, fyb = lap1b - lap2b;  // y fluxes between rows R-2 and R-1
-    const bool kya = flux_kept(fya, u1a - u2a), kyb = flux_kept(fyb, u1b - u2b);
+    const bool kya = flux_kept(fya, gs * (u1a - u2a)), kyb = flux_kept(fyb, gs * (u1b - u2b));
     const T Fy2a = kya ? fya : T(0), Fy2b = kyb ? fyb : T(0);
     const int q = R - 2;  // out(R-2)
-    const T va = u2a - coeff * ((Fx2a - Fx2b_w) + (Fy2a - Fy3a));
-    const T vb = u2b - coeff * ((Fx2b - Fx2a) + (Fy2b - Fy3b));
+    const T diva = (Fx2a - Fx2b_w) + (Fy2a - Fy3a), divb = (Fx2b - Fx2a) + (Fy2b - Fy3b);
     const bool qrow = q >= j0 && q < j0 + TJ;  // uniform
-    if (qrow) {
-      const auto ro = row_rsrc(obase, A.o_sj * S, q, nj, (uint32_t)ni * S);
-      if constexpr (PAIR) {
-        const f32x2_t v = {va, vb};
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), ro, op_off, 0, 0);
-      } else {
-        buf_st(ro, oa_off, va);
-        buf_st(ro, ob_off, vb);
+    if constexpr (SUM) {
+      if (qrow && q < nj) {
+        sum += owna ? (double)x2a * (double)(gs * diva) : 0.0;
+        sum += ownb ? (double)x2b * (double)(gs * divb) : 0.0;
       }
     }
+    T va, vb;
+    if constexpr (MODE == kHPlain) {
+      va = u2a - coeff * diva;
+      vb = u2b - coeff * divb;
+    } else if constexpr (MODE == kHVar) {
+      va = u2a - (gs * (second.has ? x2a : coeff)) * diva;
+      vb = u2b - (gs * (second.has ? x2b : coeff)) * divb;
+    } else {
+      va = -(x2a * (gs * diva));
+      vb = -(x2b * (gs * divb));
+    }
+    if (!SUM && qrow) buf_st2<ODD>(row_rsrc(obase, A.o_sj * S, q, nj, (uint32_t)ni * S), oat, va, vb);
     if (has_mask) {
       const int rx = R - 1;
       const uint64_t bxa = __ballot(owna && kxa), bxb = __ballot(ownb && kxb);
@@ -265,33 +345,56 @@ __device__ __forceinline__ void hdiff_strip2(const StepArgs<float>& A, int t, in
   }
 #pragma unroll
   for (int s = 0; s < PD; ++s) step(n + s, s, false);
+  return sum;
 }
 
-template <bool PAIR>
-__global__ void __launch_bounds__(kWG) k_hdiff_strip2(StepArgs<float> A) {
-  const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * kStripsPerWG +
-                                               (int)(threadIdx.x >> 6));
-  if (t >= A.ntiles) return;  // whole waves only: no barrier follows
-  hdiff_strip2<kHStripRows, kHStripPD, PAIR>(A, t, blockIdx.y);
-}
-
-// ni is even and the rows of u (from its padded corner) and out keep 8-byte
-// alignment: the binary32 row walk then reads and writes column pairs
-inline bool hdiff_pairs_ok(const StepArgs<float>& A) {
-  const auto al = [](const void* p, int64_t sj, int64_t sk) {
-    return reinterpret_cast<uintptr_t>(p) % 8 == 0 && (sj * 4) % 8 == 0 && (sk * 4) % 8 == 0;
-  };
-  return A.ni % 2 == 0 && al(A.u - 2 - 2 * A.u_sj, A.u_sj, A.u_sk) && al(A.out, A.o_sj, A.o_sk);
+// LANE: columns per lane, 1, 2 (FP32, even ni) or 3: two with odd ni.
+template <typename T, int MODE, int LANE>
+__device__ __forceinline__ double hdiff_strip_of(const StepArgs<T>& A, int t, int k) {
+    constexpr int PD = MODE == kHPlain || MODE == kHCoeffBar ? kHStripPD : kHStripPD2;
+  if constexpr (LANE > 1) return hdiff_strip2<kHStripRows, PD, MODE, LANE == 3>(A, t, k);
+  else return hdiff_strip<T, kHStripRows, PD, MODE>(A, t, k);
 }
 
 // One strip per wave, at one level per grid row.
-template <typename T>
+template <typename T, int MODE, int LANE>
 __global__ void __launch_bounds__(kWG) k_hdiff_strip(StepArgs<T> A) {
   // the wave's strip (uniform: the conditions on it stay scalar branches)
   const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * kStripsPerWG +
                                                (int)(threadIdx.x >> 6));
   if (t >= A.ntiles) return;  // whole waves only: no barrier follows
-  hdiff_strip<T, kHStripRows, kHStripPD>(A, t, blockIdx.y);
+  hdiff_strip_of<T, MODE, LANE>(A, t, blockIdx.y);
 }
+
+// strips of the walk in i and in all (a single column is one strip either way)
+template <typename T>
+inline void hdiff_strip_count(StepArgs<T>& A) {
+  constexpr int W = sizeof(T) == 4 ? kHStripOut2 : kHStripOut;
+  A.tiles_i = (A.ni + W - 1) / W;
+  A.ntiles = A.tiles_i * ((A.nj + kHStripRows - 1) / kHStripRows);
+}
+
+// calls go(LANE) for the domain
+template <typename T, typename F>
+inline void hdiff_strip_lanes(const StepArgs<T>& A, F&& go) {
+  if constexpr (sizeof(T) == 4) {
+    if (A.ni > 1 && A.ni % 2 == 0) return go(std::integral_constant<int, 2>{});
+    if (A.ni > 1) return go(std::integral_constant<int, 3>{});
+  }
+  go(std::integral_constant<int, 1>{});
+}
+
+template <typename T, int MODE>
+hipError_t launch_hdiff_strip(StepArgs<T> A, hipStream_t s) {
+  hdiff_strip_count(A);
+  const dim3 grid((A.ntiles + kStripsPerWG - 1) / kStripsPerWG, A.nk), block(kWG);
+  hdiff_strip_lanes(A, [&](auto lane) {
+    hipLaunchKernelGGL((k_hdiff_strip<T, MODE, decltype(lane)::value>), grid, block, 0, s, A);
+  });
+  return hipGetLastError();
+}
+
+// grid.y's limit: the walk has one grid row per level
+constexpr int kMaxGridY = 65535;
 
 }  // namespace gt4mi

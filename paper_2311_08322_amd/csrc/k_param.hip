@@ -11,105 +11,46 @@
 // chain rule of dL/dT(k,l) = -lam_k x_l through a_j = -r/4 w_j,
 // c_{j-1} = r/4 w_j and the |a|, |c| terms of the diagonal; w_0 and w_nk do
 // not enter T and get 0.
-#include "k_step.hpp"
+#include <algorithm>
+
+#include "k_hdiff_strip.hpp"
 #include "launch.hpp"
 
 namespace gt4mi {
 
-// D(u) at the diamond's centre: the flux stage of the diffusion (the same
-// limiter and association as the forward kernels), without the update.
-// gs is the form's sign (form_sign): the damping form's divergence is gs
-// times the stated one taken with the limiter's gradient times gs.
-template <typename T>
-__device__ __forceinline__ T divergence_of(const Diamond<T>& d, T gs) {
-  const T L00 = T(4) * d.u00 - ((d.um1 + d.up1) + (d.vm1 + d.vp1));
-  const T Lp0 = T(4) * d.up1 - ((d.u00 + d.up2) + (d.mp + d.pp));
-  const T Lm0 = T(4) * d.um1 - ((d.um2 + d.u00) + (d.mm + d.pm));
-  const T L0p = T(4) * d.vp1 - ((d.pm + d.pp) + (d.u00 + d.vp2));
-  const T L0m = T(4) * d.vm1 - ((d.mm + d.mp) + (d.vm2 + d.u00));
-  const T fxr = Lp0 - L00, fxl = L00 - Lm0, fyr = L0p - L00, fyl = L00 - L0m;
-  const T Fxr = flux_kept(fxr, gs * (d.up1 - d.u00)) ? fxr : T(0);
-  const T Fxl = flux_kept(fxl, gs * (d.u00 - d.um1)) ? fxl : T(0);
-  const T Fyr = flux_kept(fyr, gs * (d.vp1 - d.u00)) ? fyr : T(0);
-  const T Fyl = flux_kept(fyl, gs * (d.u00 - d.vm1)) ? fyl : T(0);
-  return gs * ((Fxr - Fxl) + (Fyr - Fyl));
-}
-
-// One workgroup per TI x TJ tile of the interior marches the levels with
-// the u-tile (+2 halo) staged in LDS (one barrier per level, the next
-// level's loads in flight) and accumulates lam * D(u) in FP64; the tile's
-// sum goes to partial[tile] (fixed order: the result does not depend on
-// scheduling).  A.data holds lam.
-// FIELD: the gradient of a per-point coefficient instead, -lam(p) D(u)(p)
-// stored point by point into A.out (partial unused).
-template <typename T, int TI, int TJ, bool FIELD>
-__global__ void __launch_bounds__(TI* TJ) k_coeff_partial(StepArgs<T> A, double* partial) {
-  using TA = TileAddr<T, TI, TJ>;
-  constexpr int NT = TA::NT, HI = TA::HI, NLD = TA::NLD;
-  __shared__ T su[2][NLD * NT];
-  __shared__ double red[NT];
-  const int tile = blockIdx.x;
-  TA t;
-  t.init(tile, A.tiles_i, A.ni, A.nj, A.u_sj);
-  const int tid = threadIdx.x;
-  constexpr uint32_t S = sizeof(T);
-  const LevelView vu = level_view(A.u, A.u_sj, A.u_sk, -2, -2, A.nj + 4);
-  const LevelView vl = level_view(A.data, A.d_sj, A.d_sk, 0, 0, A.nj);
-  const uint32_t loff = ((uint32_t)t.ic + (uint32_t)t.jc * (uint32_t)A.d_sj) * S;
-  [[maybe_unused]] const LevelView vo = level_view<T>(A.out, A.o_sj, A.o_sk, 0, 0, A.nj);
-  [[maybe_unused]] const uint32_t ooff =
-      t.active ? ((uint32_t)t.ic + (uint32_t)t.jc * (uint32_t)A.o_sj) * S : kOffNone;
-  const T gs = form_sign<T>(A.form);
-  LevelCursor cu_{vu.base, vu.level_bytes, vu.window};
-  LevelCursor cl{vl.base, vl.level_bytes, vl.window};
-  const int nk = A.nk;
-  T nu[NLD], nl;
-  auto issue = [&](int k) {
-    const auto r = cu_.rsrc();
+// Sum of lam * D(u) over the strips of one workgroup (k_hdiff_strip.hpp's walk)
+// and a run of levels, in FP64, to partial[block] (fixed order: the result does
+// not depend on scheduling).  A.data holds lam.  Bound by memory; a tile marched
+// through every level with u in LDS left small domains short of waves (with the
+// final sum, FP64: 256x256x80 45 us, here 28; 384x384x64 49 and 42; 512x512x80
+// 77 to 92 and 90; FP32 31 and 20, 39 and 26, 54 and 47).
+template <typename T, int LANE>
+__global__ void __launch_bounds__(kWG) k_coeff_partial(StepArgs<T> A, int levels, double* partial) {
+  __shared__ double red[kStripsPerWG];
+  const int wave = threadIdx.x >> 6;
+  const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * kStripsPerWG + wave);
+  const int k0 = blockIdx.y * levels, k1 = min(k0 + levels, A.nk);
+  double s = 0.0;
+  if (t < A.ntiles)
+    for (int k = k0; k < k1; ++k) s += hdiff_strip_of<T, kHCoeffBar, LANE>(A, t, k);
 #pragma unroll
-    for (int q = 0; q < NLD; ++q) nu[q] = buf_ld(r, t.hoff[q], T());
-    nl = buf_ld(cl.rsrc(), loff, T());
-    const bool go = k + 1 < nk;  // hold at the last level: no branch around the loads
-    cu_.advance(go);
-    cl.advance(go);
-  };
-  issue(0);
-  const int cu = (t.tj + 2) * HI + (t.ti + 2);
-  double acc = 0.0;
-  for (int k = 0; k < nk; ++k) {
-    T* U = su[k & 1];
-#pragma unroll
-    for (int q = 0; q < NLD; ++q) U[tid + q * NT] = nu[q];
-    const T lam = nl;
-    issue(k + 1);
-    __syncthreads();
-    const T div = divergence_of(load_diamond<T, HI>(U + cu), gs);
-    if constexpr (FIELD)
-      buf_st(vo.at(k), ooff, -(lam * div));
-    else
-      acc += t.active ? (double)lam * (double)div : 0.0;
-  }
-  if constexpr (FIELD) return;
-  red[tid] = acc;
+  for (int h = 32; h > 0; h >>= 1) s += __shfl_down(s, h);
+  if ((threadIdx.x & 63) == 0) red[wave] = s;
   __syncthreads();
-#pragma unroll
-  for (int h = NT / 2; h > 0; h >>= 1) {
-    if (tid < h) red[tid] += red[tid + h];
-    __syncthreads();
-  }
-  if (tid == 0) partial[tile] = red[0];
+  if (threadIdx.x == 0) partial[blockIdx.y * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // coeff_bar = -(sum of the partials), summed in a fixed order by one workgroup.
-__global__ void __launch_bounds__(kWG) k_coeff_final(const double* partial, int n, double* coeff_bar) {
-  __shared__ double red[kWG];
+constexpr int kFinalWG = 1024;
+__global__ void __launch_bounds__(kFinalWG) k_coeff_final(const double* partial, int n, double* coeff_bar) {
+  __shared__ double red[kFinalWG];
   const int tid = threadIdx.x;
   double s = 0.0;
-  for (int p = tid; p < n; p += kWG) s += partial[p];
+  for (int p = tid; p < n; p += kFinalWG) s += partial[p];
   red[tid] = s;
   __syncthreads();
 #pragma unroll
-  for (int h = kWG / 2; h > 0; h >>= 1) {
+  for (int h = kFinalWG / 2; h > 0; h >>= 1) {
     if (tid < h) red[tid] += red[tid + h];
     __syncthreads();
   }
@@ -159,18 +100,33 @@ __global__ void __launch_bounds__(kWG) k_w_grad(WGradArgs<T> A) {
 }
 
 // ------------------------------------------------------------------ launchers
+int64_t coeff_partial_most(bool f64, int64_t ni, int64_t nj, int64_t nk) {
+  const int64_t w = f64 ? kHStripOut : kHStripOut2;
+  const int64_t strips = ((ni + w - 1) / w) * ((nj + kHStripRows - 1) / kHStripRows);
+  return (strips + kStripsPerWG - 1) / kStripsPerWG * std::min<int64_t>(nk, kMaxGridY);
+}
+
 template <typename T>
-hipError_t launch_param_grads(const StepArgs<T>& Ain, const WGradArgs<T>* W, double* partial,
+hipError_t launch_param_grads(const StepArgs<T>& Ain, const WGradArgs<T>* W, double* partial, int64_t slots,
                               double* coeff_bar, hipStream_t s) {
   StepArgs<T> A = Ain;
-  A.tiles_i = (A.ni + 63) / 64;
-  A.ntiles = A.tiles_i * ((A.nj + 3) / 4);
   const bool some = A.ni > 0 && A.nj > 0;
   if (coeff_bar) {
-    if (some && A.nk > 0)
-      hipLaunchKernelGGL((k_coeff_partial<T, 64, 4, false>), dim3(A.ntiles), dim3(kWG), 0, s, A, partial);
-    const int n = (some && A.nk > 0) ? A.ntiles : 0;
-    hipLaunchKernelGGL(k_coeff_final, dim3(1), dim3(kWG), 0, s, partial, n, coeff_bar);
+    int n = 0;
+    if (some && A.nk > 0) {
+      hdiff_strip_count(A);
+      // a run per level, or as many runs as the partials have room for (at least
+      // one: a strip workgroup covers more columns than a 64 x 4 tile)
+      const int64_t wgs = (A.ntiles + kStripsPerWG - 1) / kStripsPerWG;
+      const int runs = (int)std::min<int64_t>({A.nk, slots / wgs, kMaxGridY});
+      const int levels = (A.nk + runs - 1) / runs;
+      const dim3 grid((uint32_t)wgs, (A.nk + levels - 1) / levels);
+      n = (int)(grid.x * grid.y);
+      hdiff_strip_lanes(A, [&](auto lane) {
+        hipLaunchKernelGGL((k_coeff_partial<T, decltype(lane)::value>), grid, dim3(kWG), 0, s, A, levels, partial);
+      });
+    }
+    hipLaunchKernelGGL(k_coeff_final, dim3(1), dim3(kFinalWG), 0, s, partial, n, coeff_bar);
   }
   if (W && some) {
     WGradArgs<T> B = *W;
@@ -182,20 +138,25 @@ hipError_t launch_param_grads(const StepArgs<T>& Ain, const WGradArgs<T>* W, dou
 }
 
 template <typename T>
-hipError_t launch_coeff_field_grad(const StepArgs<T>& Ain, hipStream_t s) {
-  StepArgs<T> A = Ain;
-  A.tiles_i = (A.ni + 63) / 64;
-  A.ntiles = A.tiles_i * ((A.nj + 3) / 4);
-  if (A.ni > 0 && A.nj > 0 && A.nk > 0)
-    hipLaunchKernelGGL((k_coeff_partial<T, 64, 4, true>), dim3(A.ntiles), dim3(kWG), 0, s, A, nullptr);
-  return hipGetLastError();
+hipError_t launch_coeff_field_grad(const StepArgs<T>& A, hipStream_t s) {
+  if (A.ni <= 0 || A.nj <= 0 || A.nk <= 0) return hipGetLastError();
+  for (int k = 0; k < A.nk; k += kMaxGridY) {  // one grid row per level
+    StepArgs<T> B = A;
+    B.u += (int64_t)k * A.u_sk;
+    B.data += (int64_t)k * A.d_sk;
+    B.out += (int64_t)k * A.o_sk;
+    B.nk = std::min(A.nk - k, kMaxGridY);
+    const hipError_t e = launch_hdiff_strip<T, kHKappaBar>(B, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template hipError_t launch_coeff_field_grad<float>(const StepArgs<float>&, hipStream_t);
 template hipError_t launch_coeff_field_grad<double>(const StepArgs<double>&, hipStream_t);
-template hipError_t launch_param_grads<float>(const StepArgs<float>&, const WGradArgs<float>*, double*, double*,
+template hipError_t launch_param_grads<float>(const StepArgs<float>&, const WGradArgs<float>*, double*, int64_t, double*,
                                               hipStream_t);
-template hipError_t launch_param_grads<double>(const StepArgs<double>&, const WGradArgs<double>*, double*, double*,
+template hipError_t launch_param_grads<double>(const StepArgs<double>&, const WGradArgs<double>*, double*, int64_t, double*,
                                                hipStream_t);
 
 }  // namespace gt4mi

@@ -154,15 +154,15 @@ struct WGradArgs {
   int ni, nj, nk, tiles_i;
   T q;  // dt_dz / 4
 };
-// per-tile partial sums of the coeff gradient: one double per 64 x 4 tile
-inline size_t coeff_partial_count(int64_t ni, int64_t nj) {
-  return (size_t)((ni + 63) / 64) * (size_t)((nj + 3) / 4);
-}
-// A: u (halo) and lam in the data slot; W may be NULL (no w_bar);
-// coeff_bar may be NULL (no reduction; partial unused)
+// Partial sums of the coeff gradient (doubles): the fewest the launch takes, one
+// per 64 x 4 tile, and the most it uses, one per strip workgroup and level.
+inline int64_t coeff_partial_least(int64_t ni, int64_t nj) { return ((ni + 63) / 64) * ((nj + 3) / 4); }
+int64_t coeff_partial_most(bool f64, int64_t ni, int64_t nj, int64_t nk);
+// A: u (halo) and lam in the data slot; W may be NULL (no w_bar); coeff_bar may
+// be NULL (no reduction; partial unused); slots: doubles at partial
 template <typename T>
-hipError_t launch_param_grads(const StepArgs<T>& A, const WGradArgs<T>* W, double* partial, double* coeff_bar,
-                              hipStream_t s);
+hipError_t launch_param_grads(const StepArgs<T>& A, const WGradArgs<T>* W, double* partial, int64_t slots,
+                              double* coeff_bar, hipStream_t s);
 
 // gradient of a per-point coefficient: A.out(p) = -A.data(p) D(u)(p)
 // (A.data holds lam; A.form selects the Laplacian form)

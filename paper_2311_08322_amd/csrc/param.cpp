@@ -2,6 +2,8 @@
 #include <hip/hip_runtime.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "../../include/stencil.h"
 #include "api_internal.hpp"
 #include "launch.hpp"
@@ -12,9 +14,11 @@ namespace {
 
 int64_t r256(int64_t b) { return MaskLayout::round256(b); }
 
+// the least workspace of the coeff gradient; more is used up to what
+// stencil_param_workspace_bytes asks for
 size_t partial_bytes(const int64_t* dom) {
   if (domain_empty(dom)) return 0;
-  return (size_t)r256((int64_t)coeff_partial_count(dom[0], dom[1]) * 8);
+  return (size_t)r256(coeff_partial_least(dom[0], dom[1]) * 8);
 }
 
 Span bytes_span(const void* p, size_t n) {
@@ -25,7 +29,7 @@ Span bytes_span(const void* p, size_t n) {
 template <typename T>
 int run(const stencil_field* u, const stencil_field* w, const stencil_field* x, const stencil_field* lam,
         stencil_field* w_bar, double* coeff_bar, const int64_t* dom, double dt_dz, int form, void* ws,
-        hipStream_t s) {
+        size_t ws_bytes, hipStream_t s) {
   StepArgs<T> A = step_args<T>(u, lam, nullptr, nullptr, dom, 0.0, dt_dz, nullptr);
   A.form = form;
   WGradArgs<T> W;
@@ -48,7 +52,7 @@ int run(const stencil_field* u, const stencil_field* w, const stencil_field* x, 
     W.nk = (int)dom[2];
     W.q = (T)(0.25 * dt_dz);
   }
-  return hip_status(launch_param_grads<T>(A, w_bar ? &W : nullptr, static_cast<double*>(ws), coeff_bar, s),
+  return hip_status(launch_param_grads<T>(A, w_bar ? &W : nullptr, static_cast<double*>(ws), (int64_t)(ws_bytes / 8), coeff_bar, s),
                     "step parameter gradients");
 }
 
@@ -58,7 +62,9 @@ extern "C" {
 
 size_t stencil_param_workspace_bytes(stencil_dtype dtype, const int64_t domain[3]) {
   if (check_dtype(dtype) || !domain || check_domain(domain)) return 0;
-  return partial_bytes(domain);
+  if (domain_empty(domain)) return 0;
+  const int64_t most = coeff_partial_most(dtype == STENCIL_F64, domain[0], domain[1], domain[2]);
+  return std::max(partial_bytes(domain), (size_t)r256(most * 8));
 }
 
 int stencil_step_param_adjoint(stencil_dtype dtype, const stencil_field* u, const stencil_field* w,
@@ -104,10 +110,19 @@ int stencil_step_param_adjoint(stencil_dtype dtype, const stencil_field* u, cons
     if (w_bar) TRY(check_no_alias("coeff_bar", sc, "w_bar", span_of(w_bar, es)));
     if (need) TRY(check_no_alias("coeff_bar", sc, "the workspace", bytes_span(ws, need)));
   }
+  // what the sums may use beyond the least: what the caller gave, unless another
+  // buffer of the call lies in it
+  size_t used = need ? std::min(ws_bytes, stencil_param_workspace_bytes(dtype, domain)) : 0;
+  if (used > need) {
+    const Span su = bytes_span(ws, used);
+    bool clash = overlap(su, bytes_span(coeff_bar, 8)) || (w_bar && overlap(su, span_of(w_bar, es)));
+    for (const Span& i : in) clash = clash || overlap(su, i);
+    if (clash) used = need;
+  }
   TRY(check_device());
   return dtype == STENCIL_F64
-             ? run<double>(u, w, x, lam, w_bar, coeff_bar, domain, dt_dz, form, ws, stream)
-             : run<float>(u, w, x, lam, w_bar, coeff_bar, domain, dt_dz, form, ws, stream);
+             ? run<double>(u, w, x, lam, w_bar, coeff_bar, domain, dt_dz, form, ws, used, stream)
+             : run<float>(u, w, x, lam, w_bar, coeff_bar, domain, dt_dz, form, ws, used, stream);
 }
 
 int stencil_coeff_field_adjoint(stencil_dtype dtype, const stencil_field* u, const stencil_field* lam,
