@@ -308,6 +308,27 @@ int stencil_step_param_adjoint(stencil_dtype dtype, const stencil_field* u, cons
                                double dt_dz, const stencil_options* opts, void* ws, size_t ws_bytes,
                                hipStream_t stream);
 
+/* One training step of a time step (or, with w NULL, of the diffusion alone) on
+ * contiguous (k, j, i) buffers: u and u_bar with their 2-point halo, w and w_bar
+ * with nk+1 levels, everything else nk x nj x ni.
+ * forward: the step of stencil_step (stencil_hdiff), saving the mask.  The
+ *   coefficient is kappa (per point), or the scalar at coeff_dev (device memory,
+ *   of coeff_dtype, read when the kernel runs; its value in dtype is left at
+ *   coeff_copy; nk within the two-ended step's limit), or coeff.
+ * backward: u_bar and data_bar as stencil_step_adjoint (stencil_hdiff_adjoint),
+ *   and those of w_bar (needs x, the forward's output), kappa_bar and coeff_bar
+ *   (one value in dtype; needs stencil_param_workspace_bytes at ws; both need u)
+ *   that are not NULL.  coeff_copy: what the forward left there, or NULL. */
+int stencil_train_forward(stencil_dtype dtype, const void* u, const void* data, const void* w, void* out,
+                          void* mask, const void* kappa, double coeff, const void* coeff_dev,
+                          stencil_dtype coeff_dtype, void* coeff_copy, int64_t ni, int64_t nj, int64_t nk,
+                          double dt_dz, int form, hipStream_t stream);
+int stencil_train_backward(stencil_dtype dtype, const void* x_bar, const void* mask, const void* u, const void* w,
+                           const void* x, const void* kappa, double coeff, const void* coeff_copy, void* u_bar,
+                           void* data_bar, void* w_bar, void* kappa_bar, void* coeff_bar, void* ws,
+                           size_t ws_bytes, int64_t ni, int64_t nj, int64_t nk, double dt_dz, int form,
+                           hipStream_t stream);
+
 /* Gradient with respect to the per-point coefficient of the generalised
  * diffusion: out(p) depends on kappa(p) only through -kappa(p) D(u)(p), so
  *   kappa_bar(p) = -lam(p) D(u)(p)

@@ -109,6 +109,7 @@ VP = ctypes.c_void_p
 I = ctypes.c_int
 D = ctypes.c_double
 SZ = ctypes.c_size_t
+I64 = ctypes.c_int64
 
 SIGNATURES = {
     "stencil_version": (I, []),
@@ -126,6 +127,9 @@ SIGNATURES = {
     "stencil_halo_update": (I, [I, PF, PI64, I, VP]),
     "stencil_step_param_adjoint": (I, [I, PF, PF, PF, PF, PF, VP, PI64, D, PO, VP, SZ, VP]),
     "stencil_coeff_field_adjoint": (I, [I, PF, PF, PF, PI64, PO, VP]),
+    "stencil_train_forward": (I, [I, VP, VP, VP, VP, VP, VP, D, VP, I, VP, I64, I64, I64, D, I, VP]),
+    "stencil_train_backward": (I, [I, VP, VP, VP, VP, VP, VP, D, VP, VP, VP, VP, VP, VP, VP, SZ, I64, I64, I64, D, I,
+                                   VP]),
     "stencil_batch_workspace_bytes": (SZ, [I, I, ctypes.POINTER(StencilBatchItem)]),
     "stencil_batch_adjoint_workspace_bytes": (SZ, [I, I, ctypes.POINTER(StencilBatchAdjointItem)]),
     "stencil_step_batched": (I, [I, I, ctypes.POINTER(StencilBatchItem), VP, SZ, PO, VP]),
@@ -175,5 +179,7 @@ def check(rc: int) -> None:
 
 
 def domain3(domain) -> I64x3:
-    d = I64x3(*[int(x) for x in domain])
-    return d
+    try:
+        return I64x3(*domain)
+    except TypeError:  # numbers that are not ints
+        return I64x3(*[int(x) for x in domain])

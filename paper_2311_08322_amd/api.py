@@ -28,7 +28,7 @@ __all__ = [
     "stencil_workspace_bytes", "stencil_hdiff", "stencil_vadv", "stencil_step",
     "stencil_hdiff_adjoint", "stencil_vadv_adjoint", "stencil_step_adjoint",
     "stencil_param_workspace_bytes", "stencil_step_param_adjoint", "stencil_coeff_field_adjoint",
-    "stencil_halo_update",
+    "stencil_halo_update", "stencil_train_forward", "stencil_train_backward",
     "stencil_batch_workspace_bytes", "stencil_batch_adjoint_workspace_bytes",
     "stencil_step_batched", "stencil_step_adjoint_batched", "stencil_graph_capture_steps",
     "stencil_graph_launch", "stencil_graph_destroy", "stencil_autotune", "stencil_autotune_fields",
@@ -131,6 +131,8 @@ def _opts(o):
 
 def _stream(s) -> Optional[int]:
     if s is None:
+        if torch.cuda.is_initialized():  # the current stream's handle, without the stream object
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(s, int):
         return s
@@ -229,6 +231,25 @@ def stencil_coeff_field_adjoint(u, lam, kappa_bar, domain, opts=None, stream=Non
     _lib.check(_lib.lib().stencil_coeff_field_adjoint(
         _dt(dtype, lam, kappa_bar), _fld(u), _fld(lam), _fld(kappa_bar), _lib.domain3(domain), _opts(opts),
         _stream(stream)))
+
+
+# ------------------------------------------------------------------ training calls
+def stencil_train_forward(u, data, w, out, mask, kappa, coeff, coeff_dev, coeff_copy, domain, dt_dz, form, stream=None):
+    """Contiguous tensors; data and w None: the diffusion alone.  coeff_dev: a
+    one-element device tensor, whose value is left at the address coeff_copy."""
+    _lib.check(_lib.lib().stencil_train_forward(
+        _dtype_code(out.dtype), u.data_ptr(), _ptr(data), _ptr(w), out.data_ptr(), mask.data_ptr(), _ptr(kappa), coeff,
+        _ptr(coeff_dev), 0 if coeff_dev is None else _dtype_code(coeff_dev.dtype), coeff_copy, *domain, dt_dz, form,
+        _stream(stream)))
+
+
+def stencil_train_backward(x_bar, mask, u, w, x, kappa, coeff, coeff_copy, u_bar, data_bar, w_bar, kappa_bar, coeff_bar,
+                           ws, domain, dt_dz, form, stream=None):
+    """Contiguous tensors or None; coeff_copy: the address the forward was given."""
+    _lib.check(_lib.lib().stencil_train_backward(
+        _dtype_code(x_bar.dtype), x_bar.data_ptr(), mask.data_ptr(), _ptr(u), _ptr(w), _ptr(x), _ptr(kappa), coeff,
+        coeff_copy, u_bar.data_ptr(), _ptr(data_bar), _ptr(w_bar), _ptr(kappa_bar), _ptr(coeff_bar), _ptr(ws),
+        0 if ws is None else ws.numel(), *domain, dt_dz, form, _stream(stream)))
 
 
 # ------------------------------------------------------------------ batched

@@ -38,6 +38,55 @@ def _opts(coeff, damping):
                        coeff_field=_f(coeff, 0) if field else None), field
 
 
+# longest columns of the step that reads its coefficient from device memory
+_DEV_COEFF_NK = {torch.float64: 144, torch.float32: 160}
+
+
+def _dense_call(like, shapes, *tensors):
+    """Whether the tensors are what the training calls take: non-empty contiguous
+    device tensors of one floating type on one device, in the canonical shapes
+    (other calls go through fields, which also serve larger tensors)."""
+    return (like.is_cuda and like.dtype in _DEV_COEFF_NK and like.numel() > 0 and
+            all(t.shape == s and t.dtype == like.dtype and t.device == like.device for t, s in zip(tensors, shapes)))
+
+
+def _forward_dense(ctx, u, data, w, out, kap, coeff, dom, dt_dz, damping):
+    """The forward call.  A scalar coefficient tensor on the fields' device is
+    read by the kernel, which leaves its value behind the mask for the backward:
+    no copy to the host, and later changes of the tensor do not reach it."""
+    n = api.stencil_mask_bytes(dom)
+    mask = torch.empty(n + 256, dtype=torch.uint8, device=out.device)
+    dev = None
+    if kap is None and torch.is_tensor(coeff) and coeff.device == out.device and coeff.dtype in _DEV_COEFF_NK and (
+            coeff.numel() == 1 and (w is None or dom[2] <= _DEV_COEFF_NK[out.dtype])):
+        dev = coeff.detach()
+        dev.record_stream(torch.cuda.current_stream())  # the kernel may read it after the caller drops it
+    c = 0.0 if kap is not None or dev is not None else float(coeff)
+    ctx.copy_at = n if dev is not None else None
+    api.stencil_train_forward(u, data, w, out, mask, kap, c, dev, mask.data_ptr() + n if dev is not None else None,
+                              dom, float(dt_dz), api.HDIFF_DAMPING if damping else api.HDIFF_STATED)
+    return mask, c
+
+
+def _backward_dense(ctx, xbar, mask, u, w, out, kap, want_w, want_c):
+    """One call for every gradient: (u_bar, data_bar, w_bar, coeff_bar)."""
+    ni, nj, nk = ctx.dom
+    dt, dev = xbar.dtype, xbar.device
+    ubar = torch.empty((nk, nj + 2 * HALO, ni + 2 * HALO), dtype=dt, device=dev)
+    dbar = torch.empty_like(xbar) if w is not None else None
+    wbar = torch.empty_like(w) if want_w else None
+    kbar = torch.empty_like(xbar) if want_c and ctx.field else None
+    cbar = ws = None
+    if want_c and not ctx.field:
+        cbar = torch.empty((), dtype=dt, device=dev)
+        ws = torch.empty(api.stencil_param_workspace_bytes(dt, ctx.dom), dtype=torch.uint8, device=dev)
+    api.stencil_train_backward(xbar, mask, u, w, out, kap, ctx.coeff,
+                               None if ctx.copy_at is None else mask.data_ptr() + ctx.copy_at, ubar, dbar, wbar, kbar,
+                               cbar, ws, ctx.dom, float(ctx.dt_dz),
+                               api.HDIFF_DAMPING if ctx.damping else api.HDIFF_STATED)
+    return ubar, dbar, wbar, kbar if kbar is not None else cbar
+
+
 class StencilStep(torch.autograd.Function):
     """x = vadv(hdiff(u), data, w): one fused time step.  coeff may be a
     float, a 0-d tensor or a per-point field; gradients flow to u, data, w
@@ -50,11 +99,17 @@ class StencilStep(torch.autograd.Function):
         dom = (ni, nj, nk)
         if torch.is_tensor(coeff) and coeff.dim() == 3:
             coeff = coeff.contiguous()
-        opts, field = _opts(coeff, damping)
-        c = 0.0 if field else float(coeff)
+        field = torch.is_tensor(coeff) and coeff.dim() == 3
         out = torch.empty_like(data)
-        mask = torch.empty(max(api.stencil_mask_bytes(dom), 1), dtype=torch.uint8, device=u.device)
-        api.stencil_step(_f(u, HALO), _f(data, 0), _f(w, 0), _f(out, 0), dom, c, dt_dz, mask=mask, opts=opts)
+        ctx.dense = _dense_call(data, ((nk, nj + 2 * HALO, ni + 2 * HALO), (nk + 1, nj, ni), data.shape), u, w,
+                                *([coeff] if field else []))
+        if ctx.dense:
+            mask, c = _forward_dense(ctx, u, data, w, out, coeff if field else None, coeff, dom, dt_dz, damping)
+        else:
+            opts, _ = _opts(coeff, damping)
+            c = 0.0 if field else float(coeff)
+            mask = torch.empty(max(api.stencil_mask_bytes(dom), 1), dtype=torch.uint8, device=u.device)
+            api.stencil_step(_f(u, HALO), _f(data, 0), _f(w, 0), _f(out, 0), dom, c, dt_dz, mask=mask, opts=opts)
         ctx.params = ctx.needs_input_grad[2] or (torch.is_tensor(coeff) and ctx.needs_input_grad[3])
         # the parameter gradients need the step's input and output
         ctx.save_for_backward(w, mask, u if ctx.params else None, out if ctx.params else None,
@@ -67,8 +122,12 @@ class StencilStep(torch.autograd.Function):
     def backward(ctx, xbar):
         w, mask, u, out, kap = ctx.saved_tensors
         ni, nj, nk = ctx.dom
-        opts, _ = _opts(kap if ctx.field else ctx.coeff, ctx.damping)
         xbar = xbar.contiguous()
+        if ctx.dense:
+            ubar, dbar, wbar, cbar = _backward_dense(ctx, xbar, mask, u, w, out, kap, ctx.needs_input_grad[2],
+                                                     ctx.coeff_tensor and ctx.needs_input_grad[3])
+            return ubar, dbar, wbar, cbar, None, None
+        opts, _ = _opts(kap if ctx.field else ctx.coeff, ctx.damping)
         ubar = torch.empty((nk, nj + 2 * HALO, ni + 2 * HALO), dtype=xbar.dtype, device=xbar.device)
         dbar = torch.empty_like(xbar)
         api.stencil_step_adjoint(_f(xbar, 0), _f(w, 0), mask, _f(ubar, HALO), _f(dbar, 0), ctx.dom, ctx.coeff,
@@ -107,22 +166,31 @@ class HDiff(torch.autograd.Function):
         dom = (Ni - 2 * HALO, Nj - 2 * HALO, nk)
         if torch.is_tensor(coeff) and coeff.dim() == 3:
             coeff = coeff.contiguous()
-        opts, field = _opts(coeff, damping)
-        c = 0.0 if field else float(coeff)
+        field = torch.is_tensor(coeff) and coeff.dim() == 3
         out = torch.empty((nk, dom[1], dom[0]), dtype=u.dtype, device=u.device)
-        mask = torch.empty(max(api.stencil_mask_bytes(dom), 1), dtype=torch.uint8, device=u.device)
-        api.stencil_hdiff(_f(u, HALO), _f(out, 0), dom, c, mask=mask, opts=opts)
+        ctx.dense = _dense_call(out, (out.shape,), *([coeff] if field else []))
+        if ctx.dense:
+            mask, c = _forward_dense(ctx, u, None, None, out, coeff if field else None, coeff, dom, 0.5, damping)
+        else:
+            opts, _ = _opts(coeff, damping)
+            c = 0.0 if field else float(coeff)
+            mask = torch.empty(max(api.stencil_mask_bytes(dom), 1), dtype=torch.uint8, device=u.device)
+            api.stencil_hdiff(_f(u, HALO), _f(out, 0), dom, c, mask=mask, opts=opts)
         want_c = torch.is_tensor(coeff) and ctx.needs_input_grad[1]
         ctx.save_for_backward(mask, u if want_c else None, coeff if field else None)
         ctx.coeff, ctx.dom, ctx.damping, ctx.field, ctx.want_c = c, dom, damping, field, want_c
+        ctx.dt_dz = 0.5  # the diffusion has none
         return out
 
     @staticmethod
     def backward(ctx, obar):
         mask, u, kap = ctx.saved_tensors
         ni, nj, nk = ctx.dom
-        opts, _ = _opts(kap if ctx.field else ctx.coeff, ctx.damping)
         obar = obar.contiguous()
+        if ctx.dense:
+            ubar, _, _, cbar = _backward_dense(ctx, obar, mask, u, None, None, kap, False, ctx.want_c)
+            return ubar, cbar, None
+        opts, _ = _opts(kap if ctx.field else ctx.coeff, ctx.damping)
         ubar = torch.empty((nk, nj + 2 * HALO, ni + 2 * HALO), dtype=obar.dtype, device=obar.device)
         api.stencil_hdiff_adjoint(_f(obar, 0), mask, _f(ubar, HALO), ctx.dom, ctx.coeff, opts=opts)
         cbar = None

@@ -172,6 +172,7 @@ ResolvedOpts resolve_opts(const stencil_options* o, stencil_dtype dt, int op, co
   r.kappa = o ? o->coeff_field : nullptr;
   r.order = (o && o->tile_order) ? o->tile_order : ord;
   if (r.order != STENCIL_ORDER_DISPATCH) r.order = STENCIL_ORDER_XCD;
+  r.dev = nullptr;
   return r;
 }
 
@@ -205,6 +206,11 @@ int check_coeff_field(const stencil_options* o, const int64_t* dom, size_t es, c
 template <typename T>
 static void apply_variant(StepArgs<T>& A, const ResolvedOpts& r) {
   A.form = r.form;
+  if (r.dev) {
+    A.coeff_bytes = r.dev->f64 ? 8 : 4;
+    A.c_sj = (int64_t)reinterpret_cast<uintptr_t>(r.dev->p);
+    A.c_sk = (int64_t)reinterpret_cast<uintptr_t>(r.dev->copy);
+  }
   if (r.kappa) {
     A.kappa = at_origin<T>(r.kappa);
     A.c_sj = r.kappa->stride[1];
@@ -224,6 +230,10 @@ static void apply_variant(AdjArgs<T>& A, const ResolvedOpts& r, double coeff) {
     A.c_sj = r.kappa->stride[1];
     A.c_sk = r.kappa->stride[2];
     A.coeff = (T)sg;
+  } else if (r.dev) {
+    A.coeff = (T)sg;
+    A.coeff_in_memory = 1;
+    A.c_sj = (int64_t)reinterpret_cast<uintptr_t>(r.dev->p);
   } else {
     A.coeff = (T)(sg * coeff);
   }
@@ -444,9 +454,10 @@ static int fused_nk_ok(ResolvedOpts& r, const int64_t* dom) {
   return STENCIL_OK;
 }
 
-int stencil_hdiff(stencil_dtype dtype, const stencil_field* u, stencil_field* out,
+static int hdiff_call(stencil_dtype dtype, const stencil_field* u, stencil_field* out,
                   const int64_t domain[3], double coeff, void* mask, const stencil_options* opts,
-                  hipStream_t stream) {
+                  hipStream_t stream,
+                  const DevCoeff* dev) {
   TRY(check_dtype(dtype));
   TRY(check_domain(domain));
   TRY(check_opts(opts));
@@ -463,12 +474,19 @@ int stencil_hdiff(stencil_dtype dtype, const stencil_field* u, stencil_field* ou
   }
   if (domain_empty(domain)) return ok();
   ResolvedOpts r = resolve_opts(opts, dtype, STENCIL_OP_HDIFF, domain);
+  r.dev = dev;
   if (variant_opts(opts) && r.impl == STENCIL_IMPL_PLAIN)
     return fail(STENCIL_E_UNSUPPORTED, "the generalised diffusion runs the fused kernels only");
   if (r.impl == STENCIL_IMPL_PLAIN) TRY(need_plain_ws(r, plain_ws_bytes(es, domain)));
   TRY(check_device());
   return dtype == STENCIL_F64 ? run_hdiff<double>(u, out, domain, coeff, mask, r, stream)
                               : run_hdiff<float>(u, out, domain, coeff, mask, r, stream);
+}
+
+int stencil_hdiff(stencil_dtype dtype, const stencil_field* u, stencil_field* out,
+                  const int64_t domain[3], double coeff, void* mask, const stencil_options* opts,
+                  hipStream_t stream) {
+  return hdiff_call(dtype, u, out, domain, coeff, mask, opts, stream, nullptr);
 }
 
 int stencil_vadv(stencil_dtype dtype, const stencil_field* u, const stencil_field* data,
@@ -496,9 +514,10 @@ int stencil_vadv(stencil_dtype dtype, const stencil_field* u, const stencil_fiel
                               : run_vadv<float>(u, data, w, out, domain, dt_dz, r, stream);
 }
 
-int stencil_step(stencil_dtype dtype, const stencil_field* u, const stencil_field* data,
+static int step_call(stencil_dtype dtype, const stencil_field* u, const stencil_field* data,
                  const stencil_field* w, stencil_field* out, const int64_t domain[3], double coeff,
-                 double dt_dz, void* mask, const stencil_options* opts, hipStream_t stream) {
+                 double dt_dz, void* mask, const stencil_options* opts, hipStream_t stream,
+                  const DevCoeff* dev) {
   TRY(check_dtype(dtype));
   TRY(check_domain(domain));
   TRY(check_opts(opts));
@@ -523,6 +542,7 @@ int stencil_step(stencil_dtype dtype, const stencil_field* u, const stencil_fiel
   TRY(check_coeff_field(opts, domain, es, "out", so));
   if (domain_empty(domain)) return ok();
   ResolvedOpts r = resolve_opts(opts, dtype, STENCIL_OP_STEP, domain);
+  r.dev = dev;
   if (variant_opts(opts)) {
     if (r.impl == STENCIL_IMPL_PLAIN)
       return fail(STENCIL_E_UNSUPPORTED, "the generalised diffusion runs the fused kernels only");
@@ -542,6 +562,12 @@ int stencil_step(stencil_dtype dtype, const stencil_field* u, const stencil_fiel
   return periodic ? stencil_halo_update(dtype, out, domain, STENCIL_BOUNDARY_PERIODIC, stream) : ok();
 }
 
+int stencil_step(stencil_dtype dtype, const stencil_field* u, const stencil_field* data,
+                 const stencil_field* w, stencil_field* out, const int64_t domain[3], double coeff,
+                 double dt_dz, void* mask, const stencil_options* opts, hipStream_t stream) {
+  return step_call(dtype, u, data, w, out, domain, coeff, dt_dz, mask, opts, stream, nullptr);
+}
+
 int stencil_halo_update(stencil_dtype dtype, stencil_field* f, const int64_t domain[3], int boundary,
                         hipStream_t stream) {
   TRY(check_dtype(dtype));
@@ -558,9 +584,10 @@ int stencil_halo_update(stencil_dtype dtype, stencil_field* f, const int64_t dom
   return hip_status(e, "periodic halo update");
 }
 
-int stencil_hdiff_adjoint(stencil_dtype dtype, const stencil_field* out_bar, const void* mask,
+static int hdiff_adjoint_call(stencil_dtype dtype, const stencil_field* out_bar, const void* mask,
                           stencil_field* u_bar, const int64_t domain[3], double coeff,
-                          const stencil_options* opts, hipStream_t stream) {
+                          const stencil_options* opts, hipStream_t stream,
+                  const DevCoeff* dev) {
   TRY(check_dtype(dtype));
   TRY(check_domain(domain));
   TRY(check_opts(opts));
@@ -578,6 +605,7 @@ int stencil_hdiff_adjoint(stencil_dtype dtype, const stencil_field* out_bar, con
     TRY(check_no_alias("u_bar", sb, "mask", m));
   }
   ResolvedOpts r = resolve_opts(opts, dtype, STENCIL_OP_HDIFF_ADJOINT, domain);
+  r.dev = dev;
   TRY(check_device());
   if (dtype == STENCIL_F64) {
     return run_hdiff_adjoint<double>(at_origin<double>(out_bar), out_bar->stride[1], out_bar->stride[2],
@@ -585,6 +613,12 @@ int stencil_hdiff_adjoint(stencil_dtype dtype, const stencil_field* out_bar, con
   }
   return run_hdiff_adjoint<float>(at_origin<float>(out_bar), out_bar->stride[1], out_bar->stride[2],
                                   mask, u_bar, domain, coeff, r, stream);
+}
+
+int stencil_hdiff_adjoint(stencil_dtype dtype, const stencil_field* out_bar, const void* mask,
+                          stencil_field* u_bar, const int64_t domain[3], double coeff,
+                          const stencil_options* opts, hipStream_t stream) {
+  return hdiff_adjoint_call(dtype, out_bar, mask, u_bar, domain, coeff, opts, stream, nullptr);
 }
 
 int stencil_vadv_adjoint(stencil_dtype dtype, const stencil_field* x_bar, const stencil_field* w,
@@ -614,10 +648,11 @@ int stencil_vadv_adjoint(stencil_dtype dtype, const stencil_field* x_bar, const 
                                  domain, dt_dz, r, r.ws, stream);
 }
 
-int stencil_step_adjoint(stencil_dtype dtype, const stencil_field* x_bar, const stencil_field* w,
+static int step_adjoint_call(stencil_dtype dtype, const stencil_field* x_bar, const stencil_field* w,
                          const void* mask, stencil_field* u_bar, stencil_field* data_bar,
                          const int64_t domain[3], double coeff, double dt_dz,
-                         const stencil_options* opts, hipStream_t stream) {
+                         const stencil_options* opts, hipStream_t stream,
+                  const DevCoeff* dev) {
   TRY(check_dtype(dtype));
   TRY(check_domain(domain));
   TRY(check_opts(opts));
@@ -645,6 +680,7 @@ int stencil_step_adjoint(stencil_dtype dtype, const stencil_field* x_bar, const 
     TRY(check_no_alias("u_bar", sb, "mask", m));
   }
   ResolvedOpts r = resolve_opts(opts, dtype, STENCIL_OP_STEP_ADJOINT, domain);
+  r.dev = dev;
   const bool plain = r.impl == STENCIL_IMPL_PLAIN || domain[2] > kMaxFusedNk;
   if (r.impl == STENCIL_IMPL_FUSED && domain[2] > kMaxFusedNk)
     return fail(STENCIL_E_UNSUPPORTED, "nk = %lld exceeds the fused column limit %d", (long long)domain[2], kMaxFusedNk);
@@ -678,6 +714,92 @@ int stencil_step_adjoint(stencil_dtype dtype, const stencil_field* x_bar, const 
     }
     if (!empty) TRY(run_vadv_adjoint<T>(x_bar, w, lam, l_sj, l_sk, domain, dt_dz, r, rest, stream));
     return run_hdiff_adjoint<T>(lam, l_sj, l_sk, mask, u_bar, domain, coeff, r, stream);
+  };
+  return dtype == STENCIL_F64 ? go(double(0)) : go(float(0));
+}
+
+int stencil_step_adjoint(stencil_dtype dtype, const stencil_field* x_bar, const stencil_field* w,
+                         const void* mask, stencil_field* u_bar, stencil_field* data_bar,
+                         const int64_t domain[3], double coeff, double dt_dz,
+                         const stencil_options* opts, hipStream_t stream) {
+  return step_adjoint_call(dtype, x_bar, w, mask, u_bar, data_bar, domain, coeff, dt_dz, opts, stream, nullptr);
+}
+
+// ------------------------------------------------------------------ training calls
+// Fields over contiguous (k, j, i) buffers: h points of halo, `extra` more levels.
+static stencil_field dense(const void* p, const int64_t* dom, int h, int extra) {
+  const int64_t x = dom[0] + 2 * h, y = dom[1] + 2 * h;
+  return stencil_field{const_cast<void*>(p), {x, y, dom[2] + extra}, {1, x, x * y}, {h, h, 0}};
+}
+
+int stencil_train_forward(stencil_dtype dtype, const void* u, const void* data, const void* w, void* out,
+                          void* mask, const void* kappa, double coeff, const void* coeff_dev,
+                          stencil_dtype coeff_dtype, void* coeff_copy, int64_t ni, int64_t nj, int64_t nk,
+                          double dt_dz, int form, hipStream_t stream) {
+  const int64_t dom[3] = {ni, nj, nk};
+  TRY(check_dtype(dtype));
+  TRY(check_domain(dom));
+  if (coeff_dev) {
+    if (kappa) return fail(STENCIL_E_ARG, "both a coefficient field and a scalar coefficient in device memory");
+    TRY(check_dtype(coeff_dtype));
+    if (!coeff_copy) return fail(STENCIL_E_NULL, "coeff_copy is NULL");
+    if (w && nk > split_step_limit((int)esize(dtype)))
+      return fail(STENCIL_E_UNSUPPORTED, "a coefficient in device memory takes nk <= %d", split_step_limit((int)esize(dtype)));
+  }
+  const stencil_field fu = dense(u, dom, 2, 0), fk = dense(kappa, dom, 0, 0);
+  stencil_field fo = dense(out, dom, 0, 0);
+  stencil_options o;
+  memset(&o, 0, sizeof o);
+  o.hdiff_form = form;
+  o.coeff_field = kappa ? const_cast<stencil_field*>(&fk) : nullptr;
+  const DevCoeff dev{coeff_dev, coeff_dtype == STENCIL_F64, coeff_copy};
+  const DevCoeff* d = coeff_dev ? &dev : nullptr;
+  if (!w) return hdiff_call(dtype, &fu, &fo, dom, coeff, mask, &o, stream, d);
+  const stencil_field fd = dense(data, dom, 0, 0), fw = dense(w, dom, 0, 1);
+  return step_call(dtype, &fu, &fd, &fw, &fo, dom, coeff, dt_dz, mask, &o, stream, d);
+}
+
+int stencil_train_backward(stencil_dtype dtype, const void* x_bar, const void* mask, const void* u, const void* w,
+                           const void* x, const void* kappa, double coeff, const void* coeff_copy, void* u_bar,
+                           void* data_bar, void* w_bar, void* kappa_bar, void* coeff_bar, void* ws,
+                           size_t ws_bytes, int64_t ni, int64_t nj, int64_t nk, double dt_dz, int form,
+                           hipStream_t stream) {
+  const int64_t dom[3] = {ni, nj, nk};
+  TRY(check_dtype(dtype));
+  TRY(check_domain(dom));
+  if ((kappa_bar || coeff_bar) && !u) return fail(STENCIL_E_NULL, "u is NULL");
+  if (w_bar && !(w && x)) return fail(STENCIL_E_NULL, "w_bar needs w and x");
+  if (coeff_bar && kappa) return fail(STENCIL_E_ARG, "a coefficient field has no scalar coeff_bar");
+  if (coeff_bar && !domain_empty(dom) && ws_bytes < stencil_param_workspace_bytes(dtype, dom))
+    return fail(STENCIL_E_WORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", ws_bytes,
+                stencil_param_workspace_bytes(dtype, dom));
+  const stencil_field fx = dense(x_bar, dom, 0, 0), fk = dense(kappa, dom, 0, 0), fw = dense(w, dom, 0, 1);
+  stencil_field fb = dense(u_bar, dom, 2, 0), fd = dense(data_bar, dom, 0, 0);
+  stencil_options o;
+  memset(&o, 0, sizeof o);
+  o.hdiff_form = form;
+  o.coeff_field = kappa ? const_cast<stencil_field*>(&fk) : nullptr;
+  const DevCoeff dev{coeff_copy, false, nullptr};
+  const DevCoeff* d = coeff_copy ? &dev : nullptr;
+  if (w) TRY(step_adjoint_call(dtype, &fx, &fw, mask, &fb, &fd, dom, coeff, dt_dz, &o, stream, d));
+  else TRY(hdiff_adjoint_call(dtype, &fx, mask, &fb, dom, coeff, &o, stream, d));
+  if (!kappa_bar && !coeff_bar && !w_bar) return ok();
+  auto go = [&](auto tag) -> int {
+    using T = decltype(tag);
+    const stencil_field fu = dense(u, dom, 2, 0), lam = dense(w ? data_bar : x_bar, dom, 0, 0);
+    stencil_field kb = dense(kappa_bar, dom, 0, 0), wb = dense(w_bar, dom, 0, 1);
+    StepArgs<T> A = step_args<T>(u ? &fu : nullptr, &lam, nullptr, kappa_bar ? &kb : nullptr, dom, 0.0, dt_dz, nullptr);
+    A.form = form;
+    if (kappa_bar && !domain_empty(dom)) TRY(hip_status(launch_coeff_field_grad<T>(A, stream), "coefficient field gradient"));
+    if (!coeff_bar && !w_bar) return ok();
+    WGradArgs<T> W;
+    if (w_bar) {
+      const stencil_field xo = dense(x, dom, 0, 0);
+      W = w_grad_args<T>(&fw, &xo, &lam, &wb, dom, dt_dz);
+    }
+    return hip_status(launch_param_grads<T>(A, w_bar ? &W : nullptr, static_cast<double*>(ws), (int64_t)(ws_bytes / 8),
+                                            coeff_bar, dtype == STENCIL_F32, stream),
+                      "step parameter gradients");
   };
   return dtype == STENCIL_F64 ? go(double(0)) : go(float(0));
 }

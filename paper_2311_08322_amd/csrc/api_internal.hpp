@@ -9,6 +9,7 @@
 
 #include "../../include/stencil.h"
 #include "common.hpp"
+#include "launch.hpp"
 
 #define TRY(x)            \
   do {                    \
@@ -47,6 +48,14 @@ struct ResolvedOpts {
   int form;                    // stencil_hdiff_form
   const stencil_field* kappa;  // per-point coefficient or null
   int order;                   // stencil_tile_order (resolved: XCD or DISPATCH)
+  const struct DevCoeff* dev;  // a scalar coefficient in device memory, or null
+};
+// `copy` (nullable): where a forward call keeps the value in the fields' type,
+// which is where an adjoint call reads it (f64 then says nothing)
+struct DevCoeff {
+  const void* p;
+  bool f64;
+  void* copy;
 };
 // Tile shapes of the fused forward kernels: 256 columns (64x4, 32x8,
 // 16x16: 512-lane workgroups in the two-ended step) or, in the two-ended
@@ -80,6 +89,16 @@ template <typename T>
 AdjArgs<T> adj_args(const stencil_field* xbar, const stencil_field* w, T* lam, int64_t l_sj,
                     int64_t l_sk, stencil_field* ubar, const int64_t* dom, double coeff,
                     double dt_dz, const void* mask);
+
+template <typename T>
+inline WGradArgs<T> w_grad_args(const stencil_field* w, const stencil_field* x, const stencil_field* lam,
+                                stencil_field* w_bar, const int64_t* dom, double dt_dz) {
+  return WGradArgs<T>{at_origin<T>(w),         w->stride[1],     w->stride[2],     at_origin<T>(x),
+                      x->stride[1],            x->stride[2],     at_origin<T>(lam), lam->stride[1],
+                      lam->stride[2],          at_origin_mut<T>(w_bar), w_bar->stride[1], w_bar->stride[2],
+                      (int)dom[0],             (int)dom[1],      (int)dom[2],      0,
+                      (T)(0.25 * dt_dz)};
+}
 
 // batched forward (batched.cpp).  ItemSpans: the buffers one
 // item reads and writes.  check_step_batch validates the arguments and

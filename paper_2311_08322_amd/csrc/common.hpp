@@ -274,7 +274,22 @@ struct StepArgs {
   int form;  // 0: lap = 4u - sum of the neighbours; 1: the damping form, lap = sum - 4u
   int order;  // tile order of the two-ended step: 2 = dispatch order, else XCD runs
   int tile_i;  // batched launches: the tile width of this item's field (64, 32 or 16)
+  // a scalar coefficient in device memory, of 4 (binary32) or 8 bytes, instead of
+  // coeff (0: none): kappa is then null, c_sj holds its address and c_sk that
+  // where a step leaves the value in T for the adjoint, or 0
+  int coeff_bytes;
 };
+
+template <typename T>
+__device__ __forceinline__ T step_coeff(const StepArgs<T>& A) {
+  if (A.coeff_bytes == 0) return A.coeff;  // uniform
+  return A.coeff_bytes == 8 ? (T) * reinterpret_cast<const double*>(A.c_sj) : (T) * reinterpret_cast<const float*>(A.c_sj);
+}
+// kept by one lane of the launch
+template <typename T>
+__device__ __forceinline__ void keep_coeff(const StepArgs<T>& A, T coeff) {
+  if (A.coeff_bytes && A.c_sk && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *reinterpret_cast<T*>(A.c_sk) = coeff;
+}
 
 // Sign that folds the damping form into the stated one: its Laplacian,
 // fluxes and divergence are the exact negatives of the stated ones, so it
@@ -299,11 +314,16 @@ struct AdjArgs {
   MaskLayout ml;
   int ni, nj, nk;
   int tiles_i, ntiles;
+  int coeff_in_memory;  // a scalar coefficient at the address c_sj (kappa null; coeff holds the form's sign)
   T coeff, r4;
   // per-point coefficient of the generalised diffusion (null: the scalar
   // coeff); with it, coeff holds the form's sign
   const T* kappa;
   int64_t c_sj, c_sk;
 };
+template <typename T>
+__device__ __forceinline__ T adjoint_coeff(const AdjArgs<T>& A) {
+  return A.coeff_in_memory ? A.coeff * *reinterpret_cast<const T*>(A.c_sj) : A.coeff;  // uniform
+}
 
 }  // namespace gt4mi

@@ -38,7 +38,7 @@ __device__ __forceinline__ void hdiff_adjoint_strip(const AdjArgs<T>& A, int t, 
   const bool iI = i >= 0 && i < ni;
   const bool has_mask = A.mask != nullptr;
   const bool outc = lane >= 2 && lane < 2 + kStripOut && i < ni + 2;
-  const T ncoeff = -A.coeff;
+  const T ncoeff = -adjoint_coeff(A);
 
   // Every access goes through a descriptor of one row (uniform: its base
   // and a window of the row's width, 0 for a row outside the field) and a
@@ -157,7 +157,7 @@ __device__ __forceinline__ void hdiff_adjoint_strip2(const AdjArgs<float>& A, in
   const bool aI = ia >= 0 && ia < ni, bI = ib >= 0 && ib < ni;
   const bool has_mask = A.mask != nullptr;
   const bool outl = lane >= 1 && lane <= 62;
-  const T ncoeff = -A.coeff;
+  const T ncoeff = -adjoint_coeff(A);
 
   const auto row_rsrc = [&](const char* base, int64_t row_bytes, int r, int rows, uint32_t width) {
     const bool in = r >= 0 && r < rows;

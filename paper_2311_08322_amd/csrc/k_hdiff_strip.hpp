@@ -45,6 +45,29 @@ constexpr int kHStripPD = 4;     // u rows in flight ahead of their use
 // The sum takes 4 (10 and 20: 256x256x80 FP64 30.3 and 33.9 us against 28.4).
 constexpr int kHStripPD2 = 5;
 
+// A sum carried to twice the precision of binary64: hi is the plain sum, lo what
+// its additions rounded off (Knuth's TwoSum), so that the order of the addends,
+// which the domain's split fixes, does not show in the result.  Where hi is not
+// finite, lo means nothing.
+struct Sum2 {
+  double hi, lo;
+  __device__ __forceinline__ void add(double p, double e) {
+#pragma clang fp contract(off)
+    const double t = hi + p, z = t - hi;
+    lo += ((hi - (t - z)) + (p - z)) + e;
+    hi = t;
+  }
+  __device__ __forceinline__ void add_product(double a, double b) {
+#pragma clang fp contract(off)
+    const double p = a * b;
+    add(p, __builtin_fma(a, b, -p));
+  }
+  // binary32 factors: the product is exact, and the plain sum's error (1e-16 of
+  // it) is far below the factors' own rounding
+  __device__ __forceinline__ void add_product(float a, float b) { hi += (double)a * (double)b; }
+  __device__ __forceinline__ double value() const { return __builtin_isfinite(hi) ? hi + lo : hi; }
+};
+
 enum HdiffMode { kHPlain, kHVar, kHKappaBar, kHCoeffBar };
 
 // the second field of a mode: kappa (VAR) or lam, which sits in the data slot
@@ -71,7 +94,7 @@ struct HdiffSecond {
 // The strip `t` (A.tiles_i strips in i times the row blocks in j) at level k.
 // Returns the lane's share of the sum (kHCoeffBar).
 template <typename T, int TJ, int PD, int MODE>
-__device__ __forceinline__ double hdiff_strip(const StepArgs<T>& A, int t, int k) {
+__device__ __forceinline__ Sum2 hdiff_strip(const StepArgs<T>& A, int t, int k) {
   static_assert((TJ + 4) % PD == 0, "the row walk is unrolled by the prefetch depth");
   constexpr uint32_t S = sizeof(T);
   const int lane = threadIdx.x & 63;
@@ -82,10 +105,11 @@ __device__ __forceinline__ double hdiff_strip(const StepArgs<T>& A, int t, int k
   const bool own = lane >= 4 && lane < 4 + kHStripOut && i < ni;
   constexpr bool SUM = MODE == kHCoeffBar;
   const bool has_mask = (MODE == kHPlain || MODE == kHVar) && A.mask != nullptr;
-  const T coeff = A.coeff;
+  const T coeff = MODE == kHPlain || MODE == kHVar ? step_coeff(A) : T(0);
+  if constexpr (MODE == kHPlain || MODE == kHVar) keep_coeff(A, coeff);
   const T gs = MODE == kHPlain ? T(1) : form_sign<T>(A.form);
   const HdiffSecond<MODE, T> second(A);
-  [[maybe_unused]] double sum = 0.0;
+  Sum2 sum{0.0, 0.0};
 
   // One descriptor per row (uniform base, a window of the row's width, empty
   // for a row outside the field) and a lane offset fixed for the walk.
@@ -150,7 +174,7 @@ __device__ __forceinline__ double hdiff_strip(const StepArgs<T>& A, int t, int k
     const T div = (Fx2 - Fxw2) + (Fy2 - Fy3);
     const bool qrow = q >= j0 && q < j0 + TJ;  // uniform
     if constexpr (SUM) {
-      if (qrow && q < nj) sum += own ? (double)x2 * (double)(gs * div) : 0.0;
+      if (qrow && q < nj) sum.add_product(own ? x2 : T(0), own ? gs * div : T(0));
     }
     T v;
     if constexpr (MODE == kHPlain) v = u2 - coeff * div;
@@ -206,7 +230,7 @@ __device__ __forceinline__ uint32_t spread4(uint32_t v) {
 // (pair_at).  Reading odd rows column by column took 30.2 us at 501x403x60
 // against 26.2.
 template <int TJ, int PD, int MODE, bool ODD>
-__device__ __forceinline__ double hdiff_strip2(const StepArgs<float>& A, int t, int k) {
+__device__ __forceinline__ Sum2 hdiff_strip2(const StepArgs<float>& A, int t, int k) {
   static_assert((TJ + 4) % PD == 0, "the row walk is unrolled by the prefetch depth");
   using T = float;
   constexpr uint32_t S = 4;
@@ -219,10 +243,11 @@ __device__ __forceinline__ double hdiff_strip2(const StepArgs<float>& A, int t, 
   const bool ownb = lane >= 2 && lane < 2 + kHStripOut2 / 2 && ib < ni;
   constexpr bool SUM = MODE == kHCoeffBar;
   const bool has_mask = (MODE == kHPlain || MODE == kHVar) && A.mask != nullptr;
-  const T coeff = A.coeff;
+  const T coeff = MODE == kHPlain || MODE == kHVar ? step_coeff(A) : T(0);
+  if constexpr (MODE == kHPlain || MODE == kHVar) keep_coeff(A, coeff);
   const T gs = MODE == kHPlain ? T(1) : form_sign<T>(A.form);
   const HdiffSecond<MODE, T> second(A);
-  [[maybe_unused]] double sum = 0.0;
+  Sum2 sum{0.0, 0.0};
 
   const auto row_rsrc = [&](const char* base, int64_t row_bytes, int r, int rows, uint32_t width) {
     const bool in = r >= 0 && r < rows;
@@ -294,8 +319,8 @@ __device__ __forceinline__ double hdiff_strip2(const StepArgs<float>& A, int t, 
     const bool qrow = q >= j0 && q < j0 + TJ;  // uniform
     if constexpr (SUM) {
       if (qrow && q < nj) {
-        sum += owna ? (double)x2a * (double)(gs * diva) : 0.0;
-        sum += ownb ? (double)x2b * (double)(gs * divb) : 0.0;
+        sum.add_product(owna ? x2a : T(0), owna ? gs * diva : T(0));
+        sum.add_product(ownb ? x2b : T(0), ownb ? gs * divb : T(0));
       }
     }
     T va, vb;
@@ -350,7 +375,7 @@ __device__ __forceinline__ double hdiff_strip2(const StepArgs<float>& A, int t, 
 
 // LANE: columns per lane, 1, 2 (FP32, even ni) or 3: two with odd ni.
 template <typename T, int MODE, int LANE>
-__device__ __forceinline__ double hdiff_strip_of(const StepArgs<T>& A, int t, int k) {
+__device__ __forceinline__ Sum2 hdiff_strip_of(const StepArgs<T>& A, int t, int k) {
     constexpr int PD = MODE == kHPlain || MODE == kHCoeffBar ? kHStripPD : kHStripPD2;
   if constexpr (LANE > 1) return hdiff_strip2<kHStripRows, PD, MODE, LANE == 3>(A, t, k);
   else return hdiff_strip<T, kHStripRows, PD, MODE>(A, t, k);

@@ -26,35 +26,41 @@ namespace gt4mi {
 // 77 to 92 and 90; FP32 31 and 20, 39 and 26, 54 and 47).
 template <typename T, int LANE>
 __global__ void __launch_bounds__(kWG) k_coeff_partial(StepArgs<T> A, int levels, double* partial) {
-  __shared__ double red[kStripsPerWG];
+  __shared__ Sum2 red[kStripsPerWG];
   const int wave = threadIdx.x >> 6;
   const int t = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * kStripsPerWG + wave);
   const int k0 = blockIdx.y * levels, k1 = min(k0 + levels, A.nk);
-  double s = 0.0;
+  Sum2 s{0.0, 0.0};
   if (t < A.ntiles)
-    for (int k = k0; k < k1; ++k) s += hdiff_strip_of<T, kHCoeffBar, LANE>(A, t, k);
+    for (int k = k0; k < k1; ++k) {
+      const Sum2 l = hdiff_strip_of<T, kHCoeffBar, LANE>(A, t, k);
+      s.add(l.hi, l.lo);
+    }
 #pragma unroll
-  for (int h = 32; h > 0; h >>= 1) s += __shfl_down(s, h);
+  for (int h = 32; h > 0; h >>= 1) s.add(__shfl_down(s.hi, h), __shfl_down(s.lo, h));
   if ((threadIdx.x & 63) == 0) red[wave] = s;
   __syncthreads();
-  if (threadIdx.x == 0) partial[blockIdx.y * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (threadIdx.x) return;
+  for (int w = 1; w < kStripsPerWG; ++w) s.add(red[w].hi, red[w].lo);
+  partial[blockIdx.y * gridDim.x + blockIdx.x] = s.value();
 }
 
 // coeff_bar = -(sum of the partials), summed in a fixed order by one workgroup.
 constexpr int kFinalWG = 1024;
-__global__ void __launch_bounds__(kFinalWG) k_coeff_final(const double* partial, int n, double* coeff_bar) {
-  __shared__ double red[kFinalWG];
+__global__ void __launch_bounds__(kFinalWG) k_coeff_final(const double* partial, int n, void* coeff_bar, bool f32) {
+  __shared__ Sum2 red[kFinalWG / 64];
   const int tid = threadIdx.x;
-  double s = 0.0;
-  for (int p = tid; p < n; p += kFinalWG) s += partial[p];
-  red[tid] = s;
-  __syncthreads();
+  Sum2 s{0.0, 0.0};
+  for (int p = tid; p < n; p += kFinalWG) s.add(partial[p], 0.0);
 #pragma unroll
-  for (int h = kFinalWG / 2; h > 0; h >>= 1) {
-    if (tid < h) red[tid] += red[tid + h];
-    __syncthreads();
-  }
-  if (tid == 0) coeff_bar[0] = n > 0 ? -red[0] : 0.0;
+  for (int h = 32; h > 0; h >>= 1) s.add(__shfl_down(s.hi, h), __shfl_down(s.lo, h));
+  if ((tid & 63) == 0) red[tid >> 6] = s;
+  __syncthreads();
+  if (tid) return;
+  for (int w = 1; w < kFinalWG / 64; ++w) s.add(red[w].hi, red[w].lo);
+  const double v = n > 0 ? -s.value() : 0.0;
+  if (f32) *static_cast<float*>(coeff_bar) = (float)v;
+  else *static_cast<double*>(coeff_bar) = v;
 }
 
 // w_bar per column, one lane per column of a 64 x 4 tile, marching the
@@ -108,7 +114,7 @@ int64_t coeff_partial_most(bool f64, int64_t ni, int64_t nj, int64_t nk) {
 
 template <typename T>
 hipError_t launch_param_grads(const StepArgs<T>& Ain, const WGradArgs<T>* W, double* partial, int64_t slots,
-                              double* coeff_bar, hipStream_t s) {
+                              void* coeff_bar, bool f32, hipStream_t s) {
   StepArgs<T> A = Ain;
   const bool some = A.ni > 0 && A.nj > 0;
   if (coeff_bar) {
@@ -126,7 +132,7 @@ hipError_t launch_param_grads(const StepArgs<T>& Ain, const WGradArgs<T>* W, dou
         hipLaunchKernelGGL((k_coeff_partial<T, decltype(lane)::value>), grid, dim3(kWG), 0, s, A, levels, partial);
       });
     }
-    hipLaunchKernelGGL(k_coeff_final, dim3(1), dim3(kFinalWG), 0, s, partial, n, coeff_bar);
+    hipLaunchKernelGGL(k_coeff_final, dim3(1), dim3(kFinalWG), 0, s, partial, n, coeff_bar, f32);
   }
   if (W && some) {
     WGradArgs<T> B = *W;
@@ -154,9 +160,9 @@ hipError_t launch_coeff_field_grad(const StepArgs<T>& A, hipStream_t s) {
 
 template hipError_t launch_coeff_field_grad<float>(const StepArgs<float>&, hipStream_t);
 template hipError_t launch_coeff_field_grad<double>(const StepArgs<double>&, hipStream_t);
-template hipError_t launch_param_grads<float>(const StepArgs<float>&, const WGradArgs<float>*, double*, int64_t, double*,
+template hipError_t launch_param_grads<float>(const StepArgs<float>&, const WGradArgs<float>*, double*, int64_t, void*, bool,
                                               hipStream_t);
-template hipError_t launch_param_grads<double>(const StepArgs<double>&, const WGradArgs<double>*, double*, int64_t, double*,
+template hipError_t launch_param_grads<double>(const StepArgs<double>&, const WGradArgs<double>*, double*, int64_t, void*, bool,
                                                hipStream_t);
 
 }  // namespace gt4mi

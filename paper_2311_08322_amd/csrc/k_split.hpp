@@ -162,7 +162,8 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
   T ev[NKH];
   T fv[COL == 1 ? NKH : 1];
   T wp = T(0), e = T(0), f = T(0);
-  const T coeff = A.coeff;
+  const T coeff = step_coeff(A);
+  keep_coeff(A, coeff);
   [[maybe_unused]] const T gs = form_sign<T>(A.form);
   const T sn = half ? A.r4 : -A.r4;  // near coefficient per unit w: top a = -r/4 w, bottom c = +r/4 w
   const int cu = (t.tj + 2) * HI + (t.ti + 2);

@@ -374,6 +374,8 @@ __global__ void __launch_bounds__(TI* TJ) k_hdiff_fused(StepArgs<T> A) {
   const LevelView vk = level_view(has_kappa ? A.kappa : A.u, A.c_sj, A.c_sk, 0, 0, has_kappa ? A.nj : 0);
   const uint32_t koff = ((uint32_t)t.ic + (uint32_t)t.jc * (uint32_t)A.c_sj) * (uint32_t)sizeof(T);
   const T gs = form_sign<T>(A.form);
+  const T coeff = step_coeff(A);
+  keep_coeff(A, coeff);
   T pu[NLD], pk = T(0);
   {
     const auto ru = vu.at(kbeg);
@@ -396,9 +398,9 @@ __global__ void __launch_bounds__(TI* TJ) k_hdiff_fused(StepArgs<T> A) {
     bool kxr, kxl, kyr, kyl;
     T h;
     if constexpr (VAR)
-      h = hdiff_var_of(load_diamond<T, HI>(U + cu), has_kappa ? kk : A.coeff, gs, kxr, kxl, kyr, kyl);
+      h = hdiff_var_of(load_diamond<T, HI>(U + cu), has_kappa ? kk : coeff, gs, kxr, kxl, kyr, kyl);
     else
-      h = hdiff_diamond<T, HI>(U + cu, A.coeff, kxr, kxl, kyr, kyl);
+      h = hdiff_diamond<T, HI>(U + cu, coeff, kxr, kxl, kyr, kyl);
     if (A.mask) mw.record<TI>(k, active, kxr, kyr, kxl, kyl);
     if (active) buf_st(vo.at(k), ooff, h);
   }

@@ -159,10 +159,10 @@ struct WGradArgs {
 inline int64_t coeff_partial_least(int64_t ni, int64_t nj) { return ((ni + 63) / 64) * ((nj + 3) / 4); }
 int64_t coeff_partial_most(bool f64, int64_t ni, int64_t nj, int64_t nk);
 // A: u (halo) and lam in the data slot; W may be NULL (no w_bar); coeff_bar may
-// be NULL (no reduction; partial unused); slots: doubles at partial
+// be NULL (no reduction; partial unused), a float if f32; slots: doubles at partial
 template <typename T>
 hipError_t launch_param_grads(const StepArgs<T>& A, const WGradArgs<T>* W, double* partial, int64_t slots,
-                              double* coeff_bar, hipStream_t s);
+                              void* coeff_bar, bool f32, hipStream_t s);
 
 // gradient of a per-point coefficient: A.out(p) = -A.data(p) D(u)(p)
 // (A.data holds lam; A.form selects the Laplacian form)

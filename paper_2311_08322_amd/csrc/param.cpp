@@ -33,26 +33,8 @@ int run(const stencil_field* u, const stencil_field* w, const stencil_field* x, 
   StepArgs<T> A = step_args<T>(u, lam, nullptr, nullptr, dom, 0.0, dt_dz, nullptr);
   A.form = form;
   WGradArgs<T> W;
-  memset(&W, 0, sizeof W);
-  if (w_bar) {
-    W.w = at_origin<T>(w);
-    W.w_sj = w->stride[1];
-    W.w_sk = w->stride[2];
-    W.x = at_origin<T>(x);
-    W.x_sj = x->stride[1];
-    W.x_sk = x->stride[2];
-    W.lam = at_origin<T>(lam);
-    W.l_sj = lam->stride[1];
-    W.l_sk = lam->stride[2];
-    W.wbar = at_origin_mut<T>(w_bar);
-    W.b_sj = w_bar->stride[1];
-    W.b_sk = w_bar->stride[2];
-    W.ni = (int)dom[0];
-    W.nj = (int)dom[1];
-    W.nk = (int)dom[2];
-    W.q = (T)(0.25 * dt_dz);
-  }
-  return hip_status(launch_param_grads<T>(A, w_bar ? &W : nullptr, static_cast<double*>(ws), (int64_t)(ws_bytes / 8), coeff_bar, s),
+  if (w_bar) W = w_grad_args<T>(w, x, lam, w_bar, dom, dt_dz);
+  return hip_status(launch_param_grads<T>(A, w_bar ? &W : nullptr, static_cast<double*>(ws), (int64_t)(ws_bytes / 8), coeff_bar, false, s),
                     "step parameter gradients");
 }
 

@@ -29,6 +29,7 @@ from typing import Dict, Optional
 
 import torch
 
+from .. import api
 from . import build as _build
 from . import ir
 from .analysis import StencilAnalysisError, analyse
@@ -161,33 +162,26 @@ class StencilObject:
             domain = tuple(max(0, x) for x in d)
         domain = tuple(int(x) for x in domain)
         L = self.build(dts)
-        arr = (_build.GtsField * max(1, len(fl)))()
-        for idx, (name, t, o) in enumerate(fl):
-            shp = (t.shape[2], t.shape[1], t.shape[0])
-            st = (t.stride(2), t.stride(1), t.stride(0))
-            f = arr[idx]
-            f.data = t.data_ptr() + (o[0] * st[0] + o[1] * st[1] + o[2] * st[2]) * t.element_size()
-            for ax in range(3):
-                f.stride[ax] = st[ax]
-                f.lo[ax] = o[ax]
-                f.hi[ax] = shp[ax] - o[ax]
+        words = []  # the GtsField of each field: data, then stride, lo and hi in (i, j, k)
+        for name, t, o in fl:
+            sk, sj, si = t.stride()
+            nk, nj, ni = t.shape
+            words += (t.data_ptr() + (o[0] * si + o[1] * sj + o[2] * sk) * t.element_size(), si, sj, sk, *o,
+                      ni - o[0], nj - o[1], nk - o[2])
+        arr = (ctypes.c_int64 * max(10, len(words)))(*words)
         sc = (ctypes.c_double * max(1, len(sd.scalars)))(*[float(scalars[s]) for s in sd.scalars])
         dom = (ctypes.c_int64 * 3)(*domain)
         nb = L.gts_workspace_bytes(dom)
-        if stream is None:
-            ts = torch.cuda.current_stream() if torch.cuda.is_available() else None
-        elif isinstance(stream, int):
-            ts = torch.cuda.ExternalStream(stream)
-        else:
-            ts = stream
-        s = ts.cuda_stream if ts is not None else None
+        s = api._stream(stream)
         ws = None
         if nb:
             # one workspace per call from torch's caching allocator, tied to the
             # stream the kernels run on (overlapping calls never share one)
             ws = torch.empty(nb + 256, dtype=torch.uint8, device=fl[0][1].device)
-            if ts is not None and ts != torch.cuda.current_stream():
-                ws.record_stream(ts)
+            if stream is not None:
+                ts = torch.cuda.ExternalStream(stream) if isinstance(stream, int) else stream
+                if ts != torch.cuda.current_stream():
+                    ws.record_stream(ts)
         wp = 0 if ws is None else (ws.data_ptr() + 255) // 256 * 256
         rc = L.gts_run(arr, len(fl), sc, len(sd.scalars), dom, wp or None, nb, s)
         if rc != 0:

@@ -72,7 +72,8 @@ class GtsField(ctypes.Structure):
 def load(path: str):
     L = ctypes.CDLL(path)
     L.gts_run.restype = ctypes.c_int
-    L.gts_run.argtypes = [ctypes.POINTER(GtsField), ctypes.c_int, ctypes.POINTER(ctypes.c_double), ctypes.c_int,
+    L.gts_run.argtypes = [ctypes.c_void_p, ctypes.c_int,  # an array of GtsField
+                          ctypes.POINTER(ctypes.c_double), ctypes.c_int,
                           ctypes.POINTER(ctypes.c_int64), ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     L.gts_workspace_bytes.restype = ctypes.c_size_t
     L.gts_workspace_bytes.argtypes = [ctypes.POINTER(ctypes.c_int64)]
