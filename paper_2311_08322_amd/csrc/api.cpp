@@ -742,6 +742,7 @@ int stencil_train_forward(stencil_dtype dtype, const void* u, const void* data, 
   if (coeff_dev) {
     if (kappa) return fail(STENCIL_E_ARG, "both a coefficient field and a scalar coefficient in device memory");
     TRY(check_dtype(coeff_dtype));
+    if (!mask) return fail(STENCIL_E_NULL, "mask is NULL");
     if (!coeff_copy) return fail(STENCIL_E_NULL, "coeff_copy is NULL");
     if (w && nk > split_step_limit((int)esize(dtype)))
       return fail(STENCIL_E_UNSUPPORTED, "a coefficient in device memory takes nk <= %d", split_step_limit((int)esize(dtype)));

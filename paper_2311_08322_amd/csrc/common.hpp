@@ -280,15 +280,22 @@ struct StepArgs {
   int coeff_bytes;
 };
 
+// Uniform reads through the scalar cache (the constant address space: nothing
+// writes a coefficient while a kernel reads it).
+template <typename V>
+__device__ __forceinline__ V scalar_at(int64_t address) {
+  return *reinterpret_cast<const __attribute__((address_space(4))) V*>(address);
+}
 template <typename T>
 __device__ __forceinline__ T step_coeff(const StepArgs<T>& A) {
   if (A.coeff_bytes == 0) return A.coeff;  // uniform
-  return A.coeff_bytes == 8 ? (T) * reinterpret_cast<const double*>(A.c_sj) : (T) * reinterpret_cast<const float*>(A.c_sj);
+  return A.coeff_bytes == 8 ? (T)scalar_at<double>(A.c_sj) : (T)scalar_at<float>(A.c_sj);
 }
-// kept by one lane of the launch
+// Kept by one lane of the launch, at the kernel's end.
 template <typename T>
 __device__ __forceinline__ void keep_coeff(const StepArgs<T>& A, T coeff) {
-  if (A.coeff_bytes && A.c_sk && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *reinterpret_cast<T*>(A.c_sk) = coeff;
+  if (A.coeff_bytes && A.c_sk && (blockIdx.x | blockIdx.y | threadIdx.x) == 0)
+    *reinterpret_cast<__attribute__((address_space(1))) T*>(A.c_sk) = coeff;
 }
 
 // Sign that folds the damping form into the stated one: its Laplacian,
@@ -323,7 +330,7 @@ struct AdjArgs {
 };
 template <typename T>
 __device__ __forceinline__ T adjoint_coeff(const AdjArgs<T>& A) {
-  return A.coeff_in_memory ? A.coeff * *reinterpret_cast<const T*>(A.c_sj) : A.coeff;  // uniform
+  return A.coeff_in_memory ? A.coeff * scalar_at<T>(A.c_sj) : A.coeff;  // uniform
 }
 
 }  // namespace gt4mi

@@ -106,7 +106,6 @@ __device__ __forceinline__ Sum2 hdiff_strip(const StepArgs<T>& A, int t, int k) 
   constexpr bool SUM = MODE == kHCoeffBar;
   const bool has_mask = (MODE == kHPlain || MODE == kHVar) && A.mask != nullptr;
   const T coeff = MODE == kHPlain || MODE == kHVar ? step_coeff(A) : T(0);
-  if constexpr (MODE == kHPlain || MODE == kHVar) keep_coeff(A, coeff);
   const T gs = MODE == kHPlain ? T(1) : form_sign<T>(A.form);
   const HdiffSecond<MODE, T> second(A);
   Sum2 sum{0.0, 0.0};
@@ -210,6 +209,7 @@ __device__ __forceinline__ Sum2 hdiff_strip(const StepArgs<T>& A, int t, int k) 
   }
 #pragma unroll
   for (int s = 0; s < PD; ++s) step(n + s, s, false);
+  if constexpr (MODE == kHPlain || MODE == kHVar) keep_coeff(A, coeff);
   return sum;
 }
 
@@ -244,7 +244,6 @@ __device__ __forceinline__ Sum2 hdiff_strip2(const StepArgs<float>& A, int t, in
   constexpr bool SUM = MODE == kHCoeffBar;
   const bool has_mask = (MODE == kHPlain || MODE == kHVar) && A.mask != nullptr;
   const T coeff = MODE == kHPlain || MODE == kHVar ? step_coeff(A) : T(0);
-  if constexpr (MODE == kHPlain || MODE == kHVar) keep_coeff(A, coeff);
   const T gs = MODE == kHPlain ? T(1) : form_sign<T>(A.form);
   const HdiffSecond<MODE, T> second(A);
   Sum2 sum{0.0, 0.0};
@@ -370,6 +369,7 @@ __device__ __forceinline__ Sum2 hdiff_strip2(const StepArgs<float>& A, int t, in
   }
 #pragma unroll
   for (int s = 0; s < PD; ++s) step(n + s, s, false);
+  if constexpr (MODE == kHPlain || MODE == kHVar) keep_coeff(A, coeff);
   return sum;
 }
 

@@ -375,7 +375,6 @@ __global__ void __launch_bounds__(TI* TJ) k_hdiff_fused(StepArgs<T> A) {
   const uint32_t koff = ((uint32_t)t.ic + (uint32_t)t.jc * (uint32_t)A.c_sj) * (uint32_t)sizeof(T);
   const T gs = form_sign<T>(A.form);
   const T coeff = step_coeff(A);
-  keep_coeff(A, coeff);
   T pu[NLD], pk = T(0);
   {
     const auto ru = vu.at(kbeg);
@@ -404,6 +403,7 @@ __global__ void __launch_bounds__(TI* TJ) k_hdiff_fused(StepArgs<T> A) {
     if (A.mask) mw.record<TI>(k, active, kxr, kyr, kxl, kyl);
     if (active) buf_st(vo.at(k), ooff, h);
   }
+  keep_coeff(A, coeff);
 }
 
 // ------------------------------------------------------------------ class dispatch
