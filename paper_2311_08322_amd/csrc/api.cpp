@@ -173,6 +173,7 @@ ResolvedOpts resolve_opts(const stencil_options* o, stencil_dtype dt, int op, co
   r.order = (o && o->tile_order) ? o->tile_order : ord;
   if (r.order != STENCIL_ORDER_DISPATCH) r.order = STENCIL_ORDER_XCD;
   r.dev = nullptr;
+  r.wrapped = false;
   return r;
 }
 
@@ -362,6 +363,7 @@ int run_step(const stencil_field* u, const stencil_field* data, const stencil_fi
   StepArgs<T> A = step_args<T>(u, data, w, out, dom, coeff, dt_dz, mask);
   apply_variant(A, r);
   A.order = r.order;
+  A.wrapped = r.wrapped;
   return hip_status(launch_step_fused<T>(A, r.tile_i, r.tile_j, r.column_store, s), "step (fused)");
 }
 
@@ -517,7 +519,7 @@ int stencil_vadv(stencil_dtype dtype, const stencil_field* u, const stencil_fiel
 static int step_call(stencil_dtype dtype, const stencil_field* u, const stencil_field* data,
                  const stencil_field* w, stencil_field* out, const int64_t domain[3], double coeff,
                  double dt_dz, void* mask, const stencil_options* opts, hipStream_t stream,
-                  const DevCoeff* dev) {
+                  const DevCoeff* dev, bool wrapped = false, bool fill = true) {
   TRY(check_dtype(dtype));
   TRY(check_domain(domain));
   TRY(check_opts(opts));
@@ -557,9 +559,10 @@ static int step_call(stencil_dtype dtype, const stencil_field* u, const stencil_
                 r.tile_i, r.tile_j, split_step_limit((int)es));
   if (r.impl == STENCIL_IMPL_PLAIN) TRY(need_plain_ws(r, plain_ws_bytes(es, domain)));
   TRY(check_device());
+  r.wrapped = wrapped;
   TRY(dtype == STENCIL_F64 ? run_step<double>(u, data, w, out, domain, coeff, dt_dz, mask, r, stream)
                            : run_step<float>(u, data, w, out, domain, coeff, dt_dz, mask, r, stream));
-  return periodic ? stencil_halo_update(dtype, out, domain, STENCIL_BOUNDARY_PERIODIC, stream) : ok();
+  return periodic && fill ? stencil_halo_update(dtype, out, domain, STENCIL_BOUNDARY_PERIODIC, stream) : ok();
 }
 
 int stencil_step(stencil_dtype dtype, const stencil_field* u, const stencil_field* data,
@@ -567,6 +570,28 @@ int stencil_step(stencil_dtype dtype, const stencil_field* u, const stencil_fiel
                  double dt_dz, void* mask, const stencil_options* opts, hipStream_t stream) {
   return step_call(dtype, u, data, w, out, domain, coeff, dt_dz, mask, opts, stream, nullptr);
 }
+
+}  // extern "C"
+
+namespace gt4mi {
+
+// the two-ended step, and a period no shorter than the halo
+bool loop_wraps(stencil_dtype dtype, const int64_t* dom, const stencil_options* opts) {
+  if (!opts || opts->boundary != STENCIL_BOUNDARY_PERIODIC || domain_empty(dom) || check_opts(opts)) return false;
+  const ResolvedOpts r = resolve_opts(opts, dtype, STENCIL_OP_STEP, dom);
+  return r.impl != STENCIL_IMPL_PLAIN && (variant_opts(opts) || r.column_store == STENCIL_COLUMN_SPLIT) &&
+         dom[2] <= split_step_limit((int)esize(dtype)) && dom[0] >= kHalo && dom[1] >= kHalo;
+}
+
+int loop_step(stencil_dtype dtype, const stencil_field* u, const stencil_field* data, const stencil_field* w,
+              stencil_field* out, const int64_t* dom, double coeff, double dt_dz, const stencil_options* opts,
+              bool wrapped, bool fill, hipStream_t stream) {
+  return step_call(dtype, u, data, w, out, dom, coeff, dt_dz, nullptr, opts, stream, nullptr, wrapped, fill);
+}
+
+}  // namespace gt4mi
+
+extern "C" {
 
 int stencil_halo_update(stencil_dtype dtype, stencil_field* f, const int64_t domain[3], int boundary,
                         hipStream_t stream) {

@@ -22,6 +22,12 @@ namespace gt4mi {
 int fail(int code, const char* fmt, ...);
 int ok();
 int hip_status(hipError_t e, const char* what);
+// A step inside a periodic loop.  wrapped: u is a state whose halo nobody filled;
+// fill: out's halo is filled.  loop_wraps: whether the steps can run so.
+bool loop_wraps(stencil_dtype dtype, const int64_t* dom, const stencil_options* opts);
+int loop_step(stencil_dtype dtype, const stencil_field* u, const stencil_field* data, const stencil_field* w,
+              stencil_field* out, const int64_t* dom, double coeff, double dt_dz, const stencil_options* opts,
+              bool wrapped, bool fill, hipStream_t stream);
 int check_device();
 int check_dtype(stencil_dtype dt);
 int check_domain(const int64_t* dom);
@@ -49,6 +55,7 @@ struct ResolvedOpts {
   const stencil_field* kappa;  // per-point coefficient or null
   int order;                   // stencil_tile_order (resolved: XCD or DISPATCH)
   const struct DevCoeff* dev;  // a scalar coefficient in device memory, or null
+  bool wrapped;                // StepArgs::wrapped
 };
 // `copy` (nullable): where a forward call keeps the value in the fields' type,
 // which is where an adjoint call reads it (f64 then says nothing)

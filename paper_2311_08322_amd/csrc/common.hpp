@@ -266,7 +266,8 @@ struct StepArgs {
   MaskLayout ml;
   int ni, nj, nk;
   int tiles_i, ntiles;
-  int k0, k1;  // level range of this launch (hdiff kernels)
+  int wrapped;   // the two-ended step takes u's halo from its interior, one period away (ni, nj >= 2)
+  int k1;        // levels per workgroup (k_hdiff_fused)
   T coeff, r4;  // r4 = dt_dz / 4
   // generalised diffusion (read only by the kernels built for it)
   const T* kappa;  // per-point coefficient at domain (0,0,0), or null (scalar coeff)
@@ -286,15 +287,31 @@ template <typename V>
 __device__ __forceinline__ V scalar_at(int64_t address) {
   return *reinterpret_cast<const __attribute__((address_space(4))) V*>(address);
 }
+// a value that every lane holds, in scalar registers
+__device__ __forceinline__ float uniform_value(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double uniform_value(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
 template <typename T>
 __device__ __forceinline__ T step_coeff(const StepArgs<T>& A) {
-  if (A.coeff_bytes == 0) return A.coeff;  // uniform
-  return A.coeff_bytes == 8 ? (T)scalar_at<double>(A.c_sj) : (T)scalar_at<float>(A.c_sj);
+  T c = A.coeff;
+  if (A.coeff_bytes)  // uniform
+    c = A.coeff_bytes == 8 ? (T)scalar_at<double>(A.c_sj) : (T)scalar_at<float>(A.c_sj);
+  return uniform_value(c);
 }
-// Kept by one lane of the launch, at the kernel's end.
+// The lane of the wave, formed on the spot: a kernel's end that needs it holds no
+// register for it throughout.
+__device__ __forceinline__ int lane_here() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+// Kept by one lane of the launch (wave: uniform, the wave of the workgroup), at
+// the kernel's end.
 template <typename T>
-__device__ __forceinline__ void keep_coeff(const StepArgs<T>& A, T coeff) {
-  if (A.coeff_bytes && A.c_sk && (blockIdx.x | blockIdx.y | threadIdx.x) == 0)
+__device__ __forceinline__ void keep_coeff(const StepArgs<T>& A, T coeff, int wave) {
+  if (A.coeff_bytes && A.c_sk && (blockIdx.x | blockIdx.y | (uint32_t)wave) == 0 && lane_here() == 0)
     *reinterpret_cast<__attribute__((address_space(1))) T*>(A.c_sk) = coeff;
 }
 

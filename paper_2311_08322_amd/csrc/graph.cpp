@@ -1,5 +1,5 @@
 // graph.cpp -- a time loop of stencil steps captured once into a HIP graph
-// and replayed with one launch (ping-pong state buffers, frozen halo).
+// and replayed with one launch (ping-pong state buffers, frozen or periodic halo).
 #include <hip/hip_runtime.h>
 
 #include "../../include/stencil.h"
@@ -12,6 +12,13 @@ struct stencil_graph {
 };
 
 using namespace gt4mi;
+
+template <typename T>
+static int fill_both(stencil_field* a, stencil_field* b, const int64_t* dom, hipStream_t s) {
+  return hip_status(launch_halo_periodic_pair<T>(at_origin_mut<T>(a), a->stride[1], a->stride[2], at_origin_mut<T>(b),
+                                                 b->stride[1], b->stride[2], (int)dom[0], (int)dom[1], (int)dom[2], s),
+                    "periodic halo update");
+}
 
 extern "C" {
 
@@ -35,11 +42,20 @@ int stencil_graph_capture_steps(stencil_dtype dtype, int nsteps, stencil_field* 
   hipError_t e = hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return hip_status(e, "hipStreamBeginCapture");
   int rc = STENCIL_OK;
+  // Periodic boundaries: the first step reads u_a's own halo; later ones take their
+  // halo points from the state's interior, so that only the states that the loop
+  // leaves behind need theirs filled, both by one launch at its end (a launch after
+  // each step cost 5 us: FP64 256x256x80, 8 steps 296 us).
+  const bool wraps = loop_wraps(dtype, domain, opts);
   for (int s = 0; s < nsteps && rc == STENCIL_OK; ++s) {
     const stencil_field* src = (s % 2 == 0) ? u_a : u_b;
     stencil_field* dst = (s % 2 == 0) ? u_b : u_a;
-    rc = stencil_step(dtype, src, data, w, dst, domain, coeff, dt_dz, nullptr, opts, stream);
+    rc = loop_step(dtype, src, data, w, dst, domain, coeff, dt_dz, opts, wraps && s > 0, !wraps, stream);
   }
+  if (wraps && rc == STENCIL_OK)
+    rc = nsteps == 1 ? stencil_halo_update(dtype, u_b, domain, STENCIL_BOUNDARY_PERIODIC, stream)
+         : dtype == STENCIL_F64 ? fill_both<double>(u_a, u_b, domain, stream)
+                                : fill_both<float>(u_a, u_b, domain, stream);
   hipGraph_t g = nullptr;
   e = hipStreamEndCapture(stream, &g);
   if (rc != STENCIL_OK) {

@@ -24,7 +24,6 @@ hipError_t launch_hdiff_fused(StepArgs<T> A, int tile_i, hipStream_t s) {
   A.ntiles = A.tiles_i * ((A.nj + tj - 1) / tj);
   int kper = A.nk;
   while (kper > 4 && (int64_t)A.ntiles * ((A.nk + kper - 1) / kper) < 4096) kper = (kper + 1) / 2;
-  A.k0 = 0;
   A.k1 = kper;
   dim3 grid(A.ntiles, (A.nk + kper - 1) / kper), block(kWG);
 #define GT4MI_HDIFF_LAUNCH(TI, TJ)                                                  \

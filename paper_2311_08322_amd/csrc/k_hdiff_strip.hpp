@@ -209,7 +209,7 @@ __device__ __forceinline__ Sum2 hdiff_strip(const StepArgs<T>& A, int t, int k) 
   }
 #pragma unroll
   for (int s = 0; s < PD; ++s) step(n + s, s, false);
-  if constexpr (MODE == kHPlain || MODE == kHVar) keep_coeff(A, coeff);
+  if constexpr (MODE == kHPlain || MODE == kHVar) keep_coeff(A, coeff, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6));
   return sum;
 }
 
@@ -369,7 +369,7 @@ __device__ __forceinline__ Sum2 hdiff_strip2(const StepArgs<float>& A, int t, in
   }
 #pragma unroll
   for (int s = 0; s < PD; ++s) step(n + s, s, false);
-  if constexpr (MODE == kHPlain || MODE == kHVar) keep_coeff(A, coeff);
+  if constexpr (MODE == kHPlain || MODE == kHVar) keep_coeff(A, coeff, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6));
   return sum;
 }
 

@@ -112,10 +112,11 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
   constexpr int NT = TA::NT, HI = TA::HI, NLD = TA::NLD;
   static_assert(NT == 256 || NT == 128, "a tile holds 256 or 128 columns");
 
-  const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);  // 0: top, 1: bottom
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int half = wave / (NT / 64);  // 0: top, 1: bottom
   const int ltid = threadIdx.x - half * NT;
   TA t;
-  t.init_lane(ltid, tile, A.tiles_i, A.ni, A.nj, A.u_sj);
+  t.init_lane(ltid, tile, A.tiles_i, A.ni, A.nj, A.u_sj, !MASK && A.wrapped);
   const int nk = A.nk, m = nk / 2;
   const int nlev = half ? nk - m : m;  // levels this half eliminates
   const int nsteps = nk - m;           // steps of the workgroup (the larger half)
@@ -249,7 +250,7 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
       buf_st<GT4MI_CP_ONCE>(ro, ooff, x);
     }
   }
-  if constexpr (MASK) keep_coeff(A, coeff);
+  if constexpr (MASK) keep_coeff(A, coeff, wave);
 }
 
 

@@ -172,8 +172,10 @@ struct TileAddr {
   __device__ __forceinline__ void init(int tile, int tiles_i, int ni, int nj, int64_t u_sj) {
     init_lane(threadIdx.x, tile, tiles_i, ni, nj, u_sj);
   }
-  // `tid`: the lane's index among the NT lanes that share the tile
-  __device__ __forceinline__ void init_lane(int tid, int tile, int tiles_i, int ni, int nj, int64_t u_sj) {
+  // `tid`: the lane's index among the NT lanes that share the tile; wrapped: halo
+  // points are read one period away, inside the domain
+  __device__ __forceinline__ void init_lane(int tid, int tile, int tiles_i, int ni, int nj, int64_t u_sj,
+                                            bool wrapped = false) {
     ti = tid % TI;
     tj = tid / TI;
     const int bi = tile % tiles_i, bj = tile / tiles_i;
@@ -188,7 +190,11 @@ struct TileAddr {
     for (int q = 0; q < NLD; ++q) {
       const int e = min(tid + q * NT, HN - 1);
       const int hj = e / HI, hi = e - hj * HI;
-      const int gi = min(i0 + hi, ni + 3), gj = min(j0 + hj, nj + 3);  // padded coordinates
+      int gi = min(i0 + hi, ni + 3), gj = min(j0 + hj, nj + 3);  // padded coordinates
+      if (wrapped) {  // uniform
+        gi += gi < 2 ? ni : gi >= ni + 2 ? -ni : 0;
+        gj += gj < 2 ? nj : gj >= nj + 2 ? -nj : 0;
+      }
       hoff[q] = ((uint32_t)gi + (uint32_t)gj * (uint32_t)u_sj) * (uint32_t)sizeof(T);
     }
   }
@@ -403,7 +409,7 @@ __global__ void __launch_bounds__(TI* TJ) k_hdiff_fused(StepArgs<T> A) {
     if (A.mask) mw.record<TI>(k, active, kxr, kyr, kxl, kyl);
     if (active) buf_st(vo.at(k), ooff, h);
   }
-  keep_coeff(A, coeff);
+  keep_coeff(A, coeff, __builtin_amdgcn_readfirstlane(tid >> 6));
 }
 
 // ------------------------------------------------------------------ class dispatch

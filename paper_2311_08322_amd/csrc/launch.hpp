@@ -173,6 +173,11 @@ hipError_t launch_coeff_field_grad(const StepArgs<T>& A, hipStream_t s);
 template <typename T>
 hipError_t launch_halo_periodic(T* p, int64_t sj, int64_t sk, int ni, int nj, int nk, hipStream_t s);
 
+// the same for two fields of one domain
+template <typename T>
+hipError_t launch_halo_periodic_pair(T* p, int64_t p_sj, int64_t p_sk, T* q, int64_t q_sj, int64_t q_sk, int ni, int nj,
+                                     int nk, hipStream_t s);
+
 // fill a strided box with a deterministic pattern (autotuner scratch)
 template <typename T>
 hipError_t launch_fill_pattern(T* p, int64_t n, T lo, T hi, uint32_t seed, hipStream_t s);
