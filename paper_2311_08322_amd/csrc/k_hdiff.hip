@@ -12,8 +12,8 @@ hipError_t launch_hdiff_fused(StepArgs<T> A, int tile_i, hipStream_t s) {
   // the walk addresses the mask through one 32-bit window
   const bool small_mask = A.mask == nullptr || A.ml.total <= (int64_t)kOffNone - 16;
   if (small_mask) {
-    // strips of 56 x kHStripRows outputs (FP32: 120, two columns per lane),
-    // four per workgroup, one level per grid row (the tile option does not apply)
+    // strips of 56 columns (FP32: 120, two columns per lane), four per workgroup,
+    // one level per grid row (the tile option does not apply)
     if (!var) return launch_hdiff_strip<T, kHPlain>(A, s);
     if (A.nk <= kMaxGridY) return launch_hdiff_strip<T, kHVar>(A, s);
   }

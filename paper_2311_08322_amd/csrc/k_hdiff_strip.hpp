@@ -10,7 +10,7 @@
 // are the same bit for bit.
 //
 // One wavefront owns 64 consecutive i (lane = i) of one level and walks
-// 16 + 4 rows in j, one u row loaded per step PD rows ahead; neighbours in i
+// 8 + 4 rows in j (HStrip), one u row loaded per step PD rows ahead; neighbours in i
 // come from DPP wave shifts, neighbours in j from the rows already walked.
 // Per step it forms lap of the row before the newest, its x fluxes, the y
 // fluxes below it, and out of the row two back: every value once.  Lanes
@@ -38,12 +38,21 @@
 namespace gt4mi {
 
 constexpr int kHStripOut = 56;   // output columns per strip: 7 bytes of a mask row
-constexpr int kHStripRows = 16;  // output rows per strip
-constexpr int kHStripPD = 4;     // u rows in flight ahead of their use
-// the same with a second field read and a result written (10 and 20 rows: FP32
-// kappa_bar 256x256x80 17.2 and 19.2 us against 16.3; FP64 the same within 2%).
-// The sum takes 4 (10 and 20: 256x256x80 FP64 30.3 and 33.9 us against 28.4).
-constexpr int kHStripPD2 = 5;
+// Output rows of a strip and rows in flight ahead of their use, by what the walk
+// does and its columns per lane (LANE below).  Eight rows with all twelve input
+// rows in flight against 16 and 4 (5 with a second field), on cold buffers: FP64
+// 512x512x80 67 against 68.5 us, with the mask 74 / 76, kappa field 92.5 / 96;
+// 256x256x80 19.0 / 20.4, 22.4 / 24.4, 27.5 / 29.3; FP32 with odd rows 501x403x60
+// 23.5 / 26.2 and 29 / 34.3, kappa field 512x512x80 50.7 / 53.2.  FP32 in aligned
+// pairs keeps 16 and 4 (256x256x80 10.7 against 11.3, with the mask 15.9 / 16.4),
+// as does the sum, which only reads (FP64 512x512x80 95 against 117 us, 3.9 TB/s:
+// what plain read streams reach).
+enum HdiffMode { kHPlain, kHVar, kHKappaBar, kHCoeffBar };
+template <int MODE, int LANE>
+struct HStrip {
+  static constexpr bool few = MODE == kHCoeffBar || (MODE == kHPlain && LANE == 2);
+  static constexpr int rows = few ? 16 : 8, pd = few ? 4 : 12;
+};
 
 // A sum carried to twice the precision of binary64: hi is the plain sum, lo what
 // its additions rounded off (Knuth's TwoSum), so that the order of the addends,
@@ -67,8 +76,6 @@ struct Sum2 {
   __device__ __forceinline__ void add_product(float a, float b) { hi += (double)a * (double)b; }
   __device__ __forceinline__ double value() const { return __builtin_isfinite(hi) ? hi + lo : hi; }
 };
-
-enum HdiffMode { kHPlain, kHVar, kHKappaBar, kHCoeffBar };
 
 // the second field of a mode: kappa (VAR) or lam, which sits in the data slot
 template <int MODE, typename T>
@@ -376,9 +383,9 @@ __device__ __forceinline__ Sum2 hdiff_strip2(const StepArgs<float>& A, int t, in
 // LANE: columns per lane, 1, 2 (FP32, even ni) or 3: two with odd ni.
 template <typename T, int MODE, int LANE>
 __device__ __forceinline__ Sum2 hdiff_strip_of(const StepArgs<T>& A, int t, int k) {
-    constexpr int PD = MODE == kHPlain || MODE == kHCoeffBar ? kHStripPD : kHStripPD2;
-  if constexpr (LANE > 1) return hdiff_strip2<kHStripRows, PD, MODE, LANE == 3>(A, t, k);
-  else return hdiff_strip<T, kHStripRows, PD, MODE>(A, t, k);
+    using H = HStrip<MODE, LANE>;
+  if constexpr (LANE > 1) return hdiff_strip2<H::rows, H::pd, MODE, LANE == 3>(A, t, k);
+  else return hdiff_strip<T, H::rows, H::pd, MODE>(A, t, k);
 }
 
 // One strip per wave, at one level per grid row.
@@ -391,12 +398,12 @@ __global__ void __launch_bounds__(kWG) k_hdiff_strip(StepArgs<T> A) {
   hdiff_strip_of<T, MODE, LANE>(A, t, blockIdx.y);
 }
 
-// strips of the walk in i and in all (a single column is one strip either way)
-template <typename T>
+// strips of the walk in i and in all
+template <typename T, int MODE, int LANE>
 inline void hdiff_strip_count(StepArgs<T>& A) {
-  constexpr int W = sizeof(T) == 4 ? kHStripOut2 : kHStripOut;
+  constexpr int W = LANE > 1 ? kHStripOut2 : kHStripOut, R = HStrip<MODE, LANE>::rows;
   A.tiles_i = (A.ni + W - 1) / W;
-  A.ntiles = A.tiles_i * ((A.nj + kHStripRows - 1) / kHStripRows);
+  A.ntiles = A.tiles_i * ((A.nj + R - 1) / R);
 }
 
 // calls go(LANE) for the domain
@@ -411,10 +418,11 @@ inline void hdiff_strip_lanes(const StepArgs<T>& A, F&& go) {
 
 template <typename T, int MODE>
 hipError_t launch_hdiff_strip(StepArgs<T> A, hipStream_t s) {
-  hdiff_strip_count(A);
-  const dim3 grid((A.ntiles + kStripsPerWG - 1) / kStripsPerWG, A.nk), block(kWG);
   hdiff_strip_lanes(A, [&](auto lane) {
-    hipLaunchKernelGGL((k_hdiff_strip<T, MODE, decltype(lane)::value>), grid, block, 0, s, A);
+    constexpr int L = decltype(lane)::value;
+    hdiff_strip_count<T, MODE, L>(A);
+    const dim3 grid((A.ntiles + kStripsPerWG - 1) / kStripsPerWG, A.nk), block(kWG);
+    hipLaunchKernelGGL((k_hdiff_strip<T, MODE, L>), grid, block, 0, s, A);
   });
   return hipGetLastError();
 }

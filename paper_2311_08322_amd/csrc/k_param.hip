@@ -63,8 +63,18 @@ __global__ void __launch_bounds__(kFinalWG) k_coeff_final(const double* partial,
   else *static_cast<double*>(coeff_bar) = v;
 }
 
-// w_bar per column, one lane per column of a 64 x 4 tile, marching the
-// staggered levels 0..nk with the level below in registers.
+// w_bar of a few staggered levels of a 64 x 4 tile's columns, a lane per column,
+// every load in flight before the first use; the level below is read again by the
+// run below.  Bound by memory (FP64 512x512x80 114 us: 5.9 TB/s of the four
+// streams).  One lane marching its column a level ahead kept too little in flight:
+// FP64 512x512x80 124 us, 256x256x80 53 (31 here), 301x203x137 91 (51); FP32 70
+// (62), 44 (16.6), 76 (28).  Levels per run 2, 4, 8, 16: FP64 512x512x80 114, 123,
+// 131, 132 us, FP32 60.5, 62, 67, 72, but 256x256x80 17.2, 16.6, 17.7, 18.0.
+// Runs of one tile side by side on an XCD were slower (130 us).
+template <typename T>
+constexpr int w_grad_levels() {
+  return sizeof(T) == 8 ? 2 : 4;
+}
 template <typename T>
 __global__ void __launch_bounds__(kWG) k_w_grad(WGradArgs<T> A) {
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -73,6 +83,7 @@ __global__ void __launch_bounds__(kWG) k_w_grad(WGradArgs<T> A) {
   const bool active = i < A.ni && j < A.nj;
   const int ic = min(i, A.ni - 1), jc = min(j, A.nj - 1);
   constexpr uint32_t S = sizeof(T);
+  constexpr int L = w_grad_levels<T>();
   const LevelView vw = level_view(A.w, A.w_sj, A.w_sk, 0, 0, A.nj);
   const LevelView vx = level_view(A.x, A.x_sj, A.x_sk, 0, 0, A.nj);
   const LevelView vl = level_view(A.lam, A.l_sj, A.l_sk, 0, 0, A.nj);
@@ -82,33 +93,37 @@ __global__ void __launch_bounds__(kWG) k_w_grad(WGradArgs<T> A) {
   const uint32_t loff = ((uint32_t)ic + (uint32_t)jc * (uint32_t)A.l_sj) * S;
   const uint32_t boff = active ? ((uint32_t)ic + (uint32_t)jc * (uint32_t)A.b_sj) * S : kOffNone;
   const int nk = A.nk;
-  // w_0 does not enter T
-  buf_st(vb.at(0), boff, T(0));
-  if (nk < 1) return;
-  T lp = buf_ld(vl.at(0), loff, T()), xp = buf_ld(vx.at(0), xoff, T());
-  // the loads of level j run one level ahead (clamped at the last level)
-  T ln = buf_ld(vl.at(min(1, nk - 1)), loff, T()), xn = buf_ld(vx.at(min(1, nk - 1)), xoff, T());
-  T wn = buf_ld(vw.at(1), woff, T());
-  for (int jl = 1; jl < nk; ++jl) {
-    const T lj = ln, xj = xn, wj = wn;
-    const int nx = min(jl + 1, nk - 1);
-    ln = buf_ld(vl.at(nx), loff, T());
-    xn = buf_ld(vx.at(nx), xoff, T());
-    wn = buf_ld(vw.at(min(jl + 1, nk)), woff, T());
-    const T s = wj > T(0) ? T(1) : (wj < T(0) ? T(-1) : T(0));
-    const T g = A.q * ((lj * xp - lp * xj) - s * (lj * xj + lp * xp));
-    buf_st(vb.at(jl), boff, g);
-    lp = lj;
-    xp = xj;
+  if (nk < 1) {  // one staggered level, no column
+    buf_st(vb.at(0), boff, T(0));
+    return;
   }
-  // w_nk does not enter T
-  buf_st(vb.at(nk), boff, T(0));
+  for (int k0 = blockIdx.y * L; k0 <= nk; k0 += gridDim.y * L) {
+    T l[L + 1], x[L + 1], w[L];
+#pragma unroll
+    for (int n = 0; n <= L; ++n) {  // levels k0 - 1 .. k0 + L - 1 (clamped: an edge level's value goes unused)
+      const int k = max(min(k0 + n - 1, nk - 1), 0);
+      l[n] = buf_ld(vl.at(k), loff, T());
+      x[n] = buf_ld(vx.at(k), xoff, T());
+      if (n) w[n - 1] = buf_ld(vw.at(min(k0 + n - 1, nk)), woff, T());
+    }
+    pin_prefetch();
+#pragma unroll
+    for (int n = 0; n < L; ++n) {
+      const int k = k0 + n;
+      if (k > nk) break;  // uniform
+      const T s = w[n] > T(0) ? T(1) : (w[n] < T(0) ? T(-1) : T(0));
+      const T g = A.q * ((l[n + 1] * x[n] - l[n] * x[n + 1]) - s * (l[n + 1] * x[n + 1] + l[n] * x[n]));
+      // w_0 and w_nk do not enter T
+      buf_st(vb.at(k), boff, k == 0 || k == nk ? T(0) : g);
+    }
+  }
 }
 
 // ------------------------------------------------------------------ launchers
 int64_t coeff_partial_most(bool f64, int64_t ni, int64_t nj, int64_t nk) {
   const int64_t w = f64 ? kHStripOut : kHStripOut2;
-  const int64_t strips = ((ni + w - 1) / w) * ((nj + kHStripRows - 1) / kHStripRows);
+  constexpr int R = HStrip<kHCoeffBar, 1>::rows;
+  const int64_t strips = ((ni + w - 1) / w) * ((nj + R - 1) / R);
   return (strips + kStripsPerWG - 1) / kStripsPerWG * std::min<int64_t>(nk, kMaxGridY);
 }
 
@@ -120,7 +135,7 @@ hipError_t launch_param_grads(const StepArgs<T>& Ain, const WGradArgs<T>* W, dou
   if (coeff_bar) {
     int n = 0;
     if (some && A.nk > 0) {
-      hdiff_strip_count(A);
+      hdiff_strip_lanes(A, [&](auto lane) { hdiff_strip_count<T, kHCoeffBar, decltype(lane)::value>(A); });
       // a run per level, or as many runs as the partials have room for (at least
       // one: a strip workgroup covers more columns than a 64 x 4 tile)
       const int64_t wgs = (A.ntiles + kStripsPerWG - 1) / kStripsPerWG;
@@ -138,7 +153,8 @@ hipError_t launch_param_grads(const StepArgs<T>& Ain, const WGradArgs<T>* W, dou
     WGradArgs<T> B = *W;
     B.tiles_i = (B.ni + 63) / 64;
     const int nt = B.tiles_i * ((B.nj + 3) / 4);
-    hipLaunchKernelGGL(k_w_grad<T>, dim3(nt), dim3(kWG), 0, s, B);
+    const int runs = B.nk / w_grad_levels<T>() + 1;  // of the nk + 1 staggered levels
+    hipLaunchKernelGGL(k_w_grad<T>, dim3(nt, std::min(runs, kMaxGridY)), dim3(kWG), 0, s, B);
   }
   return hipGetLastError();
 }
