@@ -215,7 +215,8 @@ struct LevelCursor {
   const char* p;
   int64_t step;
   uint32_t window;
-  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc() const { return make_rsrc(p, window); }
+  // on: 0 = an empty window, whose loads return zeros without reading memory
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(bool on = true) const { return make_rsrc(p, on ? window : 0u); }
   __device__ __forceinline__ void advance(bool go) { p += go ? step : 0; }
 };
 
@@ -228,6 +229,12 @@ struct LevelCursor {
 // An empty asm that clobbers memory keeps the loads where they are written
 // without forcing a wait for them.
 __device__ __forceinline__ void pin_prefetch() { __asm__ volatile("" ::: "memory"); }
+
+// Waits for every load in flight.  At the end of an unrolled column the last
+// prefetches are still counted, into registers that hold other values on the paths
+// where the column is longer, and the compiler would guard each of those values in
+// the substitution: waits between its stores, for the stores.
+__device__ __forceinline__ void drain_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0) alone
 
 // ------------------------------------------------------------ limiter
 // The flux is zeroed where flux * gradient > 0 (the workload's definition

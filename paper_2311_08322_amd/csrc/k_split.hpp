@@ -106,7 +106,8 @@ struct SplitSmem {
 
 // VAR: the generalised diffusion (per-point coefficient when A.kappa is
 // set, the scalar otherwise; the form's sign on the limiter and coefficient).
-template <typename T, int TI, int TJ, int NKH, int PD, bool MASK, int COL, bool VAR = false>
+// WRAP: A.wrapped counts (loops of single fields).
+template <typename T, int TI, int TJ, int NKH, int PD, bool MASK, int COL, bool VAR = false, bool WRAP = false>
 __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, SplitSmem<T, TI, TJ>& sm) {
   using TA = TileAddr<T, TI, TJ>;
   constexpr int NT = TA::NT, HI = TA::HI, NLD = TA::NLD;
@@ -116,7 +117,7 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
   const int half = wave / (NT / 64);  // 0: top, 1: bottom
   const int ltid = threadIdx.x - half * NT;
   TA t;
-  t.init_lane(ltid, tile, A.tiles_i, A.ni, A.nj, A.u_sj, !MASK && A.wrapped);
+  t.init_lane(ltid, tile, A.tiles_i, A.ni, A.nj, A.u_sj, WRAP && A.wrapped);
   const int nk = A.nk, m = nk / 2;
   const int nlev = half ? nk - m : m;  // levels this half eliminates
   const int nsteps = nk - m;           // steps of the workgroup (the larger half)
@@ -135,6 +136,15 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
 
   // Load cursors walk this half's levels in step order and hold at its last
   // level, so steps past it (odd nk, class padding) reload a valid level.
+  // The loads are pinned to their step (pin_prefetch).  In FP32 those past the half's
+  // last level read an empty window, and the column's end waits for them (DRAIN:
+  // see drain_loads).  Measured without either, with the pin, with both: FP32
+  // 400x300x90 75.5, 70.1, 67.3 us, 512x512x80 82.0, 81.8, 78.5, 32 fields 588, 583,
+  // 557; FP64 400x300x90 110.4, 106.8, 107.1, 256x256x80 37.1, 36.0, 36.2, 32
+  // fields 1009, 1010, 1016.
+  // FP32 saving a mask has stores in every step, which pin the loads by themselves:
+  // 512x512x80 87.7 us, with both 89.
+  constexpr bool PIN = sizeof(T) == 8 || !MASK, DRAIN = sizeof(T) == 4 && !MASK;
   LevelCursor cur_u{vu.base + (int64_t)k0 * vu.level_bytes, dir * vu.level_bytes, vu.window};
   LevelCursor cur_d{vd.base + (int64_t)k0 * vd.level_bytes, dir * vd.level_bytes, vd.window};
   LevelCursor cur_w{vw.base + (int64_t)(half ? k0 : 1) * vw.level_bytes, dir * vw.level_bytes, vw.window};
@@ -145,12 +155,13 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
   LevelCursor cur_k{vk.base + (int64_t)k0 * vk.level_bytes, dir * vk.level_bytes, vk.window};
   T pu[PD][NLD], pd[PD], pw[PD], pk[VAR ? PD : 1];
   auto issue = [&](int slot, int s) {
-    const auto ru = cur_u.rsrc();
+    const bool on = !DRAIN || s < nlev;
+    const auto ru = cur_u.rsrc(on);
 #pragma unroll
     for (int q = 0; q < NLD; ++q) pu[slot][q] = buf_ld<GT4MI_CP_HALO>(ru, t.hoff[q], T());
-    pd[slot] = buf_ld<GT4MI_CP_ONCE>(cur_d.rsrc(), doff, T());
-    pw[slot] = buf_ld<GT4MI_CP_ONCE>(cur_w.rsrc(), woff, T());  // the w level new at this step
-    if constexpr (VAR) pk[slot] = buf_ld<GT4MI_CP_ONCE>(cur_k.rsrc(), koff, T());
+    pd[slot] = buf_ld<GT4MI_CP_ONCE>(cur_d.rsrc(on), doff, T());
+    pw[slot] = buf_ld<GT4MI_CP_ONCE>(cur_w.rsrc(on), woff, T());  // the w level new at this step
+    if constexpr (VAR) pk[slot] = buf_ld<GT4MI_CP_ONCE>(cur_k.rsrc(on), koff, T());
     const bool go = s + 1 < nlev;
     cur_u.advance(go);
     cur_d.advance(go);
@@ -203,6 +214,7 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
     [[maybe_unused]] T kk = coeff;
     if constexpr (VAR) kk = has_kappa ? pk[slot] : coeff;
     if (s + PD < NKH) issue(slot, s + PD);
+    if constexpr (PIN) pin_prefetch();
     __syncthreads();
     const Diamond<T> dm = load_diamond<T, HI>(U + cu);
     if (s > 0) {
@@ -220,6 +232,7 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
     wq = wn;
     if constexpr (MASK) mr.record<TI>(min(max(k0 + dir * s, 0), nk - 1), s < nlev, active, kxr, kyr, kxl, kyl);
   }
+  if constexpr (DRAIN) drain_loads();
   {  // the elimination of the last step
     const int sl = nsteps - 1;
     const bool act = eliminate(sl);
@@ -257,7 +270,7 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
 template <typename T, int TI, int TJ, int NKH, int PD, bool MASK, int COL, bool VAR>
 __global__ void __launch_bounds__(2 * TI * TJ) k_step_split(StepArgs<T> A) {
   __shared__ SplitSmem<T, TI, TJ> sm;
-  step_split_tile<T, TI, TJ, NKH, PD, MASK, COL, VAR>(A, ordered_tile(A.order, blockIdx.x, gridDim.x), sm);
+  step_split_tile<T, TI, TJ, NKH, PD, MASK, COL, VAR, !MASK>(A, ordered_tile(A.order, blockIdx.x, gridDim.x), sm);
 }
 
 // One instantiation per half-column register class.  With the early exit a
