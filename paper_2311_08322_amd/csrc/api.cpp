@@ -147,11 +147,40 @@ static bool narrow_tile_runs(const ResolvedOpts& r, int op, stencil_dtype dt, co
          dom[2] <= split_step_limit((int)esize(dt));
 }
 
+// The two-ended step's tile where nothing chose one.  While the step's four fields
+// fit the last-level cache, a level costs its instructions, not its bytes: tiles of
+// 128 columns spread them over twice the workgroups (one wave per SIMD each where
+// the chip is not full) and, in FP64, 16-wide rows load the box in two passes
+// instead of three.  64x4 against 16x8 (FP64) and 32x4 (FP32), us: FP64 39x89x29
+// 12.1, 8.6, 128x128x80 28.3, 19.8, 256x200x80 30.6, 27.1; FP32 39x89x29 9.5, 8.3,
+// 256x200x80 22.8, 21.0.  From half the cache on (other buffers of the program share
+// it) only where 64x4 would leave the chip's last round of workgroups a third empty
+// or more: FP64 300x300x60 46.3, 36.1 (with mask 54.7, 41.5), 400x300x60 67.7, 49.0,
+// FP32 350x250x110 52.5, 31.4; but 256x256x80, one tile per CU, 33.8, 34.6.  Beyond
+// the cache 64x4 streams best (FP64 512x256x80 76.3, 87.0, 512x512x80 148, 163).
+// FP64 columns of 81..96 levels of the generalised step spill in 128-column tiles
+// (100x500x90 50, 65).
+constexpr int64_t kLastLevelCache = int64_t(256) << 20;
+constexpr int kCus = 256;
+static void default_step_tile(ResolvedOpts& r, stencil_dtype dt, const int64_t* dom, bool variant) {
+  const int64_t es = (int64_t)esize(dt), nk = dom[2], bytes = 4 * es * dom[0] * dom[1] * nk;
+  if (bytes > kLastLevelCache) return;
+  if (es == 8 && variant && nk > 80 && nk <= kSplitRegNkF64) return;
+  if (2 * bytes > kLastLevelCache) {
+    // workgroups of a 64x4 tile that a CU holds, by register class
+    const int64_t per_cu = es == 8 ? (nk <= 32 ? 2 : 1) : (nk <= 48 ? 3 : nk <= 80 ? 2 : 1), slots = kCus * per_cu;
+    const int64_t tiles = ((dom[0] + 63) / 64) * ((dom[1] + 3) / 4), idle = (slots - tiles % slots) % slots;
+    if (10 * idle < 3 * slots) return;
+  }
+  r.tile_i = es == 8 ? 16 : 32;
+  r.tile_j = 128 / r.tile_i;
+}
+
 ResolvedOpts resolve_opts(const stencil_options* o, stencil_dtype dt, int op, const int64_t* dom) {
   ResolvedOpts r;
   r.impl = o ? o->impl : STENCIL_IMPL_AUTO;
   int32_t ti = 0, tj = 0, col = 0, ord = 0;
-  tuning_get(dt, op, dom, &ti, &tj, &col, &ord);
+  const bool tuned = tuning_get(dt, op, dom, &ti, &tj, &col, &ord);
   const bool own_tile = o && o->tile_i;
   r.tile_i = own_tile ? o->tile_i : ti;
   r.tile_j = own_tile ? (o->tile_j ? o->tile_j : kWG / o->tile_i) : tj;
@@ -166,6 +195,7 @@ ResolvedOpts resolve_opts(const stencil_options* o, stencil_dtype dt, int op, co
   // (another column store, or columns past its limit) takes the 256-column
   // tile of the same width; a caller's own such tile is refused by the step
   if (!own_tile && !narrow_tile_runs(r, op, dt, dom)) r.tile_j = kWG / r.tile_i;
+  if (!own_tile && !tuned && narrow_tile_runs(r, op, dt, dom)) default_step_tile(r, dt, dom, variant_opts(o));
   r.ws = o ? o->workspace : nullptr;
   r.ws_bytes = o ? o->workspace_bytes : 0;
   r.form = o ? o->hdiff_form : STENCIL_HDIFF_STATED;
