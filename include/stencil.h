@@ -458,8 +458,8 @@ int stencil_autotune_fields(stencil_dtype dtype, int op, const stencil_field* u,
                             const stencil_field* data, const stencil_field* w, stencil_field* out,
                             const int64_t domain[3], int reps, hipStream_t stream, double* best_us);
 /* Tile, column store and tile order chosen for (dtype, op, domain) -- the
- * tuned entry or the table's default (an untuned step on a domain that fits the
- * caches takes a 128-column tile instead).  tile_order may be NULL. */
+ * tuned entry or the table's default (an untuned step whose domain fits the
+ * caches, or would leave 64x4 tiles partly idle, takes another tile).  tile_order may be NULL. */
 int stencil_tuning_lookup(stencil_dtype dtype, int op, const int64_t domain[3], int32_t* tile_i,
                           int32_t* tile_j, int32_t* column_store, int32_t* tile_order);
 /* Persist / restore the tuning table as JSON. */

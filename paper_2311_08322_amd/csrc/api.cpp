@@ -152,28 +152,39 @@ static bool narrow_tile_runs(const ResolvedOpts& r, int op, stencil_dtype dt, co
 // 128 columns spread them over twice the workgroups (one wave per SIMD each where
 // the chip is not full) and, in FP64, 16-wide rows load the box in two passes
 // instead of three.  64x4 against 16x8 (FP64) and 32x4 (FP32), us: FP64 39x89x29
-// 12.1, 8.6, 128x128x80 28.3, 19.8, 256x200x80 30.6, 27.1; FP32 39x89x29 9.5, 8.3,
-// 256x200x80 22.8, 21.0.  From half the cache on (other buffers of the program share
-// it) only where 64x4 would leave the chip's last round of workgroups a third empty
-// or more: FP64 300x300x60 46.3, 36.1 (with mask 54.7, 41.5), 400x300x60 67.7, 49.0,
-// FP32 350x250x110 52.5, 31.4; but 256x256x80, one tile per CU, 33.8, 34.6.  Beyond
-// the cache 64x4 streams best (FP64 512x256x80 76.3, 87.0, 512x512x80 148, 163).
-// FP64 columns of 81..96 levels of the generalised step spill in 128-column tiles
-// (100x500x90 50, 65).
+// 11.9, 8.3, 128x128x80 28.5, 20.0, 256x200x80 30.7, 29.8; FP32 39x89x29 9.2, 8.0,
+// 256x200x80 22.4, 20.6, 256x256x80 22.9, 21.1.  Past half the cache (other buffers
+// of the program share it) 64x4 loses where it leaves places for workgroups idle, a
+// tenth of them where a CU holds one workgroup: 64x4 against 32x4, FP64 501x403x60
+// 107, 98.6 (with mask 113, 104), 400x300x60 66.9, 48.9, 384x384x64 79.5, 73.0,
+// 400x256x100 104, 99.4; FP32 512x300x90 68.8, 52.4, 400x256x100 52.2, 49.3.  Where
+// a CU holds two, the other keeps it busy until a quarter is idle: FP32 400x300x60
+// 35.3, 25.6, FP64 512x300x32 36.2, 32.4, but FP32 512x400x80, 22% idle, 58.9, 60.7;
+// with three it does not matter (FP32 500x500x40, 35% idle, 35.5, 37.5).  With whole
+// rounds 32x8 is faster in FP64 while the fields fit the cache (256x256x80 32.4 to
+// 34.2, 30.6; the generalised step not: 512x512x28 69.5, 71.2) and 64x4
+// streams best elsewhere (against 32x4: FP64 512x256x80 74.6, 78.3, 512x512x80 151.4,
+// 152.5; FP32 512x256x80 33.4, 38.2, 512x512x80 77.9, 89.1).  FP64 columns of the
+// generalised step that spill with 128 columns keep 64x4: 81 to 96 levels
+// (512x300x90 155, 173), and longer ones on large domains (400x256x100 144, 158; but
+// 60x60x110 71.3, 55.5 and 200x200x100 78.5, 76.7 with 16x8).
 constexpr int64_t kLastLevelCache = int64_t(256) << 20;
 constexpr int kCus = 256;
 static void default_step_tile(ResolvedOpts& r, stencil_dtype dt, const int64_t* dom, bool variant) {
   const int64_t es = (int64_t)esize(dt), nk = dom[2], bytes = 4 * es * dom[0] * dom[1] * nk;
-  if (bytes > kLastLevelCache) return;
-  if (es == 8 && variant && nk > 80 && nk <= kSplitRegNkF64) return;
-  if (2 * bytes > kLastLevelCache) {
-    // workgroups of a 64x4 tile that a CU holds, by register class
-    const int64_t per_cu = es == 8 ? (nk <= 32 ? 2 : 1) : (nk <= 48 ? 3 : nk <= 80 ? 2 : 1), slots = kCus * per_cu;
-    const int64_t tiles = ((dom[0] + 63) / 64) * ((dom[1] + 3) / 4), idle = (slots - tiles % slots) % slots;
-    if (10 * idle < 3 * slots) return;
+  const bool f64 = es == 8, small = 2 * bytes <= kLastLevelCache;
+  if (f64 && variant && nk > 80 && (nk <= kSplitRegNkF64 || !small)) return;
+  // workgroups of a 64x4 tile that a CU holds, by register class
+  const int64_t per_cu = f64 ? (nk <= 32 ? 2 : 1) : (nk <= 48 ? 3 : nk <= 80 ? 2 : 1), slots = kCus * per_cu;
+  const int64_t tiles = ((dom[0] + 63) / 64) * ((dom[1] + 3) / 4), places = (tiles + slots - 1) / slots * slots;
+  const bool idle = per_cu < 3 && (per_cu == 1 ? 10 : 4) * (places - tiles) >= places;
+  if (small || idle) {
+    r.tile_i = f64 && small ? 16 : 32;
+    r.tile_j = 128 / r.tile_i;
+  } else if (f64 && !variant && bytes <= kLastLevelCache) {
+    r.tile_i = 32;
+    r.tile_j = 8;
   }
-  r.tile_i = es == 8 ? 16 : 32;
-  r.tile_j = 128 / r.tile_i;
 }
 
 ResolvedOpts resolve_opts(const stencil_options* o, stencil_dtype dt, int op, const int64_t* dom) {

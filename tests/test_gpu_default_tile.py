@@ -1,5 +1,5 @@
 """The untuned step's tile: on both sides of the rule (domains that fit half the
-last-level cache, whole rounds of workgroups, the generalised step's spilling
+last-level cache or all of it, whole rounds of workgroups or partly idle ones, the generalised step's spilling
 class) the default equals the 64 x 4 tile bit for bit, masks included."""
 import pytest
 import torch
@@ -11,7 +11,8 @@ DEV = "cuda"
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
-@pytest.mark.parametrize("dims", [(1, 1, 1), (17, 9, 31), (130, 61, 96), (33, 20, 144), (256, 256, 80), (300, 300, 60)],
+@pytest.mark.parametrize("dims", [(1, 1, 1), (17, 9, 31), (130, 61, 96), (33, 20, 144), (256, 256, 80), (300, 300, 60),
+                                  (384, 384, 64), (512, 512, 48)],
                          ids=lambda d: "x".join(map(str, d)))
 def test_default_tile(dims, dtype):
     ni, nj, nk = dims
