@@ -3,7 +3,7 @@
 // another, since fields run concurrently), the work list (fields sorted
 // longest column first, prefix sums of their work items) and its upload into
 // the caller's workspace, then one launch per kernel and register class of
-// the column length.  Workspace layout, each part 256-byte aligned:
+// the column length (small classes share one).  Workspace layout, each part 256-byte aligned:
 //   forward:  [header + prefix][argument blocks]
 //   adjoint:  [column table][horizontal table][lambda of items without data_bar]
 #include <hip/hip_runtime.h>
@@ -217,8 +217,33 @@ BatchRange table_range(const char* p, const std::vector<int32_t>& items, int e0,
 }
 
 // ---------------------------------------------------------------- forward
-// Each register class (step_batch_class) of the batch runs in a launch of its
-// own, the longest columns first.
+// Class of the launch in which each register class of the batch runs: its own,
+// or the next longer one present while it has less than two rounds of the chip's
+// workgroups (a CU holds one of FP64, two of FP32).  The tail of so short a launch
+// costs more than its class saves: one launch per class against this, us: 7 FP32
+// fields (about 200x200x100) 223, 205, 5 fields 101, 73, 24 fields 641, 638; FP64
+// 5 fields 148, 120, 7 fields 371, 348, 24 fields 1173, 1177.  All in one launch
+// loses on large batches (24 fields: FP32 655, FP64 1235).
+template <typename T>
+void merge_classes(const std::vector<int>& ord, const stencil_batch_item* it, int into[kStepBatchClasses]) {
+  constexpr int64_t two_rounds = sizeof(T) == 8 ? 512 : 1024;  // tiles of 256 columns
+  int64_t tiles[kStepBatchClasses] = {};
+  for (int a : ord) {
+    const int64_t* d = it[a].domain;
+    tiles[step_batch_class<T>(d[2])] += ((d[0] + 63) / 64) * ((d[1] + 3) / 4);
+  }
+  for (int c = 0; c < kStepBatchClasses; ++c) into[c] = c;
+  for (int c = kStepBatchClasses - 1; c > 0; --c) {
+    int longer = c - 1;
+    while (longer > 0 && tiles[longer] == 0) --longer;
+    if (tiles[c] >= two_rounds || tiles[longer] == 0) continue;
+    tiles[longer] += tiles[c];
+    for (int q = c; q < kStepBatchClasses; ++q)
+      if (into[q] == c) into[q] = longer;
+  }
+}
+
+// One launch per class that merge_classes leaves, the longest columns first.
 template <typename T>
 int run_step_batched(int n, const stencil_batch_item* it, void* ws, const stencil_options* opts, hipStream_t s) {
   constexpr stencil_dtype dt = sizeof(T) == 8 ? STENCIL_F64 : STENCIL_F32;
@@ -230,12 +255,14 @@ int run_step_batched(int n, const stencil_batch_item* it, void* ws, const stenci
   std::vector<int32_t> items(m);
   std::vector<int> cls(m);
   bool any_mask[kStepBatchClasses] = {};
+  int into[kStepBatchClasses];
+  merge_classes<T>(ord, it, into);
   int64_t total = 0;
   for (int e = 0; e < m; ++e) {
     const stencil_batch_item& x = it[ord[e]];
     StepArgs<T> A = step_args<T>(&x.u, &x.data, &x.w, const_cast<stencil_field*>(&x.out), x.domain, x.coeff,
                                  x.dt_dz, x.mask);
-    cls[e] = step_batch_class<T>(x.domain[2]);
+    cls[e] = into[step_batch_class<T>(x.domain[2])];
     const int nt = step_batch_nt<T>(cls[e]);
     A.tile_i = field_tile_i(opts, dt, x.domain, nt);
     const int tile_j = nt / A.tile_i;

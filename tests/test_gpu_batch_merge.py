@@ -1,0 +1,45 @@
+"""Batches whose short columns are few share the long columns' launch, many
+have one of their own: either way the batch equals the separate calls bit for
+bit.  65x5 is 4 tiles of 64x4; 2048x128 is the 1024 that FP32 needs for a launch,
+1024x128 the 512 of FP64."""
+import pytest
+import torch
+
+from paper_2311_08322_amd import api, fields, inputs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+BATCHES = {
+    "all_few": [(65, 5, 130), (65, 5, 90), (65, 5, 7)],
+    "middle_absent": [(33, 9, 144), (65, 5, 80)],
+    "short_many": [(65, 5, 130), (65, 5, 96), (2048, 128, 3)],
+    "middle_many": [(65, 5, 130), (2048, 128, 97), (65, 5, 3)],
+    "just_many_f64": [(65, 5, 100), (1024, 128, 5)],
+    "just_few_f64": [(65, 5, 100), (1024, 124, 5)],
+    "no_long": [(65, 5, 81), (65, 5, 2)],
+}
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("name", list(BATCHES))
+def test_batch_launches(name, dtype):
+    items, singles = [], []
+    for n, dom in enumerate(BATCHES[name]):
+        ni, nj, nk = dom
+        torch.manual_seed(n)
+        u = fields.alloc(ni, nj, nk, dtype, DEV)
+        data, out, ref = (fields.alloc(ni, nj, nk, dtype, DEV, halo=0, fill=0.0) for _ in range(3))
+        w = fields.alloc(ni, nj, nk, dtype, DEV, halo=0, kextra=1)
+        u.tensor.uniform_(0, 1), data.tensor.uniform_(0, 1), w.tensor.uniform_(-1, 1)
+        mask = fields.mask_tensor(dom, DEV) if n == 0 else None
+        items.append(dict(u=u, data=data, w=w, out=out, domain=dom, coeff=0.025, dt_dz=inputs.DT_DZ, mask=mask))
+        singles.append((ref, fields.mask_tensor(dom, DEV) if n == 0 else None))
+    print(f"batch {name} {dtype}", flush=True)
+    ws = torch.empty(api.stencil_batch_workspace_bytes(dtype, items), dtype=torch.uint8, device=DEV)
+    api.stencil_step_batched(dtype, items, ws)
+    for it, (ref, mask) in zip(items, singles):
+        api.stencil_step(it["u"], it["data"], it["w"], ref, it["domain"], 0.025, inputs.DT_DZ, mask=mask)
+    torch.cuda.synchronize()
+    for it, (ref, mask) in zip(items, singles):
+        assert torch.equal(fields.interior(it["out"], *it["domain"]), fields.interior(ref, *it["domain"]))
+        assert mask is None or torch.equal(it["mask"], mask)
