@@ -115,7 +115,7 @@ def copy_bandwidth(mib: int, reps: int) -> dict:
 
 
 def bench_batched(api, fields, inputs, time_eager, dtype) -> dict:
-    """The 32-field uneven workload: the forward step as one persistent
+    """The 32-field uneven workload: the forward step as one batched
     launch against 32 separate fused launches (and, in FP64, 32 plain
     per-stage chains), and the step adjoint of the batch (with data_bar)
     against 32 separate adjoint calls."""
@@ -591,13 +591,13 @@ def main():
                            "handwritten_speedup": round(t_gen / t_step, 3),
                            "what": "the step written in the stencil language: one generated kernel "
                                    "(the run of parallel computations fused into the forward sweep, the "
-                                   "backward sweep appended; c' and d' through a workspace), timed "
+                                   "backward sweep appended; c' and d' on chip as far as they fit), timed "
                                    "eagerly; the same algorithmic bytes as the fused step"}
         del u_a, u_b, data, w, xo
 
     # ------------------------------------------------ batched uneven fields
     if not args.only_step:
-        print("bench: 32 uneven fields, persistent launch vs separate launches", file=sys.stderr, flush=True)
+        print("bench: 32 uneven fields, batched vs separate launches", file=sys.stderr, flush=True)
         out["batched"] = bench_batched(api, fields, inputs, time_eager, torch.float64)
         out["batched_f32"] = bench_batched(api, fields, inputs, time_eager, torch.float32)
 
