@@ -334,7 +334,20 @@ int run_step_adjoint_batched(int n, const stencil_batch_adjoint_item* it, void* 
     }
   }
 
-  // column adjoints: 64-wide column tiles, one launch per register class
+  // column adjoints: 64-wide column tiles, one launch per register class; in FP32
+  // one for all while the short columns are fewer than 1024 tiles of 256: the tail
+  // of their launch costs more than the class saves (two launches against one, us,
+  // whole adjoint: 5 fields 87, 76, 10 fields 242, 231; unchanged from 14 on).  The
+  // long FP64 class takes no short column: its f of 36 levels per half in LDS needs
+  // halves of that many.
+  int64_t short_tiles = 0;
+  bool any_long = false;
+  for (int a : vord) {
+    const int64_t* d = it[a].domain;
+    if (d[2] > kVadjBatchedShortNk) any_long = true;
+    else short_tiles += ((d[0] + 63) / 64) * ((d[1] + 3) / 4);
+  }
+  const bool one_launch = sizeof(T) == 4 && any_long && short_tiles < 1024;
   std::vector<StepArgs<T>> vargs(mv);
   std::vector<int> vcls(mv);
   std::vector<int32_t> vitems(mv);
@@ -347,7 +360,7 @@ int run_step_adjoint_batched(int n, const stencil_batch_adjoint_item* it, void* 
     C.o_sj = lsj[a];
     C.o_sk = lsk[a];
     C.tiles_i = (C.ni + 63) / 64;
-    vcls[e] = C.nk > kVadjBatchedShortNk ? 0 : 1;
+    vcls[e] = one_launch || C.nk > kVadjBatchedShortNk ? 0 : 1;
     const int rows = vadj_batched_tile_rows(sizeof(T) == 8, vcls[e]);
     C.ntiles = C.tiles_i * ((C.nj + rows - 1) / rows);
     vargs[e] = C;

@@ -171,6 +171,8 @@ hipError_t launch_vadj_batched(int cls, const BatchRange& r, const StepArgs<T>* 
     hipLaunchKernelGGL(kernel, dim3(r.items), dim3(2 * nt), 0, s, r, ent);
     return hipGetLastError();
   };
+  // the host puts short FP32 columns into class 0, so it may stash no levels
+  static_assert(sizeof(T) == 8 || ColClass<T, 72>::lst == 0);
   return cls == 0 ? go(k_vadj_batched<T, 72>, ColClass<T, 72>::nt) : go(k_vadj_batched<T, 48>, ColClass<T, 48>::nt);
 }
 

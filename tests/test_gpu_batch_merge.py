@@ -43,3 +43,30 @@ def test_batch_launches(name, dtype):
     for it, (ref, mask) in zip(items, singles):
         assert torch.equal(fields.interior(it["out"], *it["domain"]), fields.interior(ref, *it["domain"]))
         assert mask is None or torch.equal(it["mask"], mask)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("dims", [[(65, 5, 130), (65, 5, 96), (33, 9, 1)], [(65, 5, 97), (2048, 128, 3)],
+                                  [(65, 5, 97), (2048, 124, 3)], [(65, 5, 96)]],
+                         ids=["few", "many", "just_few", "no_long"])
+def test_batch_adjoint_launches(dims, dtype):
+    items = []
+    for n, dom in enumerate(dims):
+        ni, nj, nk = dom
+        torch.manual_seed(n)
+        x = fields.alloc(ni, nj, nk, dtype, DEV, halo=0)
+        w = fields.alloc(ni, nj, nk, dtype, DEV, halo=0, kextra=1)
+        x.tensor.uniform_(-1, 1), w.tensor.uniform_(-1, 1)
+        mask = torch.randint(0, 256, fields.mask_tensor(dom, DEV).shape, dtype=torch.uint8, device=DEV)
+        items.append(dict(x_bar=x, w=w, mask=mask, u_bar=fields.alloc(ni, nj, nk, dtype, DEV, fill=0.0),
+                          data_bar=fields.alloc(ni, nj, nk, dtype, DEV, halo=0, fill=0.0), domain=dom, coeff=0.025,
+                          dt_dz=inputs.DT_DZ))
+    print(f"batch adjoint {dims} {dtype}", flush=True)
+    ws = torch.empty(api.stencil_batch_adjoint_workspace_bytes(dtype, items), dtype=torch.uint8, device=DEV)
+    api.stencil_step_adjoint_batched(dtype, items, ws)
+    for it in items:
+        dom = it["domain"]
+        ub, db = fields.alloc(*dom, dtype, DEV, fill=0.0), fields.alloc(*dom, dtype, DEV, halo=0, fill=0.0)
+        api.stencil_step_adjoint(it["x_bar"], it["w"], it["mask"], ub, db, dom, 0.025, inputs.DT_DZ)
+        torch.cuda.synchronize()
+        assert torch.equal(ub.tensor, it["u_bar"].tensor) and torch.equal(db.tensor, it["data_bar"].tensor), dom
