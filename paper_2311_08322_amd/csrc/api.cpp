@@ -586,6 +586,9 @@ static int step_call(stencil_dtype dtype, const stencil_field* u, const stencil_
   if (domain_empty(domain)) return ok();
   ResolvedOpts r = resolve_opts(opts, dtype, STENCIL_OP_STEP, domain);
   r.dev = dev;
+  // only the two-ended step reads a coefficient from device memory, whatever column
+  // store the tuning table holds (a one-lane entry's 256-column tile serves it too)
+  if (dev) r.column_store = STENCIL_COLUMN_SPLIT;
   if (variant_opts(opts)) {
     if (r.impl == STENCIL_IMPL_PLAIN)
       return fail(STENCIL_E_UNSUPPORTED, "the generalised diffusion runs the fused kernels only");

@@ -28,7 +28,11 @@ static hipError_t split_by_tile(const StepArgs<T>& A, int tile_i, bool var, hipS
 template <typename T>
 hipError_t launch_step_fused(StepArgs<T> A, int tile_i, int tile_j, int col, hipStream_t s) {
   const bool var = A.kappa != nullptr || A.form != 0;  // the generalised diffusion: two-ended step only
-  if (var || (col == 3 && A.nk <= split_step_limit(sizeof(T)))) {  // STENCIL_COLUMN_SPLIT
+  const bool split = var || (col == 3 && A.nk <= split_step_limit(sizeof(T)));  // STENCIL_COLUMN_SPLIT
+  // what only the two-ended step knows: a coefficient in device memory (its form
+  // that saves the mask), wrapped halo reads (the form that does not)
+  if ((A.coeff_bytes && !(split && A.mask)) || (A.wrapped && (!split || A.mask))) return hipErrorInvalidValue;
+  if (split) {
     if (A.nk > split_step_limit(sizeof(T))) return hipErrorInvalidValue;
     if constexpr (sizeof(T) == 8) {
       if (!var && A.nk > kSplitRegNkF64) {  // 97..144 levels: 128-column tiles, all in VGPRs
