@@ -74,8 +74,8 @@ def _merge_blocks(prun):
 class _Values:
     """Demand-driven evaluation of a PARALLEL block's variables: each (variable,
     version, offset) becomes one local.  A definition is an expression in the
-    environment (variable -> version) of its statement, or a selection by a
-    condition (an if/else)."""
+    environment (variable -> version) of its statement ("expr", or "cond" for
+    the condition of an if), or a selection by a condition ("sel")."""
 
     def __init__(self, pk):
         self.pk = pk
@@ -83,16 +83,16 @@ class _Values:
         self.memo = {}
         self.lines = []
 
-    def _new(self, name, d):
-        self.defs.append((name, d))
+    def _new(self, d):
+        self.defs.append(d)
         return len(self.defs) - 1
 
     def run(self, stmts, env):
         for s in stmts:
             if isinstance(s, ir.Assign):
-                env[s.target] = self._new(s.target, ("expr", s.value, dict(env)))
+                env[s.target] = self._new(("expr", s.value, dict(env)))
                 continue
-            c = self._new("cond", ("expr", s.cond, dict(env)))
+            c = self._new(("cond", s.cond, dict(env)))
             et, ee = dict(env), dict(env)
             self.run(s.then, et)
             self.run(s.orelse, ee)
@@ -101,14 +101,14 @@ class _Values:
                     continue
                 if n not in et or n not in ee:
                     raise Ineligible(f"{n} is written in one branch only")
-                env[n] = self._new(n, ("sel", c, et[n], ee[n]))
+                env[n] = self._new(("sel", c, et[n], ee[n]))
 
     def value(self, v, off):
         key = (v, off)
         if key in self.memo:
             return self.memo[key]
-        name, d = self.defs[v]
-        typ = "real"
+        d = self.defs[v]
+        typ = "bool" if d[0] == "cond" else "real"
         if d[0] == "sel":
             c, a, b = (self.value(x, off) for x in d[1:])
             text = f"({c} ? {a} : {b})"
@@ -116,9 +116,7 @@ class _Values:
             if off != (0, 0) and _costly(d[1]):
                 raise Ineligible("a costly value is read at an offset")
             text = self.pk.gen.expr(d[1], lambda a: self._access(a, d[2], off))
-            if name == "cond":
-                typ = "bool"
-        var = f"{'c' if name == 'cond' else 'v'}{v}_{_off(off[0])}{_off(off[1])}"
+        var = f"{typ[0]}{v}_{_off(off[0])}{_off(off[1])}"
         self.lines.append(f"const {typ} {var} = ({typ})({text});")
         self.pk.locals += 1
         if self.pk.locals > MAX_LOCALS:
