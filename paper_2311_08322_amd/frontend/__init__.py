@@ -166,7 +166,7 @@ class StencilObject:
         for name, t, o in fl:
             sk, sj, si = t.stride()
             nk, nj, ni = t.shape
-            words += (t.data_ptr() + (o[0] * si + o[1] * sj + o[2] * sk) * t.element_size(), si, sj, sk, *o,
+            words += (t.data_ptr() + (o[0] * si + o[1] * sj + o[2] * sk) * t.element_size(), si, sj, sk, *o[:3],
                       ni - o[0], nj - o[1], nk - o[2])
         arr = (ctypes.c_int64 * max(10, len(words)))(*words)
         sc = (ctypes.c_double * max(1, len(sd.scalars)))(*[float(scalars[s]) for s in sd.scalars])
