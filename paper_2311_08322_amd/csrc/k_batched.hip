@@ -146,12 +146,23 @@ __global__ void __launch_bounds__(kWG) k_hadj_batched(BatchRange r, const AdjArg
 }
 
 // ------------------------------------------------------------------ launchers
+// One workgroup of `lanes` per work item.  A grid counts its lanes in 32 bits and a
+// larger one is cut off without an error, so longer ranges take several launches
+// (kernels number their items from r.first).
+template <typename K, typename A>
+static hipError_t launch_range(K kernel, int lanes, BatchRange r, const A* ent, hipStream_t s) {
+  const int most = (int)(UINT32_MAX / (uint32_t)lanes);
+  for (int left = r.items; left > 0; left -= most, r.first += most) {
+    hipLaunchKernelGGL(kernel, dim3(left < most ? left : most), dim3(lanes), 0, s, r, ent);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 template <typename T>
 hipError_t launch_step_batched(int cls, const BatchRange& r, const StepArgs<T>* ent, bool mask, hipStream_t s) {
-  auto go = [&](auto kernel, int nt) {
-    hipLaunchKernelGGL(kernel, dim3(r.items), dim3(2 * nt), 0, s, r, ent);
-    return hipGetLastError();
-  };
+  auto go = [&](auto kernel, int nt) { return launch_range(kernel, 2 * nt, r, ent, s); };
 #define GT4MI_BATCH_STEP(C)                                                                               \
   if (cls == C) {                                                                                         \
     using K = StepBatchClass<T, C>;                                                                       \
@@ -167,10 +178,7 @@ hipError_t launch_step_batched(int cls, const BatchRange& r, const StepArgs<T>* 
 
 template <typename T>
 hipError_t launch_vadj_batched(int cls, const BatchRange& r, const StepArgs<T>* ent, hipStream_t s) {
-  auto go = [&](auto kernel, int nt) {
-    hipLaunchKernelGGL(kernel, dim3(r.items), dim3(2 * nt), 0, s, r, ent);
-    return hipGetLastError();
-  };
+  auto go = [&](auto kernel, int nt) { return launch_range(kernel, 2 * nt, r, ent, s); };
   // the host puts short FP32 columns into class 0, so it may stash no levels
   static_assert(sizeof(T) == 8 || ColClass<T, 72>::lst == 0);
   return cls == 0 ? go(k_vadj_batched<T, 72>, ColClass<T, 72>::nt) : go(k_vadj_batched<T, 48>, ColClass<T, 48>::nt);
@@ -178,8 +186,7 @@ hipError_t launch_vadj_batched(int cls, const BatchRange& r, const StepArgs<T>* 
 
 template <typename T>
 hipError_t launch_hadj_batched(const BatchRange& r, const AdjArgs<T>* ent, hipStream_t s) {
-  hipLaunchKernelGGL(k_hadj_batched<T>, dim3(r.items), dim3(kWG), 0, s, r, ent);
-  return hipGetLastError();
+  return launch_range(k_hadj_batched<T>, kWG, r, ent, s);
 }
 
 #ifdef GT4MI_UPLOAD
