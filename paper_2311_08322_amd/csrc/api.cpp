@@ -560,7 +560,7 @@ int stencil_vadv(stencil_dtype dtype, const stencil_field* u, const stencil_fiel
 static int step_call(stencil_dtype dtype, const stencil_field* u, const stencil_field* data,
                  const stencil_field* w, stencil_field* out, const int64_t domain[3], double coeff,
                  double dt_dz, void* mask, const stencil_options* opts, hipStream_t stream,
-                  const DevCoeff* dev, bool wrapped = false, bool fill = true) {
+                  const DevCoeff* dev, const LoopPlan* loop = nullptr, bool wrapped = false) {
   TRY(check_dtype(dtype));
   TRY(check_domain(domain));
   TRY(check_opts(opts));
@@ -584,7 +584,7 @@ static int step_call(stencil_dtype dtype, const stencil_field* u, const stencil_
   }
   TRY(check_coeff_field(opts, domain, es, "out", so));
   if (domain_empty(domain)) return ok();
-  ResolvedOpts r = resolve_opts(opts, dtype, STENCIL_OP_STEP, domain);
+  ResolvedOpts r = loop ? loop->opts : resolve_opts(opts, dtype, STENCIL_OP_STEP, domain);
   r.dev = dev;
   // only the two-ended step reads a coefficient from device memory, whatever column
   // store the tuning table holds (a one-lane entry's 256-column tile serves it too)
@@ -606,7 +606,7 @@ static int step_call(stencil_dtype dtype, const stencil_field* u, const stencil_
   r.wrapped = wrapped;
   TRY(dtype == STENCIL_F64 ? run_step<double>(u, data, w, out, domain, coeff, dt_dz, mask, r, stream)
                            : run_step<float>(u, data, w, out, domain, coeff, dt_dz, mask, r, stream));
-  return periodic && fill ? stencil_halo_update(dtype, out, domain, STENCIL_BOUNDARY_PERIODIC, stream) : ok();
+  return periodic && !(loop && loop->wraps) ? stencil_halo_update(dtype, out, domain, STENCIL_BOUNDARY_PERIODIC, stream) : ok();
 }
 
 int stencil_step(stencil_dtype dtype, const stencil_field* u, const stencil_field* data,
@@ -619,18 +619,21 @@ int stencil_step(stencil_dtype dtype, const stencil_field* u, const stencil_fiel
 
 namespace gt4mi {
 
-// the two-ended step, and a period no shorter than the halo
-bool loop_wraps(stencil_dtype dtype, const int64_t* dom, const stencil_options* opts) {
-  if (!opts || opts->boundary != STENCIL_BOUNDARY_PERIODIC || domain_empty(dom) || check_opts(opts)) return false;
-  const ResolvedOpts r = resolve_opts(opts, dtype, STENCIL_OP_STEP, dom);
-  return r.impl != STENCIL_IMPL_PLAIN && (variant_opts(opts) || r.column_store == STENCIL_COLUMN_SPLIT) &&
-         dom[2] <= split_step_limit((int)esize(dtype)) && dom[0] >= kHalo && dom[1] >= kHalo;
+int plan_loop(stencil_dtype dtype, const int64_t* dom, const stencil_options* opts, LoopPlan* p) {
+  TRY(check_opts(opts));
+  p->opts = resolve_opts(opts, dtype, STENCIL_OP_STEP, dom);
+  const ResolvedOpts& r = p->opts;
+  // the two-ended step, and a period no shorter than the halo
+  p->wraps = opts && opts->boundary == STENCIL_BOUNDARY_PERIODIC && !domain_empty(dom) &&
+             r.impl != STENCIL_IMPL_PLAIN && (variant_opts(opts) || r.column_store == STENCIL_COLUMN_SPLIT) &&
+             dom[2] <= split_step_limit((int)esize(dtype)) && dom[0] >= kHalo && dom[1] >= kHalo;
+  return STENCIL_OK;
 }
 
 int loop_step(stencil_dtype dtype, const stencil_field* u, const stencil_field* data, const stencil_field* w,
               stencil_field* out, const int64_t* dom, double coeff, double dt_dz, const stencil_options* opts,
-              bool wrapped, bool fill, hipStream_t stream) {
-  return step_call(dtype, u, data, w, out, dom, coeff, dt_dz, nullptr, opts, stream, nullptr, wrapped, fill);
+              const LoopPlan& p, bool first, hipStream_t stream) {
+  return step_call(dtype, u, data, w, out, dom, coeff, dt_dz, nullptr, opts, stream, nullptr, &p, p.wraps && !first);
 }
 
 }  // namespace gt4mi

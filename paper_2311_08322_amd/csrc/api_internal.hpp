@@ -22,12 +22,6 @@ namespace gt4mi {
 int fail(int code, const char* fmt, ...);
 int ok();
 int hip_status(hipError_t e, const char* what);
-// A step inside a periodic loop.  wrapped: u is a state whose halo nobody filled;
-// fill: out's halo is filled.  loop_wraps: whether the steps can run so.
-bool loop_wraps(stencil_dtype dtype, const int64_t* dom, const stencil_options* opts);
-int loop_step(stencil_dtype dtype, const stencil_field* u, const stencil_field* data, const stencil_field* w,
-              stencil_field* out, const int64_t* dom, double coeff, double dt_dz, const stencil_options* opts,
-              bool wrapped, bool fill, hipStream_t stream);
 int check_device();
 int check_dtype(stencil_dtype dt);
 int check_domain(const int64_t* dom);
@@ -64,6 +58,17 @@ struct DevCoeff {
   bool f64;
   void* copy;
 };
+// What all steps of a captured loop share, resolved once: another thread may change
+// the tuning table meanwhile.  wraps: a periodic loop whose steps after the first
+// read u's halo from its interior and leave out's halo unfilled.
+struct LoopPlan {
+  ResolvedOpts opts;
+  bool wraps;
+};
+int plan_loop(stencil_dtype dtype, const int64_t* dom, const stencil_options* opts, LoopPlan* p);
+int loop_step(stencil_dtype dtype, const stencil_field* u, const stencil_field* data, const stencil_field* w,
+              stencil_field* out, const int64_t* dom, double coeff, double dt_dz, const stencil_options* opts,
+              const LoopPlan& p, bool first, hipStream_t stream);
 // Tile shapes of the fused forward kernels: 256 columns (64x4, 32x8,
 // 16x16: 512-lane workgroups in the two-ended step) or, in the two-ended
 // step only, 128 columns (64x2, 32x4, 16x8: 256-lane workgroups).

@@ -41,18 +41,18 @@ int stencil_graph_capture_steps(stencil_dtype dtype, int nsteps, stencil_field* 
   // validate one step eagerly-in-metadata only: stencil_step validates every call below
   hipError_t e = hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return hip_status(e, "hipStreamBeginCapture");
-  int rc = STENCIL_OK;
+  LoopPlan plan;
+  int rc = plan_loop(dtype, domain, opts, &plan);
   // Periodic boundaries: the first step reads u_a's own halo; later ones take their
   // halo points from the state's interior, so that only the states that the loop
   // leaves behind need theirs filled, both by one launch at its end (a launch after
   // each step cost 5 us: FP64 256x256x80, 8 steps 296 us).
-  const bool wraps = loop_wraps(dtype, domain, opts);
   for (int s = 0; s < nsteps && rc == STENCIL_OK; ++s) {
     const stencil_field* src = (s % 2 == 0) ? u_a : u_b;
     stencil_field* dst = (s % 2 == 0) ? u_b : u_a;
-    rc = loop_step(dtype, src, data, w, dst, domain, coeff, dt_dz, opts, wraps && s > 0, !wraps, stream);
+    rc = loop_step(dtype, src, data, w, dst, domain, coeff, dt_dz, opts, plan, s == 0, stream);
   }
-  if (wraps && rc == STENCIL_OK)
+  if (rc == STENCIL_OK && plan.wraps)
     rc = nsteps == 1 ? stencil_halo_update(dtype, u_b, domain, STENCIL_BOUNDARY_PERIODIC, stream)
          : dtype == STENCIL_F64 ? fill_both<double>(u_a, u_b, domain, stream)
                                 : fill_both<float>(u_a, u_b, domain, stream);
