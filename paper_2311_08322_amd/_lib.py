@@ -179,7 +179,8 @@ def check(rc: int) -> None:
 
 
 def domain3(domain) -> I64x3:
+    d = tuple(domain)  # may be readable only once
     try:
-        return I64x3(*domain)
+        return I64x3(*d)
     except TypeError:  # numbers that are not ints
-        return I64x3(*[int(x) for x in domain])
+        return I64x3(*[int(x) for x in d])
