@@ -317,8 +317,12 @@ int stencil_step_param_adjoint(stencil_dtype dtype, const stencil_field* u, cons
  *   coeff_copy; nk within the two-ended step's limit), or coeff.
  * backward: u_bar and data_bar as stencil_step_adjoint (stencil_hdiff_adjoint),
  *   and those of w_bar (needs x, the forward's output), kappa_bar and coeff_bar
- *   (one value in dtype; needs stencil_param_workspace_bytes at ws; both need u)
- *   that are not NULL.  coeff_copy: what the forward left there, or NULL. */
+ *   (one value in dtype; needs stencil_param_workspace_bytes at ws, 8-byte
+ *   aligned; both need u) that are not NULL.  coeff_copy: what the forward left
+ *   there, or NULL (with kappa: STENCIL_E_ARG).
+ * Outputs (u_bar, data_bar, w_bar, kappa_bar, coeff_bar and ws; out, mask and
+ * coeff_copy) may not overlap inputs or each other (STENCIL_E_ALIAS); the scalars
+ * in device memory are aligned to their type (STENCIL_E_DTYPE). */
 int stencil_train_forward(stencil_dtype dtype, const void* u, const void* data, const void* w, void* out,
                           void* mask, const void* kappa, double coeff, const void* coeff_dev,
                           stencil_dtype coeff_dtype, void* coeff_copy, int64_t ni, int64_t nj, int64_t nk,

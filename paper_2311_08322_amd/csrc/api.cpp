@@ -804,6 +804,36 @@ static stencil_field dense(const void* p, const int64_t* dom, int h, int extra) 
   return stencil_field{const_cast<void*>(p), {x, y, dom[2] + extra}, {1, x, x * y}, {h, h, 0}};
 }
 
+// The buffers of one call that are there, for the check that no output overlaps
+// an input or another output.
+namespace {
+struct Buffers {
+  struct { const char* name; Span s; } v[8];
+  int n = 0;
+  void add(const char* name, const void* p, size_t bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+    if (p && bytes) v[n].name = name, v[n++].s = Span{a, a + bytes};
+  }
+  void add(const char* name, const stencil_field& f, size_t es) {
+    if (f.data) v[n].name = name, v[n++].s = span_of(&f, es);
+  }
+};
+
+int check_outputs(const Buffers& out, const Buffers& in) {
+  for (int o = 0; o < out.n; ++o) {
+    for (int i = 0; i < in.n; ++i) TRY(check_no_alias(out.v[o].name, out.v[o].s, in.v[i].name, in.v[i].s));
+    for (int q = o + 1; q < out.n; ++q) TRY(check_no_alias(out.v[o].name, out.v[o].s, out.v[q].name, out.v[q].s));
+  }
+  return STENCIL_OK;
+}
+
+int check_aligned(const char* name, const void* p, size_t bytes) {
+  if (reinterpret_cast<uintptr_t>(p) % bytes)
+    return fail(STENCIL_E_DTYPE, "%s is not aligned to %zu bytes", name, bytes);
+  return STENCIL_OK;
+}
+}  // namespace
+
 int stencil_train_forward(stencil_dtype dtype, const void* u, const void* data, const void* w, void* out,
                           void* mask, const void* kappa, double coeff, const void* coeff_dev,
                           stencil_dtype coeff_dtype, void* coeff_copy, int64_t ni, int64_t nj, int64_t nk,
@@ -820,7 +850,28 @@ int stencil_train_forward(stencil_dtype dtype, const void* u, const void* data, 
       return fail(STENCIL_E_UNSUPPORTED, "a coefficient in device memory takes nk <= %d", split_step_limit((int)esize(dtype)));
   }
   const stencil_field fu = dense(u, dom, 2, 0), fk = dense(kappa, dom, 0, 0);
+  const stencil_field fd = dense(data, dom, 0, 0), fw = dense(w, dom, 0, 1);
   stencil_field fo = dense(out, dom, 0, 0);
+  if (coeff_dev) {
+    const size_t es = esize(dtype), cs = esize(coeff_dtype);
+    TRY(check_aligned("coeff_dev", coeff_dev, cs));
+    TRY(check_aligned("coeff_copy", coeff_copy, es));
+    TRY(check_field("u", &fu, dom, ROLE_HALO, es));
+    TRY(check_field("out", &fo, dom, ROLE_INTERIOR, es));
+    if (w) {
+      TRY(check_field("data", &fd, dom, ROLE_INTERIOR, es));
+      TRY(check_field("w", &fw, dom, ROLE_STAGGERED, es));
+    }
+    Buffers in, outs;
+    in.add("coeff_dev", coeff_dev, cs);
+    in.add("u", fu, es);
+    if (w) in.add("data", fd, es);
+    if (w) in.add("w", fw, es);
+    outs.add("coeff_copy", coeff_copy, es);
+    outs.add("out", fo, es);
+    outs.add("mask", mask, stencil_mask_bytes(dom));
+    if (!domain_empty(dom)) TRY(check_outputs(outs, in));
+  }
   stencil_options o;
   memset(&o, 0, sizeof o);
   o.hdiff_form = form;
@@ -828,7 +879,6 @@ int stencil_train_forward(stencil_dtype dtype, const void* u, const void* data, 
   const DevCoeff dev{coeff_dev, coeff_dtype == STENCIL_F64, coeff_copy};
   const DevCoeff* d = coeff_dev ? &dev : nullptr;
   if (!w) return hdiff_call(dtype, &fu, &fo, dom, coeff, mask, &o, stream, d);
-  const stencil_field fd = dense(data, dom, 0, 0), fw = dense(w, dom, 0, 1);
   return step_call(dtype, &fu, &fd, &fw, &fo, dom, coeff, dt_dz, mask, &o, stream, d);
 }
 
@@ -843,11 +893,42 @@ int stencil_train_backward(stencil_dtype dtype, const void* x_bar, const void* m
   if ((kappa_bar || coeff_bar) && !u) return fail(STENCIL_E_NULL, "u is NULL");
   if (w_bar && !(w && x)) return fail(STENCIL_E_NULL, "w_bar needs w and x");
   if (coeff_bar && kappa) return fail(STENCIL_E_ARG, "a coefficient field has no scalar coeff_bar");
-  if (coeff_bar && !domain_empty(dom) && ws_bytes < stencil_param_workspace_bytes(dtype, dom))
-    return fail(STENCIL_E_WORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", ws_bytes,
-                stencil_param_workspace_bytes(dtype, dom));
+  if (coeff_copy && kappa) return fail(STENCIL_E_ARG, "both a coefficient field and a scalar coefficient in device memory");
+  const size_t es = esize(dtype), need = coeff_bar ? stencil_param_workspace_bytes(dtype, dom) : 0;
+  if (need) {
+    if (!ws) return fail(STENCIL_E_WORKSPACE, "coeff_bar needs %zu bytes of workspace (ws is NULL)", need);
+    if (ws_bytes < need)
+      return fail(STENCIL_E_WORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", ws_bytes, need);
+    if (reinterpret_cast<uintptr_t>(ws) % 8) return fail(STENCIL_E_WORKSPACE, "workspace is not 8-byte aligned");
+  }
+  TRY(check_aligned("coeff_copy", coeff_copy, es));
+  TRY(check_aligned("coeff_bar", coeff_bar, es));
   const stencil_field fx = dense(x_bar, dom, 0, 0), fk = dense(kappa, dom, 0, 0), fw = dense(w, dom, 0, 1);
+  const stencil_field fu = dense(u, dom, 2, 0), fo = dense(x, dom, 0, 0);
   stencil_field fb = dense(u_bar, dom, 2, 0), fd = dense(data_bar, dom, 0, 0);
+  stencil_field kb = dense(kappa_bar, dom, 0, 0), wb = dense(w_bar, dom, 0, 1);
+  {
+    Buffers in, out;
+    auto field = [&](Buffers& set, const char* name, const stencil_field& f, Role role) -> int {
+      TRY(check_field(name, &f, dom, role, es));
+      set.add(name, f, es);
+      return STENCIL_OK;
+    };
+    TRY(field(in, "x_bar", fx, ROLE_INTERIOR));
+    TRY(field(out, "u_bar", fb, ROLE_HALO));
+    if (w) TRY(field(in, "w", fw, ROLE_STAGGERED));
+    if (w) TRY(field(out, "data_bar", fd, ROLE_INTERIOR));
+    if (kappa) TRY(field(in, "kappa", fk, ROLE_INTERIOR));
+    if (kappa_bar || coeff_bar) TRY(field(in, "u", fu, ROLE_HALO));
+    if (w_bar) TRY(field(in, "x", fo, ROLE_INTERIOR));
+    if (w_bar) TRY(field(out, "w_bar", wb, ROLE_STAGGERED));
+    if (kappa_bar) TRY(field(out, "kappa_bar", kb, ROLE_INTERIOR));
+    in.add("mask", mask, stencil_mask_bytes(dom));
+    in.add("coeff_copy", coeff_copy, es);
+    out.add("coeff_bar", coeff_bar, es);
+    out.add("the workspace", ws, need);
+    if (!domain_empty(dom)) TRY(check_outputs(out, in));
+  }
   stencil_options o;
   memset(&o, 0, sizeof o);
   o.hdiff_form = form;
@@ -859,18 +940,14 @@ int stencil_train_backward(stencil_dtype dtype, const void* x_bar, const void* m
   if (!kappa_bar && !coeff_bar && !w_bar) return ok();
   auto go = [&](auto tag) -> int {
     using T = decltype(tag);
-    const stencil_field fu = dense(u, dom, 2, 0), lam = dense(w ? data_bar : x_bar, dom, 0, 0);
-    stencil_field kb = dense(kappa_bar, dom, 0, 0), wb = dense(w_bar, dom, 0, 1);
+    const stencil_field lam = w ? fd : fx;
     StepArgs<T> A = step_args<T>(u ? &fu : nullptr, &lam, nullptr, kappa_bar ? &kb : nullptr, dom, 0.0, dt_dz, nullptr);
     A.form = form;
     if (kappa_bar && !domain_empty(dom)) TRY(hip_status(launch_coeff_field_grad<T>(A, stream), "coefficient field gradient"));
     if (!coeff_bar && !w_bar) return ok();
     WGradArgs<T> W;
-    if (w_bar) {
-      const stencil_field xo = dense(x, dom, 0, 0);
-      W = w_grad_args<T>(&fw, &xo, &lam, &wb, dom, dt_dz);
-    }
-    return hip_status(launch_param_grads<T>(A, w_bar ? &W : nullptr, static_cast<double*>(ws), (int64_t)(ws_bytes / 8),
+    if (w_bar) W = w_grad_args<T>(&fw, &fo, &lam, &wb, dom, dt_dz);
+    return hip_status(launch_param_grads<T>(A, w_bar ? &W : nullptr, static_cast<double*>(ws), (int64_t)(need / 8),
                                             coeff_bar, dtype == STENCIL_F32, stream),
                       "step parameter gradients");
   };
