@@ -1,6 +1,8 @@
 // k_hdiff.hip -- launcher of the horizontal diffusion alone: the row walk
 // (k_hdiff_strip.hpp), or the tile kernel (k_step.hpp) where the walk's 32-bit
-// mask window or its grid does not reach.
+// mask window does not reach and, for the generalised diffusion, beyond kMaxGridY
+// levels (the stated form has walked those from the first and runs on every nk:
+// tested with 65543).
 #include "k_hdiff_strip.hpp"
 #include "k_step.hpp"
 
@@ -17,8 +19,7 @@ hipError_t launch_hdiff_fused(StepArgs<T> A, int tile_i, hipStream_t s) {
     if (!var) return launch_hdiff_strip<T, kHPlain>(A, s);
     if (A.nk <= kMaxGridY) return launch_hdiff_strip<T, kHVar>(A, s);
   }
-  // masks of 4 GiB or more (and very many levels): a tile marched
-  // over a block of levels; enough workgroups to fill the chip
+  // a tile marched over a block of levels; enough workgroups to fill the chip
   const int tj = kWG / tile_i;
   A.tiles_i = (A.ni + tile_i - 1) / tile_i;
   A.ntiles = A.tiles_i * ((A.nj + tj - 1) / tj);

@@ -427,7 +427,7 @@ hipError_t launch_hdiff_strip(StepArgs<T> A, hipStream_t s) {
   return hipGetLastError();
 }
 
-// grid.y's limit: the walk has one grid row per level
+// grid.y's documented limit: the walk has one grid row per level
 constexpr int kMaxGridY = 65535;
 
 }  // namespace gt4mi
