@@ -144,7 +144,14 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
   // fields 1009, 1010, 1016.
   // FP32 saving a mask has stores in every step, which pin the loads by themselves:
   // 512x512x80 87.7 us, with both 89.
-  constexpr bool PIN = sizeof(T) == 8 || !MASK, DRAIN = sizeof(T) == 4 && !MASK;
+  // Where it costs, it is left out, over 50 sizes each: short columns, which gain
+  // little and end soon (FP32 up to 48 levels 2 to 4% slower with both, up to 4% in
+  // the worst size of 32 levels; FP64 up to 32 levels 1%, at worst 5%); and the
+  // generalised step in FP64, whose registers it takes over an edge (132 for 124,
+  // three waves per SIMD for four: 512x512x20 53.4 against 46.7 us; six spills in
+  // the 48-level class), except where f is staged in the output (1% faster with it).
+  constexpr bool PIN = sizeof(T) == 8 ? (!VAR && NKH > 16) || COL == 2 : !MASK && NKH > 24;
+  constexpr bool DRAIN = sizeof(T) == 4 && PIN;
   LevelCursor cur_u{vu.base + (int64_t)k0 * vu.level_bytes, dir * vu.level_bytes, vu.window};
   LevelCursor cur_d{vd.base + (int64_t)k0 * vd.level_bytes, dir * vd.level_bytes, vd.window};
   LevelCursor cur_w{vw.base + (int64_t)(half ? k0 : 1) * vw.level_bytes, dir * vw.level_bytes, vw.window};
