@@ -146,11 +146,12 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
   // 512x512x80 87.7 us, with both 89.
   // Where it costs, it is left out, over 50 sizes each: short columns, which gain
   // little and end soon (FP32 up to 48 levels 2 to 4% slower with both, up to 4% in
-  // the worst size of 32 levels; FP64 up to 32 levels 1%, at worst 5%); and the
-  // generalised step in FP64, whose registers it takes over an edge (132 for 124,
-  // three waves per SIMD for four: 512x512x20 53.4 against 46.7 us; six spills in
-  // the 48-level class), except where f is staged in the output (1% faster with it).
-  constexpr bool PIN = sizeof(T) == 8 ? (!VAR && NKH > 16) || COL == 2 : !MASK && NKH > 24;
+  // the worst size of 32 levels; FP64 up to 32 levels 1%, at worst 5%), and where the
+  // registers it takes cross an edge: the generalised step in FP64 up to 32 levels
+  // (132 for 124, three waves per SIMD for four: 512x512x20 53.4 against 46.7 us) and
+  // in the 48-level class (six spills).  Its classes between gain with 32x4 tiles
+  // (damping 501x403x60 102.6 against 108.2 us) what they lose with 64x4 (0.6%).
+  constexpr bool PIN = sizeof(T) == 8 ? NKH > 16 && !(VAR && NKH == 48) : !MASK && NKH > 24;
   constexpr bool DRAIN = sizeof(T) == 4 && PIN;
   LevelCursor cur_u{vu.base + (int64_t)k0 * vu.level_bytes, dir * vu.level_bytes, vu.window};
   LevelCursor cur_d{vd.base + (int64_t)k0 * vd.level_bytes, dir * vd.level_bytes, vd.window};
@@ -286,7 +287,8 @@ __global__ void __launch_bounds__(2 * TI * TJ) k_step_split(StepArgs<T> A) {
 // waves per SIMD).  Longer FP64 columns (up to 144) run in 128-column tiles
 // with e and f in VGPRs at one wave per SIMD (launch_split_long); where that
 // form is not instantiated (the generalised diffusion) they keep e and
-// stage f in the output, as the batched kernel does beyond 80 levels.
+// stage f in the output, as the batched kernel does beyond 80 levels.  What the
+// classes' registers leave of a CU is in split_tiles_per_cu (launch.hpp).
 #define GT4MI_NKH_CLASSES(X) X(16) X(24) X(40) X(48) X(56) X(80)
 constexpr int kSplitStagedNkhF64 = 72;
 // Levels loaded ahead in the long FP64 form.  It runs one wave per SIMD, so
