@@ -147,44 +147,61 @@ static bool narrow_tile_runs(const ResolvedOpts& r, int op, stencil_dtype dt, co
          dom[2] <= split_step_limit((int)esize(dt));
 }
 
-// The two-ended step's tile where nothing chose one.  While the step's four fields
-// fit the last-level cache, a level costs its instructions, not its bytes: tiles of
-// 128 columns spread them over twice the workgroups (one wave per SIMD each where
-// the chip is not full) and, in FP64, 16-wide rows load the box in two passes
-// instead of three.  64x4 against 16x8 (FP64) and 32x4 (FP32), us: FP64 39x89x29
-// 11.9, 8.3, 128x128x80 28.5, 20.0, 256x200x80 30.7, 29.8; FP32 39x89x29 9.2, 8.0,
-// 256x200x80 22.4, 20.6, 256x256x80 22.9, 21.1.  Past half the cache (other buffers
-// of the program share it) 64x4 loses where it leaves places for workgroups idle, a
-// tenth of them where a CU holds one workgroup: 64x4 against 32x4, FP64 501x403x60
-// 107, 98.6 (with mask 113, 104), 400x300x60 66.9, 48.9, 384x384x64 79.5, 73.0,
-// 400x256x100 104, 99.4; FP32 512x300x90 68.8, 52.4, 400x256x100 52.2, 49.3.  Where
-// a CU holds two, the other keeps it busy until a quarter is idle: FP32 400x300x60
-// 35.3, 25.6, FP64 512x300x32 36.2, 32.4, but FP32 512x400x80, 22% idle, 58.9, 60.7;
-// with three it does not matter (FP32 500x500x40, 35% idle, 35.5, 37.5).  With whole
-// rounds 32x8 is faster in FP64 while the fields fit the cache (256x256x80 32.4 to
-// 34.2, 30.6; the generalised step not: 512x512x28 69.5, 71.2) and 64x4
-// streams best elsewhere (against 32x4: FP64 512x256x80 74.6, 78.3, 512x512x80 151.4,
-// 152.5; FP32 512x256x80 33.4, 38.2, 512x512x80 77.9, 89.1).  FP64 columns of the
-// generalised step that spill with 128 columns keep 64x4: 81 to 96 levels
-// (512x300x90 155, 173), and longer ones on large domains (400x256x100 144, 158; but
-// 60x60x110 71.3, 55.5 and 200x200x100 78.5, 76.7 with 16x8).
+// The two-ended step's tile where nothing chose one, from 230 sizes of 8 to 144
+// levels in four forms (plain, mask, coefficient field, damping), each with fields
+// that stay in the last-level cache from call to call and with three sets in turn.
+// While the step's four fields fit half that cache, a level costs its instructions,
+// not its bytes: tiles of 128 columns spread them over twice the workgroups (one wave
+// per SIMD each where the chip is not full) and, in FP64, 16-wide rows load the box in
+// two passes instead of three.  64x4 against 16x8 (FP64) and 32x4 (FP32), us: FP64
+// 39x89x29 11.9, 8.3, 128x128x80 28.5, 20.0; FP32 39x89x29 9.2, 8.0, 256x200x80 22.4,
+// 20.6, 256x256x80 22.9, 21.1.  Not where 64x4 fills the chip by itself: FP32 of more
+// than a workgroup per CU and a quarter of the cache (three sets 771x141x61 28.2,
+// 32.6, 491x238x56 27.9, 32.9, 512x512x20 20.1, 22.2; one set the same or 5% less),
+// FP64 of more than 256 16x8 tiles in one round of 64x4 and 0.4 of the cache, which
+// take 32x8 (three sets, 64x4, 16x8, 32x8: 256x200x80 33.3, 39.3, 31.8, 626x90x73
+// 33.3, 39.9, 32.6; one set 0.90 to 0.97 and 0.95 of 64x4), or 64x4 in the long
+// class of the generalised step (763x42x113 65.6, 88.5; 626x59x107 70.7, 88.0).
+// Past half the cache (other buffers of the program share it) 64x4 loses where it
+// leaves places for workgroups idle, a tenth of them where a CU holds one workgroup:
+// 64x4 against 32x4, FP64 501x403x60 107, 98.6 (with mask 113, 104), 400x300x60 66.9,
+// 48.9, 384x384x64 79.5, 73.0, 400x256x100 104, 99.4; FP32 512x300x90 68.8, 52.4.  In
+// FP32 with just two rounds it depends on the cache: 400x256x100 one set 48.5, 41.7,
+// three 52.3, 57.4.  Where a CU holds two, the other keeps it busy until a quarter is
+// idle: FP32 400x300x60 35.3, 25.6, FP64 512x300x32 36.2, 32.4, but FP32 512x400x80,
+// 22% idle, 58.9, 60.7.  With whole rounds 32x8 is faster in FP64 while the fields fit
+// the cache (256x256x80 32.4 to 34.2, 30.6; the generalised step not: 512x512x28
+// 69.5, 71.2) and 64x4 streams best elsewhere (against 32x4: FP64 512x256x80 74.6,
+// 78.3, 512x512x80 151.4, 152.5; FP32 512x256x80 33.4, 38.2, 512x512x80 77.9, 89.1).
+// FP64 columns of the generalised step that spill with 128 columns keep 64x4: 81 to 96
+// levels (512x300x90 155, 173), and longer ones on large domains (400x256x100 144,
+// 158; but 60x60x110 71.3, 55.5 and 200x200x100 78.5, 76.7 with 16x8).  The long FP64
+// class runs tiles of 128 columns one to a CU whatever the width: no other where 64x2
+// takes fewer rounds (763x42x113 32.5, 16x8 52.9).
 constexpr int64_t kLastLevelCache = int64_t(256) << 20;
 constexpr int kCus = 256;
 static void default_step_tile(ResolvedOpts& r, stencil_dtype dt, const int64_t* dom, bool variant) {
   const int64_t es = (int64_t)esize(dt), nk = dom[2], bytes = 4 * es * dom[0] * dom[1] * nk;
-  const bool f64 = es == 8, small = 2 * bytes <= kLastLevelCache;
+  const bool f64 = es == 8;
+  bool small = 2 * bytes <= kLastLevelCache;
   if (f64 && variant && nk > 80 && (nk <= kSplitRegNkF64 || !small)) return;
-  // workgroups of a 64x4 tile that a CU holds, by register class
-  const int64_t per_cu = f64 ? (nk <= 32 ? 2 : 1) : (nk <= 48 ? 3 : nk <= 80 ? 2 : 1), slots = kCus * per_cu;
-  const int64_t tiles = ((dom[0] + 63) / 64) * ((dom[1] + 3) / 4), places = (tiles + slots - 1) / slots * slots;
-  const bool idle = per_cu < 3 && (per_cu == 1 ? 10 : 4) * (places - tiles) >= places;
-  if (small || idle) {
-    r.tile_i = f64 && small ? 16 : 32;
-    r.tile_j = 128 / r.tile_i;
-  } else if (f64 && !variant && bytes <= kLastLevelCache) {
-    r.tile_i = 32;
-    r.tile_j = 8;
+  auto tiles = [&](int ti, int tj) { return ((dom[0] + ti - 1) / ti) * ((dom[1] + tj - 1) / tj); };
+  const int64_t n = tiles(64, 4), per_cu = split_tiles_per_cu((int)es, nk), slots = kCus * per_cu;
+  const int64_t places = (n + slots - 1) / slots * slots;
+  if (!f64) small = small && (n <= kCus || 4 * bytes <= kLastLevelCache || (per_cu == 3 && n <= slots));
+  const bool idle = per_cu < 3 && (per_cu == 1 ? 10 : 4) * (places - n) >= places;
+  int ti = 64, tj = 4;
+  if (small || idle) ti = f64 && small ? 16 : 32, tj = 128 / ti;
+  else if (f64 && !variant && bytes <= kLastLevelCache) ti = 32, tj = 8;
+  if (f64 && nk > kSplitRegNkF64 && !variant) {
+    auto rounds = [&](int w) { return (tiles(w, kSplitLongNT / w) + kCus - 1) / kCus; };
+    if (rounds(ti) > rounds(64)) ti = 64, tj = 4;
+  } else if (ti == 16 && n <= slots && tiles(16, 8) > kCus) {
+    if (nk > kSplitRegNkF64) ti = 64, tj = 4;
+    else if (n > kCus || 5 * bytes > 2 * kLastLevelCache) ti = 32, tj = 8;
   }
+  r.tile_i = ti;
+  r.tile_j = tj;
 }
 
 ResolvedOpts resolve_opts(const stencil_options* o, stencil_dtype dt, int op, const int64_t* dom) {
