@@ -179,7 +179,6 @@ static bool narrow_tile_runs(const ResolvedOpts& r, int op, stencil_dtype dt, co
 // class runs tiles of 128 columns one to a CU whatever the width: no other where 64x2
 // takes fewer rounds (763x42x113 32.5, 16x8 52.9).
 constexpr int64_t kLastLevelCache = int64_t(256) << 20;
-constexpr int kCus = 256;
 static void default_step_tile(ResolvedOpts& r, stencil_dtype dt, const int64_t* dom, bool variant) {
   const int64_t es = (int64_t)esize(dt), nk = dom[2], bytes = 4 * es * dom[0] * dom[1] * nk;
   const bool f64 = es == 8;

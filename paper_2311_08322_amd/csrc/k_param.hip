@@ -14,16 +14,28 @@
 #include <algorithm>
 
 #include "k_hdiff_strip.hpp"
+#include "k_step.hpp"
 #include "launch.hpp"
 
 namespace gt4mi {
 
+// The workgroup's sum of its lanes' sums, to *out.
+__device__ __forceinline__ void workgroup_sum(Sum2 s, Sum2* red, double* out) {
+#pragma unroll
+  for (int h = 32; h > 0; h >>= 1) s.add(__shfl_down(s.hi, h), __shfl_down(s.lo, h));
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) red[wave] = s;
+  __syncthreads();
+  if (threadIdx.x) return;
+  for (int w = 1; w < kWG / 64; ++w) s.add(red[w].hi, red[w].lo);
+  *out = s.value();
+}
+
 // Sum of lam * D(u) over the strips of one workgroup (k_hdiff_strip.hpp's walk)
 // and a run of levels, in FP64, to partial[block] (fixed order: the result does
-// not depend on scheduling).  A.data holds lam.  Bound by memory; a tile marched
-// through every level with u in LDS left small domains short of waves (with the
-// final sum, FP64: 256x256x80 45 us, here 28; 384x384x64 49 and 42; 512x512x80
-// 77 to 92 and 90; FP32 31 and 20, 39 and 26, 54 and 47).
+// not depend on scheduling).  A.data holds lam.  Bound by memory; with the final
+// sum, against the tile form below, us: FP64 256x256x80 28.8, 38.2; 384x384x64 41.6,
+// 48.1; 838x538x19 39.9, 47.2; FP32 21.1, 30.9; 26.2, 31.9; 23.8, 31.0.
 template <typename T, int LANE>
 __global__ void __launch_bounds__(kWG) k_coeff_partial(StepArgs<T> A, int levels, double* partial) {
   __shared__ Sum2 red[kStripsPerWG];
@@ -36,13 +48,53 @@ __global__ void __launch_bounds__(kWG) k_coeff_partial(StepArgs<T> A, int levels
       const Sum2 l = hdiff_strip_of<T, kHCoeffBar, LANE>(A, t, k);
       s.add(l.hi, l.lo);
     }
+  workgroup_sum(s, red, partial + blockIdx.y * gridDim.x + blockIdx.x);
+}
+
+// The same sum over a 64 x 4 tile marched through every level, u in LDS (one barrier
+// per level, the next level's loads in flight), to partial[tile].  For few levels on
+// as many tiles as the chip holds, where the walk is bound by its rows' latencies
+// (512x512x20: FP64 22.1 us against 29.1, FP32 14.4 against 20.8; 1000x500x8 19.0,
+// 22.9 and 14.0, 18.2), and where the workspace holds no more than a sum per tile
+// (57x111x66 27.6, 44.8 and 23.3, 31.7).
+template <typename T>
+__global__ void __launch_bounds__(kWG) k_coeff_tile(StepArgs<T> A, double* partial) {
+  constexpr int TI = 64, TJ = kWG / TI;
+  using TA = TileAddr<T, TI, TJ>;
+  constexpr int HI = TA::HI, NLD = TA::NLD;
+  __shared__ T su[2][NLD * kWG];
+  __shared__ Sum2 red[kWG / 64];
+  TA t;
+  t.init(blockIdx.x, A.tiles_i, A.ni, A.nj, A.u_sj);
+  const LevelView vu = level_view(A.u, A.u_sj, A.u_sk, -2, -2, A.nj + 4);
+  const LevelView vl = level_view(A.data, A.d_sj, A.d_sk, 0, 0, A.nj);
+  const uint32_t loff = ((uint32_t)t.ic + (uint32_t)t.jc * (uint32_t)A.d_sj) * (uint32_t)sizeof(T);
+  const T gs = form_sign<T>(A.form);
+  LevelCursor cur_u{vu.base, vu.level_bytes, vu.window}, cur_l{vl.base, vl.level_bytes, vl.window};
+  T nu[NLD], nl;
+  auto issue = [&](int k) {  // level k, the last one again past it
+    const auto r = cur_u.rsrc();
 #pragma unroll
-  for (int h = 32; h > 0; h >>= 1) s.add(__shfl_down(s.hi, h), __shfl_down(s.lo, h));
-  if ((threadIdx.x & 63) == 0) red[wave] = s;
-  __syncthreads();
-  if (threadIdx.x) return;
-  for (int w = 1; w < kStripsPerWG; ++w) s.add(red[w].hi, red[w].lo);
-  partial[blockIdx.y * gridDim.x + blockIdx.x] = s.value();
+    for (int q = 0; q < NLD; ++q) nu[q] = buf_ld(r, t.hoff[q], T());
+    nl = buf_ld(cur_l.rsrc(), loff, T());
+    const bool go = k + 1 < A.nk;
+    cur_u.advance(go);
+    cur_l.advance(go);
+  };
+  issue(0);
+  Sum2 s{0.0, 0.0};
+  for (int k = 0; k < A.nk; ++k) {
+    T* U = su[k & 1];
+#pragma unroll
+    for (int q = 0; q < NLD; ++q) U[threadIdx.x + q * kWG] = nu[q];
+    const T lam = nl;
+    issue(k + 1);
+    __syncthreads();
+    bool kxr, kxl, kyr, kyl;
+    const T div = limited_divergence(load_diamond<T, HI>(U + (t.tj + 2) * HI + (t.ti + 2)), gs, kxr, kxl, kyr, kyl);
+    s.add_product(t.active ? lam : T(0), t.active ? gs * div : T(0));
+  }
+  workgroup_sum(s, red, partial + blockIdx.x);
 }
 
 // coeff_bar = -(sum of the partials), summed in a fixed order by one workgroup.
@@ -127,6 +179,24 @@ int64_t coeff_partial_most(bool f64, int64_t ni, int64_t nj, int64_t nk) {
   return (strips + kStripsPerWG - 1) / kStripsPerWG * std::min<int64_t>(nk, kMaxGridY);
 }
 
+// Whether the sum takes the tile form: estimated times, us, fitted to 60 sizes (of 8
+// to 140 levels) in each type.  The tile form: a level costs what the tiles on a CU
+// take, from one to four of them, and again for every 1024 tiles.  The walk: rounds
+// of 256 workgroups and, where the workspace leaves `levels` of them to a workgroup,
+// a chain of strips.  The faster form or one within 10% of it nearly everywhere
+// (512x512x80 takes the walk: FP64 86 against 81, FP32 49 against 53).
+static bool coeff_by_tiles(bool f64, int64_t tiles, int64_t wgs, int64_t nk, int64_t levels) {
+  static const double level_us[2][5] = {{0, 0.29, 0.34, 0.41, 0.55}, {0, 0.33, 0.52, 0.66, 1.0}};
+  const double* us = level_us[f64];
+  const double tile = 6.0 + nk * (us[4] * (tiles / (4 * kCus)) + us[(tiles % (4 * kCus) + kCus - 1) / kCus]);
+  double walk = 9.0 + 3.0 * ((wgs * nk + kCus - 1) / kCus);
+  if (levels > 1) {
+    const double chain = 8.0 + (f64 ? 4.1 : 4.6) * levels;
+    walk = std::max(walk, chain) + 0.1 * std::min(walk, chain);
+  }
+  return std::max(tile, 12.0) < walk;
+}
+
 template <typename T>
 hipError_t launch_param_grads(const StepArgs<T>& Ain, const WGradArgs<T>* W, double* partial, int64_t slots,
                               void* coeff_bar, bool f32, hipStream_t s) {
@@ -141,11 +211,18 @@ hipError_t launch_param_grads(const StepArgs<T>& Ain, const WGradArgs<T>* W, dou
       const int64_t wgs = (A.ntiles + kStripsPerWG - 1) / kStripsPerWG;
       const int runs = (int)std::min<int64_t>({A.nk, slots / wgs, kMaxGridY});
       const int levels = (A.nk + runs - 1) / runs;
-      const dim3 grid((uint32_t)wgs, (A.nk + levels - 1) / levels);
-      n = (int)(grid.x * grid.y);
-      hdiff_strip_lanes(A, [&](auto lane) {
-        hipLaunchKernelGGL((k_coeff_partial<T, decltype(lane)::value>), grid, dim3(kWG), 0, s, A, levels, partial);
-      });
+      const int64_t tiles = coeff_partial_least(A.ni, A.nj);
+      if (tiles <= UINT32_MAX / kWG && coeff_by_tiles(sizeof(T) == 8, tiles, wgs, A.nk, levels)) {
+        A.tiles_i = (A.ni + 63) / 64;
+        n = (int)tiles;
+        hipLaunchKernelGGL(k_coeff_tile<T>, dim3(n), dim3(kWG), 0, s, A, partial);
+      } else {
+        const dim3 grid((uint32_t)wgs, (A.nk + levels - 1) / levels);
+        n = (int)(grid.x * grid.y);
+        hdiff_strip_lanes(A, [&](auto lane) {
+          hipLaunchKernelGGL((k_coeff_partial<T, decltype(lane)::value>), grid, dim3(kWG), 0, s, A, levels, partial);
+        });
+      }
     }
     hipLaunchKernelGGL(k_coeff_final, dim3(1), dim3(kFinalWG), 0, s, partial, n, coeff_bar, f32);
   }

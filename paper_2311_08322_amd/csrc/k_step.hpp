@@ -127,14 +127,10 @@ __device__ __forceinline__ T hdiff_of(const Diamond<T>& d, T coeff, bool& kxr, b
   return d.u00 - coeff * ((Fxr - Fxl) + (Fyr - Fyl));
 }
 
-// The generalised diffusion: a per-point coefficient kap, and the form's
-// sign gs (form_sign) on the limiter's gradient and on the coefficient.
-// gs = -1 gives the damping form exactly: its fluxes are the negatives of
-// the stated ones, kept where f * (-g) <= 0, and u - kap * (-div) =
-// u - (-kap) * div.
+// The divergence of the limited fluxes, the limiter's gradient taken times gs.
 template <typename T>
-__device__ __forceinline__ T hdiff_var_of(const Diamond<T>& d, T kap, T gs, bool& kxr, bool& kxl, bool& kyr,
-                                          bool& kyl) {
+__device__ __forceinline__ T limited_divergence(const Diamond<T>& d, T gs, bool& kxr, bool& kxl, bool& kyr,
+                                                bool& kyl) {
   const T L00 = T(4) * d.u00 - ((d.um1 + d.up1) + (d.vm1 + d.vp1));
   const T Lp0 = T(4) * d.up1 - ((d.u00 + d.up2) + (d.mp + d.pp));
   const T Lm0 = T(4) * d.um1 - ((d.um2 + d.u00) + (d.mm + d.pm));
@@ -147,7 +143,18 @@ __device__ __forceinline__ T hdiff_var_of(const Diamond<T>& d, T kap, T gs, bool
   kyl = flux_kept(fyl, gs * (d.u00 - d.vm1));
   const T Fxr = kxr ? fxr : T(0), Fxl = kxl ? fxl : T(0);
   const T Fyr = kyr ? fyr : T(0), Fyl = kyl ? fyl : T(0);
-  return d.u00 - (gs * kap) * ((Fxr - Fxl) + (Fyr - Fyl));
+  return (Fxr - Fxl) + (Fyr - Fyl);
+}
+
+// The generalised diffusion: a per-point coefficient kap, and the form's
+// sign gs (form_sign) on the limiter's gradient and on the coefficient.
+// gs = -1 gives the damping form exactly: its fluxes are the negatives of
+// the stated ones, kept where f * (-g) <= 0, and u - kap * (-div) =
+// u - (-kap) * div.
+template <typename T>
+__device__ __forceinline__ T hdiff_var_of(const Diamond<T>& d, T kap, T gs, bool& kxr, bool& kxl, bool& kyr,
+                                          bool& kyl) {
+  return d.u00 - (gs * kap) * limited_divergence(d, gs, kxr, kxl, kyr, kyl);
 }
 
 template <typename T, int HI>

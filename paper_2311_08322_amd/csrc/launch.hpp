@@ -38,6 +38,7 @@ constexpr int column_split_limit(int elem_bytes) { return elem_bytes == 8 ? 144 
 #endif
 // two-ended fused step (k_split.hpp): nk <= 144 (FP64) / 160 (FP32)
 constexpr int split_step_limit(int elem_bytes) { return elem_bytes == 8 ? 144 : 160; }
+constexpr int kCus = 256;  // of the chip
 // Workgroups of its 256-column tiles that a CU holds: each has two waves per SIMD, of
 // the 4, 3, 2, 2, 2 (FP64: up to 32, 48, 80, 96, 144 levels) and 7, 5, 4, 3, 2 (FP32:
 // 32, 48, 80, 112, 160) that the registers of the class in k_split.hpp leave.
