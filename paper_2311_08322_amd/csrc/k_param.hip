@@ -115,19 +115,13 @@ __global__ void __launch_bounds__(kFinalWG) k_coeff_final(const double* partial,
   else *static_cast<double*>(coeff_bar) = v;
 }
 
-// w_bar of a few staggered levels of a 64 x 4 tile's columns, a lane per column,
-// every load in flight before the first use; the level below is read again by the
-// run below.  Bound by memory (FP64 512x512x80 114 us: 5.9 TB/s of the four
-// streams).  One lane marching its column a level ahead kept too little in flight:
-// FP64 512x512x80 124 us, 256x256x80 53 (31 here), 301x203x137 91 (51); FP32 70
-// (62), 44 (16.6), 76 (28).  Levels per run 2, 4, 8, 16: FP64 512x512x80 114, 123,
-// 131, 132 us, FP32 60.5, 62, 67, 72, but 256x256x80 17.2, 16.6, 17.7, 18.0.
-// Runs of one tile side by side on an XCD were slower (130 us).
-template <typename T>
-constexpr int w_grad_levels() {
-  return sizeof(T) == 8 ? 2 : 4;
-}
-template <typename T>
+// w_bar of L staggered levels of a 64 x 4 tile's columns, a lane per column, every
+// load in flight before the first use; the level below is read again by the run
+// below.  Bound by memory (FP64 512x512x80 114 us: 5.9 TB/s of the four streams).
+// One lane marching its column a level ahead kept too little in flight: FP64
+// 512x512x80 124 us, 256x256x80 53 (31 here), 301x203x137 91 (51); FP32 70 (60), 44
+// (14), 76 (28).  Runs of one tile side by side on an XCD were slower (130 us).
+template <typename T, int L>
 __global__ void __launch_bounds__(kWG) k_w_grad(WGradArgs<T> A) {
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int bi = tile % A.tiles_i, bj = tile / A.tiles_i;
@@ -135,7 +129,6 @@ __global__ void __launch_bounds__(kWG) k_w_grad(WGradArgs<T> A) {
   const bool active = i < A.ni && j < A.nj;
   const int ic = min(i, A.ni - 1), jc = min(j, A.nj - 1);
   constexpr uint32_t S = sizeof(T);
-  constexpr int L = w_grad_levels<T>();
   const LevelView vw = level_view(A.w, A.w_sj, A.w_sk, 0, 0, A.nj);
   const LevelView vx = level_view(A.x, A.x_sj, A.x_sk, 0, 0, A.nj);
   const LevelView vl = level_view(A.lam, A.l_sj, A.l_sk, 0, 0, A.nj);
@@ -230,8 +223,22 @@ hipError_t launch_param_grads(const StepArgs<T>& Ain, const WGradArgs<T>* W, dou
     WGradArgs<T> B = *W;
     B.tiles_i = (B.ni + 63) / 64;
     const int nt = B.tiles_i * ((B.nj + 3) / 4);
-    const int runs = B.nk / w_grad_levels<T>() + 1;  // of the nk + 1 staggered levels
-    hipLaunchKernelGGL(k_w_grad<T>, dim3(nt, std::min(runs, kMaxGridY)), dim3(kWG), 0, s, B);
+    auto go = [&](auto levels) {
+      constexpr int L = decltype(levels)::value;
+      const int runs = B.nk / L + 1;  // of the nk + 1 staggered levels
+      hipLaunchKernelGGL((k_w_grad<T, L>), dim3(nt, std::min(runs, kMaxGridY)), dim3(kWG), 0, s, B);
+    };
+    // Levels per run: each run reads one level of lam and x again, but more of them
+    // keep more streams of HBM open.  2, 3, 4, 8, us: FP64 512x512x80 118, 124, 128,
+    // 136; fields that stay in the cache 219x604x36 27.3, 25.7, 25.1, 23.9 (one lane a
+    // column 22.8), 435x231x65 37.6, 34.3, 33.5, 32.3.  A last run of one level costs a
+    // whole one (FP32 1000x500x8 14.1, 11.6, 13.2, 15.0; one lane a column 11.3): of
+    // three and four, what takes fewer accesses.
+    const bool large = sizeof(T) == 8 && 4 * (int64_t)B.ni * B.nj * B.nk * 8 > (int64_t)320 << 20;
+    auto accesses = [&](int L) { return (int64_t)(B.nk / L + 1) * (4 * L + 2); };
+    if (large) go(std::integral_constant<int, 2>{});
+    else if (accesses(3) < accesses(4)) go(std::integral_constant<int, 3>{});
+    else go(std::integral_constant<int, 4>{});
   }
   return hipGetLastError();
 }
