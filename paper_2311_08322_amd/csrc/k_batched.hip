@@ -80,6 +80,22 @@ __device__ __forceinline__ int find_entry(const int32_t* __restrict__ p, int n, 
   return at_or_below - 1;
 }
 
+// Work item of workgroup b of a launch of n: each XCD takes runs of 16 consecutive
+// items, so that tiles that share halo rows share an L2; what does not fill a round of
+// runs keeps the dispatch order.  Short runs, because a contiguous eighth of the items
+// (xcd_tile) would leave the longest columns to one XCD.  Dispatch order against runs
+// of 8, 16, 32, 64, us: FP32 10 fields 384x384x(96, 97) 706, 544, 536, 532, 534,
+// 6 fields 300x300x130 371, 309, 307, 306, 311, 16 fields of 60-140 columns a side 92,
+// 82, 82, 86, 87; FP64 6 fields 300x300x130 723 in dispatch order, 625 in runs of 16,
+// 631 in runs of 64.
+constexpr int kItemRun = 16;
+__device__ __forceinline__ int run_item(int b, int n) {
+  constexpr int round = kNumXcd * kItemRun;
+  const int first = b / round * round;
+  if (first + round > n) return b;
+  return first + b % kNumXcd * kItemRun + b % round / kNumXcd;
+}
+
 // ------------------------------------------------------------------ kernels
 // The fields of one launch may run different tile shapes (each field takes
 // the tile that wastes the fewest lanes on its ragged edges): the work item
@@ -96,7 +112,7 @@ union BatchSmem {
 template <typename T, int NT, int NKH, int PD, bool MASK>
 __global__ void __launch_bounds__(2 * NT) k_step_batched(BatchRange r, const StepArgs<T>* __restrict__ ent) {
   __shared__ BatchSmem<T, NT> sm;
-  const int w = r.first + (int)blockIdx.x;
+  const int w = r.first + run_item(blockIdx.x, gridDim.x);
   const int e = find_entry(r.prefix, r.n, w);
   const StepArgs<T> A = uniform_ld(ent + e);
   const int tile = w - uniform_ld(r.prefix + e);
