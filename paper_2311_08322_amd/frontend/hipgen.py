@@ -30,7 +30,7 @@ from . import ir
 from .analysis import Plan
 from .hippoint import Ineligible, PointKernel
 
-GEN_VERSION = 6
+GEN_VERSION = 7
 TI, TJ = 64, 4
 MIN_WGS = 2048
 

@@ -405,7 +405,7 @@ class PointKernel:
         for (kd, n, dk) in carried:
             L.append(f"  real h_{kd}_{n}_{_off(dk)} = {self._ld((kd, n, dk), kof.format(s='0'))};")
         # one level
-        L += [f"  auto level = [&](int s, int slot) {I} {{", f"    const int k = {kof.format(s='s')};"]
+        L += [f"  auto level = [&](int s, int slot, bool more) {I} {{", f"    const int k = {kof.format(s='s')};"]
         for r, (kd, n, dk) in zip(q, loaded):
             L.append(f"    const real x_{kd}_{n}_{_off(dk)} = {r}[slot];")
         # nearest the loaded level last: each reads its source before that moves on
@@ -419,7 +419,7 @@ class PointKernel:
             w, cnt, it = self._box(key)
             L += [f"    real* const B_{tag} = S_{tag} + (s & 1) * {cnt};", "#pragma unroll",
                   f"    for (int t = 0; t < {it}; ++t) B_{tag}[tid + t * {NT}] = qb_{tag}[slot][t];"]
-        L += [f"    issue(slot, s + {pd});", '    __asm__ volatile("" ::: "memory");  // the loads stay here']
+        L += [f"    if (more) issue(slot, s + {pd});", '    __asm__ volatile("" ::: "memory");  // the loads stay here']
         if self.boxes:
             L.append("    __syncthreads();")
         for key in self.boxes:
@@ -428,21 +428,28 @@ class PointKernel:
         L += ["    " + l for l in self.body]
         L.append("  };")
         if not stash:
-            L += [f"  for (int s0 = 0; s0 < n; s0 += {pd}) {{", "#pragma unroll",
-                  f"    for (int t = 0; t < {pd}; ++t)", "      if (s0 + t < n) level(s0 + t, t);", "  }"]
+            # The last pd levels load nothing ahead, and the loop before them has no
+            # branch.  With loads and a check of s < n at every level, short columns
+            # were slower than staged (FP64, us, staged, so, now: u * c + v 1000x500x8
+            # 17.6, 19.6, 16.6, 512x512x20 24.1, 27.0, 25.0, 838x538x19 40.3, 44.7,
+            # 42.7; an upwind difference 1000x500x8 18.0, 20.6, 17.5; a forward sum
+            # 384x384x64 56.8, 50.8, 33.6; FP32 33.2, 27.5, 20.6).
+            L += ["  int s0 = 0;", f"  for (; s0 + {pd} < n; s0 += {pd}) {{", "#pragma unroll",
+                  f"    for (int t = 0; t < {pd}; ++t) level(s0 + t, t, true);", "  }", "#pragma unroll",
+                  f"  for (int t = 0; t < {pd}; ++t)", "    if (s0 + t < n) level(s0 + t, t, false);"]
         else:
             c0 = seqs[0].index
             L += [f"  // the stash: levels [nl, n) in registers, [nw, nl) in LDS, [0, nw) in the workspace",
                   f"  const int nl = n > {R} ? (n - {R} + {pd - 1}) / {pd} * {pd} : 0, m = n - nl;",
                   f"  const int nw = imax(nl - {NL}, 0);",
                   f"  for (int s0 = 0; s0 < nl; s0 += {pd}) {{", "#pragma unroll",
-                  f"    for (int t = 0; t < {pd}; ++t) {{", "      const int s = s0 + t;", "      level(s, t);"]
+                  f"    for (int t = 0; t < {pd}; ++t) {{", "      const int s = s0 + t;", "      level(s, t, true);"]
             lds = [f"L_{n}[(s - nw) * {NT} + tid] = cur_{c0}_{n};" for n in stash] if NL else []
             ws = [f"tp_{n}[(int64_t)({kof.format(s='s')}) * A.t_{n}_sk] = cur_{c0}_{n};" for n in stash]
             L += ["      if (s >= nw) {"] + ["        " + l for l in lds] + ["      } else if (act) {"]
             L += ["        " + l for l in ws] + ["      }", "    }", "  }"]
             L += ["#pragma unroll", f"  for (int r = 0; r < {R}; ++r)", "    if (r < m) {",
-                  f"      level(nl + r, r % {pd});"]
+                  f"      level(nl + r, r % {pd}, true);"]
             L += [f"      R_{n}[r] = cur_{c0}_{n};" for n in stash] + ["    }"]
             # the opposite sweep
             for (kd, n, dk) in cols1:
