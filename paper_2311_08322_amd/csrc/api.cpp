@@ -158,10 +158,13 @@ static bool narrow_tile_runs(const ResolvedOpts& r, int op, stencil_dtype dt, co
 // 20.6, 256x256x80 22.9, 21.1.  Not where 64x4 fills the chip by itself: FP32 of more
 // than a workgroup per CU and a quarter of the cache (three sets 771x141x61 28.2,
 // 32.6, 491x238x56 27.9, 32.9, 512x512x20 20.1, 22.2; one set the same or 5% less),
-// FP64 of more than 256 16x8 tiles in one round of 64x4 and 0.4 of the cache, which
-// take 32x8 (three sets, 64x4, 16x8, 32x8: 256x200x80 33.3, 39.3, 31.8, 626x90x73
-// 33.3, 39.9, 32.6; one set 0.90 to 0.97 and 0.95 of 64x4), or 64x4 in the long
-// class of the generalised step (763x42x113 65.6, 88.5; 626x59x107 70.7, 88.0).
+// FP64 of one round of 64x4 where 16x8 tiles are more than 256 and the fields 0.4 of
+// the cache, or the tiles more than three to a CU, which take 32x8 (three sets, 64x4,
+// 16x8, 32x8: 256x200x80 33.3, 39.3, 31.8, 626x90x73 33.3, 39.9, 32.6; one set 0.90 to
+// 0.97 and 0.95 of 64x4; 800 tiles 512x200x32 25.9, 31.4, 26.1, one set 20.6, 22.7,
+// 20.2; but 494 tiles 200x300x30 19.8, 13.2, 18.4, one set 19.6, 13.1, 18.2, 760 tiles
+// 300x320x30 22.9, 20.8, 22.1, one set 20.1, 17.3, 19.0), or 64x4 in the long class of
+// the generalised step (763x42x113 65.6, 88.5; 626x59x107 70.7, 88.0).
 // Past half the cache (other buffers of the program share it) 64x4 loses where it
 // leaves places for workgroups idle, a tenth of them where a CU holds one workgroup:
 // 64x4 against 32x4, FP64 501x403x60 107, 98.6 (with mask 113, 104), 400x300x60 66.9,
@@ -197,7 +200,7 @@ static void default_step_tile(ResolvedOpts& r, stencil_dtype dt, const int64_t* 
     if (rounds(ti) > rounds(64)) ti = 64, tj = 4;
   } else if (ti == 16 && n <= slots && tiles(16, 8) > kCus) {
     if (nk > kSplitRegNkF64) ti = 64, tj = 4;
-    else if (n > kCus || 5 * bytes > 2 * kLastLevelCache) ti = 32, tj = 8;
+    else if (tiles(16, 8) > 3 * kCus || 5 * bytes > 2 * kLastLevelCache) ti = 32, tj = 8;
   }
   r.tile_i = ti;
   r.tile_j = tj;
