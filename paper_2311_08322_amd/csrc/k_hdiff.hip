@@ -8,24 +8,30 @@
 
 namespace gt4mi {
 
-// Whether 32 x 8 tiles are faster than the walk.
-// Narrow domains: strips (56 columns, FP32 two to a lane 120) span 1.3 times the
-// columns of tiles or more.  Walk and tiles, us, stated FP64 / damping FP64 / damping
-// FP32, by the ratio: 62x700x100 (1.75, FP32 1.88) 18.9 15.7 / 23.4 17.3 / 14.1 12.5;
-// 121x119x140 (1.31, 1.88) 9.7 8.9 / 11.4 10.2 / 9.6 8.1; 72x530x105 (1.17, 1.25)
-// 15.5 17.0 / 19.3 19.6 / 11.8 13.9; 200x200x60 (1, 1.07) 9.0 10.3 / 10.5 11.7 / 8.4
-// 9.0.
+// Whether 32 x 8 tiles are faster than the walk; us, walk and tiles, the fields in the
+// last-level cache / on cold buffers.
+// Narrow domains, by the columns that strips (56, FP32 two to a lane 120) and tiles
+// span, their ratio: FP64 1.75 64x900x140 stated 30.6 27.3 / 32.9 34.2, with the mask
+// 41.9 29.7 / 42.9 37.6, damping 38.4 29.6 / 45.0 35.6; 1.31 128x512x120 24.0 26.8 /
+// 29.4 35.4, 31.5 28.8 / 33.3 35.8, 29.0 29.2 / 36.1 34.9, but in few points (121x119x140)
+// 9.7 8.9, 12.4 10.1, 11.4 10.2; 1.17 72x530x105 15.5 17.0, 20.8 18.9, 19.3 19.6.  FP32
+// 1.88 122x600x100 stated 15.5 16.6 / 15.6 17.4, with the mask 24.6 18.7 / 24.6 18.6,
+// damping 20.9 18.3 / 20.8 18.2; 1.41 256x512x80 18.1 21.1 / 19.6 27.0, 24.7 23.1 / 26.6
+// 30.5, 20.9 23.5 / 24.8 27.8; 3.75 22x897x61 stated 9.7 6.1, damping 11.4 7.0.
 // With a mask, whose bits the walk stores byte by byte, all domains of up to 2^22
-// points.  Walk and tiles, stated / kappa field, on cold buffers: FP32 384x384x20
-// 11.2 10.1 / 12.2 11.2, 450x150x60 13.4 12.6 / 15.1 14.1, 384x384x64 21.4 24.1 /
-// 29.5 33.3; FP64 384x384x20 12.6 12.2 / 15.2 13.9, 450x150x60 17.1 16.3 / 23.7 23.5,
-// 384x384x64 36.1 41.2 / 49.6 51.9.
+// points: stated / kappa field on cold buffers, FP32 384x384x20 11.2 10.1 / 12.2 11.2,
+// 450x150x60 13.4 12.6 / 15.1 14.1, 384x384x64 21.4 24.1 / 29.5 33.3; FP64 384x384x20
+// 12.6 12.2 / 15.2 13.9, 450x150x60 17.1 16.3 / 23.7 23.5, 384x384x64 36.1 41.2 / 49.6
+// 51.9.
 template <typename T>
-static bool by_tiles(const StepArgs<T>& A) {
+static bool by_tiles(const StepArgs<T>& A, bool var) {
   constexpr int64_t w = sizeof(T) == 4 ? kHStripOut2 : kHStripOut;
   const int64_t strips = (A.ni + w - 1) / w * w, tiles = (A.ni + 31) / 32 * 32;
+  const bool few = (int64_t)A.ni * A.nj * A.nk <= 1 << 22;
   if (A.nj > 1 << 26) return false;  // a grid counts its lanes in 32 bits
-  return 10 * strips >= 13 * tiles || (A.mask && (int64_t)A.ni * A.nj * A.nk <= 1 << 22);
+  if (A.mask && few) return true;
+  const int tenths = sizeof(T) == 8 ? (few ? 13 : 15) : var || A.mask ? 15 : 30;
+  return 10 * strips >= tenths * tiles;
 }
 
 template <typename T>
@@ -33,7 +39,7 @@ hipError_t launch_hdiff_fused(StepArgs<T> A, int tile_i, hipStream_t s) {
   const bool var = A.kappa != nullptr || A.form != 0;  // the generalised diffusion
   // the walk addresses the mask through one 32-bit window
   const bool small_mask = A.mask == nullptr || A.ml.total <= (int64_t)kOffNone - 16;
-  if (small_mask && by_tiles(A)) {
+  if (small_mask && by_tiles(A, var)) {
     tile_i = 32;
   } else if (small_mask) {
     // strips of 56 columns (FP32: 120, two columns per lane), four per workgroup,

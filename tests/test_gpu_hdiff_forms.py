@@ -14,7 +14,7 @@ from .helpers import TOL, c_scalar, host, rel_err, round_f32, unpack_mask
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
 DIMS = [(1, 1, 1), (33, 9, 5), (62, 17, 3), (64, 8, 7), (73, 9, 2), (121, 11, 3), (250, 7, 5), (302, 17, 9),
-        (1009, 65, 64), (1081, 33, 118), (1082, 49, 81)]
+        (62, 700, 98), (128, 301, 110), (1009, 65, 64), (1081, 33, 118), (1082, 49, 81)]
 
 
 @pytest.mark.parametrize("aligned", [True, False], ids=["aligned", "packed"])
