@@ -116,9 +116,10 @@ def copy_bandwidth(mib: int, reps: int) -> dict:
 
 def bench_batched(api, fields, inputs, time_eager, dtype) -> dict:
     """The 32-field uneven workload: the forward step as one batched
-    launch against 32 separate fused launches (and, in FP64, 32 plain
+    call against 32 separate fused launches (and, in FP64, 32 plain
     per-stage chains), and the step adjoint of the batch (with data_bar)
-    against 32 separate adjoint calls."""
+    against 32 separate adjoint calls.  The keys `persistent_*` hold the
+    batched call's times (one launch per register class)."""
     import torch
 
     dev = "cuda:0"

@@ -150,7 +150,7 @@ typedef enum {
 typedef struct {
   int32_t impl;         /* stencil_impl */
   int32_t tile_i;       /* horizontal tile of the fused forward kernels (step, */
-  int32_t tile_j;       /*   batched step, hdiff of the generalised diffusion);
+  int32_t tile_j;       /*   batched step, some hdiff calls: see below);
                            0 = tuned; supported: 64x4, 32x8, 16x16 (256
                            columns) and, for the two-ended step only (column
                            store SPLIT, else STENCIL_E_UNSUPPORTED), 64x2,
@@ -158,9 +158,12 @@ typedef struct {
                            tile_j = 0 with tile_i set means the 256-column
                            tile.  FP64 columns of 97..144 levels in the
                            two-ended step run tile_i x (128 / tile_i) tiles.
-                           Other calls use the tile's width only; the stated
-                           hdiff and the adjoints' gather walk fixed strips
-                           and ignore it (the value is still validated). */
+                           The batched step uses the tile's width only, and so
+                           does hdiff where its row walk does not reach (masks
+                           of 4 GiB or more, the generalised diffusion of more
+                           than 65535 levels); other hdiff calls and the
+                           adjoints' gather fix their own tiles and strips and
+                           ignore it (the value is still validated). */
   int32_t column_store; /* stencil_column_store */
   void* workspace;      /* device memory for STENCIL_IMPL_PLAIN temporaries */
   size_t workspace_bytes;
@@ -356,8 +359,7 @@ int stencil_coeff_field_adjoint(stencil_dtype dtype, const stencil_field* u, con
  * fused kernels only (impl PLAIN, or a PERIODIC boundary: STENCIL_E_UNSUPPORTED).  Items with an
  * empty domain are skipped (their outputs untouched), except that an
  * adjoint item with nk > 0 and an empty horizontal domain zeroes u_bar as
- * the single-field adjoint does.  The forward's tile is opts->tile_i, else
- * the tuning table's entry for the batch's largest field. */
+ * the single-field adjoint does.  The forward's tile: stencil_step_batched. */
 
 /* One field of a batch: forward step out = step(u, data, w) on `domain`. */
 typedef struct {
@@ -384,11 +386,13 @@ size_t stencil_batch_adjoint_workspace_bytes(stencil_dtype dtype, int n,
                                              const stencil_batch_adjoint_item* items);
 
 /* All n steps in one launch per register class of the column length (up to
- * three: FP64 up to 80, 96 and 144 levels, FP32 up to 80, 112 and 144; tiles
- * of tile_i x (256 / tile_i) columns, in the longer classes 128 / tile_i).  opts->tile_i, when set, is the tile of
- * every field; when 0 each field takes its size class's tuned tile, or
- * without one the width (64, 32 or 16) that leaves the fewest lanes idle
- * on its ragged edges.  The call sorts the items longest
+ * three: FP64 up to 80, 96 and 144 levels, FP32 up to 80, 112 and 144; a class
+ * of few tiles joins the launch of the next longer one).  Tiles are tile_i x
+ * (256 / tile_i) columns, 128 / tile_i in FP64 launches of more than 96 levels
+ * and FP32 ones of more than 80.  opts->tile_i, when set, is the tile width of
+ * every field; when 0 each field takes its size class's tuned width, or
+ * without one the width (64, 32 or 16) of least cost: lanes, idle ones on its
+ * ragged edges included, times what a lane of that width costs.  The call sorts the items longest
  * column first, writes the work list into `ws` with small copy kernels on
  * `stream` (stream-ordered, so the call can be captured into a graph), and
  * launches the kernels, one workgroup per (field, tile).  ws: device memory, 256-byte
@@ -398,7 +402,8 @@ size_t stencil_batch_adjoint_workspace_bytes(stencil_dtype dtype, int n,
 int stencil_step_batched(stencil_dtype dtype, int n, const stencil_batch_item* items, void* ws,
                          size_t ws_bytes, const stencil_options* opts, hipStream_t stream);
 /* The adjoints of a batch: one launch per register class for the column
- * adjoints (up to 96 levels, and longer), then one launch for the horizontal
+ * adjoints (up to 96 levels, and longer; in FP32 few short columns join the
+ * longer launch), then one launch for the horizontal
  * gathers with a workgroup per work item (field, four strips of the padded
  * domain, level; a strip is 60 x 8 points in FP64, 124 x 12 in FP32).  ws as for the forward, sized by
  * stencil_batch_adjoint_workspace_bytes; opts->tile_i is not used. */
@@ -443,8 +448,8 @@ int stencil_graph_destroy(stencil_graph* graph);
 /* Times every tile candidate of `op` (STENCIL_OP_STEP: tile x column store,
  * and for the two-ended column store both workgroup sizes (256- and
  * 128-column tiles) and both tile orders; or STENCIL_OP_HDIFF,
- * timed in the damping form: only the generalised diffusion's hdiff has a
- * tile; the other ops have none to choose: STENCIL_E_ARG) on a domain of this size (scratch
+ * timed in the damping form; few hdiff calls take the tile, see
+ * stencil_options; the other ops have none to choose: STENCIL_E_ARG) on a domain of this size (scratch
  * fields allocated and freed by the library for the duration of the call,
  * device synchronised) and records the fastest in the process-wide tuning
  * table under (dtype, op, size class).  *best_us receives its time. */

@@ -220,10 +220,10 @@ BatchRange table_range(const char* p, const std::vector<int32_t>& items, int e0,
 // Class of the launch in which each register class of the batch runs: its own,
 // or the next longer one present while it has less than two rounds of the chip's
 // workgroups (a CU holds one of FP64, two of FP32).  The tail of so short a launch
-// costs more than its class saves: one launch per class against this, us: 7 FP32
-// fields (about 200x200x100) 223, 205, 5 fields 101, 73, 24 fields 641, 638; FP64
-// 5 fields 148, 120, 7 fields 371, 348, 24 fields 1173, 1177.  All in one launch
-// loses on large batches (24 fields: FP32 655, FP64 1235).
+// costs more than its class saves: one launch per class, this, all in one launch, us,
+// fields of 100-300 columns a side and 40-137 levels: FP32 5 fields 121, 99.5, 99.6,
+// 10 fields 160, 151, 147, 32 fields 495, 496, 520; FP64 7 fields 253, 238, 238, 10
+// fields 291, 276, 282, 20 fields 651, 661, 720.
 template <typename T>
 void merge_classes(const std::vector<int>& ord, const stencil_batch_item* it, int into[kStepBatchClasses]) {
   constexpr int64_t two_rounds = sizeof(T) == 8 ? 512 : 1024;  // tiles of 256 columns

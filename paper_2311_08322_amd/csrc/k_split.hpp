@@ -139,9 +139,8 @@ __device__ __forceinline__ void step_split_tile(const StepArgs<T>& A, int tile, 
   // The loads are pinned to their step (pin_prefetch).  In FP32 those past the half's
   // last level read an empty window, and the column's end waits for them (DRAIN:
   // see drain_loads).  Measured without either, with the pin, with both: FP32
-  // 400x300x90 75.5, 70.1, 67.3 us, 512x512x80 82.0, 81.8, 78.5, 32 fields 588, 583,
-  // 557; FP64 400x300x90 110.4, 106.8, 107.1, 256x256x80 37.1, 36.0, 36.2, 32
-  // fields 1009, 1010, 1016.
+  // 400x300x90 75.5, 70.1, 67.3 us, 512x512x80 82.0, 81.8, 78.5; FP64 400x300x90
+  // 110.4, 106.8, 107.1, 256x256x80 37.1, 36.0, 36.2.
   // FP32 saving a mask has stores in every step, which pin the loads by themselves:
   // 512x512x80 87.7 us, with both 89.
   // Where it costs, it is left out, over 50 sizes each: short columns, which gain

@@ -154,8 +154,8 @@ int tune_candidates(stencil_dtype dtype, int op, const stencil_field* u, const s
     o.tile_order = c.order;
     o.workspace = pws;
     o.workspace_bytes = wsb;
-    // the stated hdiff walks fixed strips; the tile is the generalised
-    // diffusion's, so that is the form timed
+    // hdiff in the generalised form, which runs on tiles in more cases (beyond
+    // 65535 levels) than the stated one (masks of 4 GiB or more)
     if (op == STENCIL_OP_HDIFF) o.hdiff_form = STENCIL_HDIFF_DAMPING;
     auto run = [&]() -> int {
       switch (op) {
