@@ -29,6 +29,7 @@ static bool by_tiles(const StepArgs<T>& A, bool var) {
   const int64_t strips = (A.ni + w - 1) / w * w, tiles = (A.ni + 31) / 32 * 32;
   const bool few = (int64_t)A.ni * A.nj * A.nk <= 1 << 22;
   if (A.nj > 1 << 26) return false;  // a grid counts its lanes in 32 bits
+  if (reinterpret_cast<uintptr_t>(A.mask) % 4) return false;  // tiles store whole words of it
   if (A.mask && few) return true;
   const int tenths = sizeof(T) == 8 ? (few ? 13 : 15) : var || A.mask ? 15 : 30;
   return 10 * strips >= tenths * tiles;

@@ -43,3 +43,18 @@ def test_forms(dims, dtype, aligned):
             if masked:
                 gx, gy = unpack_mask(mask, ni, nj, nk)
                 assert np.array_equal(gx, mx) and np.array_equal(gy, my)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+def test_byte_aligned_mask(dtype):
+    dims = (62, 17, 3)
+    f = inputs.fields_sized(*dims, seed=654)
+    u = fields.from_padded(f.u, dtype, DEV)
+    out = fields.alloc(*dims, dtype, DEV, halo=0, fill=0.0)
+    want = fields.mask_tensor(dims, DEV)
+    mask = torch.zeros(want.numel() + 4, dtype=torch.uint8, device=DEV)[3:-1]
+    assert mask.data_ptr() % 4 == 3
+    for m in (want, mask):
+        api.stencil_hdiff(u, out, dims, inputs.COEFF, mask=m)
+    torch.cuda.synchronize()
+    assert torch.equal(mask, want)
